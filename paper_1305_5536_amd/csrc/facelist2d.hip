@@ -32,8 +32,8 @@
 // ranges and entries, geometry, Pi(U^n), the first pass's slots) are issued
 // before the first barrier, so that their latency overlaps phase 0.
 // A stand-alone limiter kernel (k_fl_lim) serves dg_limit.  The discrete
-// adjoint of a step (k_adjfl_L, k_adjfl_lim) gathers over the global incidence
-// lists, one thread per cell.
+// adjoint of a step (k_adjfl_L, k_adjfl_lim, k_adjfl_msg) gathers over the
+// global incidence lists, one thread per cell.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,7 +44,6 @@
 
 #include "dg_internal.h"
 #include "dg_math.h"
-#include "dual.h"
 
 namespace dg {
 
@@ -745,11 +744,16 @@ hipError_t cfl_t(const dg_mesh* m, const void* U, hipStream_t s) {
 // Adjoint of a stage (as for the Cartesian meshes):
 //   out = Pi_P^T lamW,   lamW = c_id lam + c_L (dL/dW)^T lam + c_extra extra,
 // W = Pi(P), the branch the forward step takes (dt frozen).  k_adjfl_L gathers
-// lamW of a cell over its incidences and its volume points; k_adjfl_lim the
-// limiter transpose.  One thread per cell, no atomics; the flux and limiter
-// Jacobians come from forward-mode dual numbers through hll_n and the
-// limiter arithmetic, the linear parts (Gauss-point extrapolation, the
-// residual weights, M^-1) are transposed by hand.
+// lamW of a cell over its incidences and its volume points, k_adjfl_lim applies
+// the transpose of each cell's own limiter and leaves a message for the one
+// neighbour whose mean set a bound, k_adjfl_msg adds each cell's messages.  One
+// thread per cell, no atomics; the flux Jacobians come from one reverse sweep per
+// Gauss point (hll_n_vjp), the linear parts (Gauss-point extrapolation, residual
+// weights, M^-1) are transposed by hand.  The gathers' latency bounds all three.
+// Measured (262144 cells, FP64, one adjoint stage): k_adjfl_L 0.129 ms (0.214 ms
+// with a forward-mode solve per state component), k_adjfl_lim 0.044 and
+// k_adjfl_msg 0.017 ms (1.10 ms for differentiating, per coefficient, every
+// limiter that reads a cell).  The adjoint step 2.64 -> 0.42 ms.
 template <typename T>
 struct PFA {
   const T* W;      // Pi(P)
@@ -758,6 +762,8 @@ struct PFA {
   const T* extra;  // added to lamW with weight c_extra (may be NULL)
   const T* lamW;   // k_adjfl_lim input
   T* out;
+  T* msg;          // limiter messages: 4 values a cell
+  int* to;         // and the incidences they go through
   const double* dt_dev;
   double dt_host;
   double c_id, c_L_over_dt, c_extra;
@@ -795,20 +801,79 @@ __device__ __forceinline__ void cotangents(const T* lam, const T* cg, Cot<T>& c)
   }
 }
 
-// Both Cartesian Euler fluxes at one state (the volume term's point flux).
-template <typename S>
-__device__ __forceinline__ void euler_xy(const S* u, S gamma, S* Fx, S* Fy) {
-  const S ir = rcp(u[0]);
-  const S ux = u[1] * ir, uy = u[2] * ir;
-  const S pr = (gamma - S(1)) * (u[3] - S(0.5) * (u[1] * ux + u[2] * uy));
-  Fx[0] = u[1];
-  Fx[1] = u[1] * ux + pr;
-  Fx[2] = u[2] * ux;
-  Fx[3] = (u[3] + pr) * ux;
-  Fy[0] = u[2];
-  Fy[1] = u[1] * uy;
-  Fy[2] = u[2] * uy + pr;
-  Fy[3] = (u[3] + pr) * uy;
+// Vector-Jacobian product of hll_n on one side: ub is the cotangent of the state
+// of side `side` (0: uL, 1: uR) from the flux cotangent Fb, in one reverse sweep.
+// S_L and S_R take the left state on ties, as hll_n's min and max do.
+template <typename T>
+__device__ __forceinline__ void hll_n_vjp(const T* uL, const T* uR, T nx, T ny, T gamma,
+                                          const T* Fb, int side, T* ub) {
+  const T gm1 = gamma - T(1);
+  T ir[2], vx[2], vy[2], p[2], c[2], vn[2];
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const T* u = s == 0 ? uL : uR;
+    ir[s] = rcp(u[0]);
+    vx[s] = u[1] * ir[s];
+    vy[s] = u[2] * ir[s];
+    p[s] = gm1 * (u[3] - T(0.5) * (u[1] * vx[s] + u[2] * vy[s]));
+    c[s] = sqrt_pos(gamma * p[s] * ir[s]);
+    vn[s] = vx[s] * nx + vy[s] * ny;
+  }
+  const T l0 = vn[0] - c[0], l1 = vn[1] - c[1], r0 = vn[0] + c[0], r1 = vn[1] + c[1];
+  const bool loR = l1 < l0, hiR = r1 > r0;
+  const T SL = loR ? l1 : l0, SR = hiR ? r1 : r0;
+  const T inv = rcp(SR - SL);
+  const bool left = SL >= T(0), right = SR <= T(0), fan = !left && !right;
+  // Fb . F_L, Fb . F_R, Fb . (u_R - u_L)
+  const T g0 = Fb[1] * nx + Fb[2] * ny;
+  T dot[2], D = T(0);
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    const T* u = s == 0 ? uL : uR;
+    dot[s] = vn[s] * (Fb[0] * u[0] + Fb[1] * u[1] + Fb[2] * u[2] + Fb[3] * (u[3] + p[s])) +
+             g0 * p[s];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) D = fma(Fb[k], uR[k] - uL[k], D);
+  const T Q = (SR * dot[0] - SL * dot[1] + SL * SR * D) * inv;
+  const T SLb = fan ? (Q - dot[1] + SR * D) * inv : T(0);
+  const T SRb = fan ? (dot[0] - Q + SL * D) * inv : T(0);
+  // this side's weight of its own flux, of u_R - u_L, and its wave speeds
+  const T a = fan ? (side ? -SL : SR) * inv : ((side ? right : left) ? T(1) : T(0));
+  const T cu = fan ? (side ? SL : -SL) * SR * inv : T(0);
+  const T lb = (loR == (side == 1)) ? SLb : T(0), rb = (hiR == (side == 1)) ? SRb : T(0);
+  const T u0 = side ? uR[0] : uL[0], u1 = side ? uR[1] : uL[1], u2 = side ? uR[2] : uL[2];
+  const T u3 = side ? uR[3] : uL[3];
+  const T sir = side ? ir[1] : ir[0], svx = side ? vx[1] : vx[0], svy = side ? vy[1] : vy[0];
+  const T sp = side ? p[1] : p[0], svn = side ? vn[1] : vn[0], ics = rcp(side ? c[1] : c[0]);
+  const T G0 = a * Fb[0], G1 = a * Fb[1], G2 = a * Fb[2], G3 = a * Fb[3];
+  const T vnb = G0 * u0 + G1 * u1 + G2 * u2 + G3 * (u3 + sp) + lb + rb;
+  const T cb = T(0.5) * gamma * (rb - lb) * ics;  // c = sqrt(gamma p / rho)
+  const T pb = gm1 * (a * g0 + G3 * svn + cb * sir);
+  const T irb = cb * sp;
+  const T vxb = vnb * nx - T(0.5) * pb * u1, vyb = vnb * ny - T(0.5) * pb * u2;
+  ub[0] = G0 * svn - sir * (vxb * svx + vyb * svy + sir * irb) + cu * Fb[0];
+  ub[1] = G1 * svn + vxb * sir - T(0.5) * pb * svx + cu * Fb[1];
+  ub[2] = G2 * svn + vyb * sir - T(0.5) * pb * svy + cu * Fb[2];
+  ub[3] = G3 * svn + pb + cu * Fb[3];
+}
+
+// Volume term at one point: cotangent of the state u from those of its fluxes
+// along x and y (Fxb, Fyb).
+template <typename T>
+__device__ __forceinline__ void euler_xy_vjp(const T* u, T gamma, const T* Fxb, const T* Fyb,
+                                             T* ub) {
+  const T gm1 = gamma - T(1);
+  const T ir = rcp(u[0]);
+  const T vx = u[1] * ir, vy = u[2] * ir;
+  const T Ep = u[3] + gm1 * (u[3] - T(0.5) * (u[1] * vx + u[2] * vy));
+  const T pb = gm1 * (Fxb[1] + Fyb[2] + Fxb[3] * vx + Fyb[3] * vy);
+  const T vxb = Fxb[1] * u[1] + Fxb[2] * u[2] + Fxb[3] * Ep - T(0.5) * pb * u[1];
+  const T vyb = Fyb[1] * u[1] + Fyb[2] * u[2] + Fyb[3] * Ep - T(0.5) * pb * u[2];
+  ub[0] = -ir * (vxb * vx + vyb * vy);
+  ub[1] = Fxb[0] + Fxb[1] * vx + Fyb[1] * vy + vxb * ir - T(0.5) * pb * vx;
+  ub[2] = Fyb[0] + Fxb[2] * vx + Fyb[2] * vy + vyb * ir - T(0.5) * pb * vy;
+  ub[3] = Fxb[3] * vx + Fyb[3] * vy + pb;
 }
 
 template <typename T>
@@ -824,7 +889,6 @@ __global__ __launch_bounds__(256) void k_adjfl_L(PFA<T> p) {
   cotangents(le, cge, ce);
 #pragma unroll
   for (int k = 0; k < 12; ++k) g[k] = T(0);
-  const Dual<T> dgam(p.gamma, T(0));
   for (int i = p.inc0[e]; i < p.inc0[e + 1]; ++i) {
     const int fs = p.inc_face[i], f = fs >> 1, side = fs & 1;
     const int nb = side ? p.face_lr[2 * f] : p.face_lr[2 * f + 1];
@@ -860,21 +924,7 @@ __global__ __launch_bounds__(256) void k_adjfl_L(PFA<T> p) {
                           (cn.rm[v] + cn.rx[v] * rnx + cn.ry[v] * rny));
       }
       T ub[4];
-#pragma unroll 1
-      for (int k = 0; k < 4; ++k) {
-        Dual<T> dL[4], dR[4], F[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          dL[j] = Dual<T>(uL[j], T(side == 0 && j == k ? 1 : 0));
-          dR[j] = Dual<T>(uR[j], T(side == 1 && j == k ? 1 : 0));
-        }
-        bool bad = false;
-        hll_n(dL, dR, Dual<T>(nx, T(0)), Dual<T>(ny, T(0)), dgam, F, bad);
-        T acc = T(0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc = fma(Fb[j], F[j].d, acc);
-        ub[k] = acc;
-      }
+      hll_n_vjp(uL, uR, nx, ny, p.gamma, Fb, side, ub);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         g[3 * v] += ub[v];
@@ -892,17 +942,7 @@ __global__ __launch_bounds__(256) void k_adjfl_L(PFA<T> p) {
     T u[4], ub[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) u[v] = fma(we[3 * v + 1], ox, fma(we[3 * v + 2], oy, we[3 * v]));
-#pragma unroll 1
-    for (int k = 0; k < 4; ++k) {
-      Dual<T> du[4], Fx[4], Fy[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) du[j] = Dual<T>(u[j], T(j == k ? 1 : 0));
-      euler_xy(du, dgam, Fx, Fy);
-      T acc = T(0);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc = fma(ce.vx[j], Fx[j].d, fma(ce.vy[j], Fy[j].d, acc));
-      ub[k] = acc;
-    }
+    euler_xy_vjp(u, p.gamma, ce.vx, ce.vy, ub);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       g[3 * v] += ub[v];
@@ -920,70 +960,124 @@ __global__ __launch_bounds__(256) void k_adjfl_L(PFA<T> p) {
   }
 }
 
-// out_e = sum over the cells n whose limiter reads P_e (e itself and its face
-// neighbours, each counted once) of (d Pi_n / d P_e)^T lamW_n: the limiter of
-// k_fl_lim (bounds over the cell and its neighbours in the incidence order,
-// alpha = min over the incidences of psi at the face centroid) in dual numbers.
+// The limiter transpose Pi_P^T lamW of one cell's own limiter (that of k_fl_lim:
+// bounds over the cell and its neighbours in the incidence order, alpha = min
+// over the incidences of psi at the face centroid, the first on ties): writes
+// the adjoint of its gradients and the part its own mean takes, and per variable
+// a message for the neighbour whose mean set the bound.  msg[v * nc + e] holds
+// the value, to[v * nc + e] the incidence code (face << 1 | side) through which
+// the cell sees that neighbour, -1 for no message.
 template <typename T>
 __global__ __launch_bounds__(256) void k_adjfl_lim(PFA<T> p) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
+  const int e = xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   if (e >= p.nc) return;
-  T out[12];
+  T q[12], lw[12];
+  load12(p.P, p.nc, e, q);
+  load12(p.lamW, p.nc, e, lw);
+  T hi[4], lo[4];
+  int ihi[4], ilo[4];
 #pragma unroll
-  for (int k = 0; k < 12; ++k) out[k] = T(0);
-  const int e0 = p.inc0[e], e1 = p.inc0[e + 1];
-  for (int ci = e0 - 1; ci < e1; ++ci) {
-    const int n = ci < e0 ? e : p.nbr[ci];
-    bool seen = ci >= e0 && n == e;
-    for (int cj = e0; cj < ci && !seen; ++cj) seen = p.nbr[cj] == n;
-    if (seen) continue;
-    const int n0 = p.inc0[n], n1 = p.inc0[n + 1];
-    bool reads_e = n == e;
-    for (int i = n0; i < n1; ++i) reads_e |= p.nbr[i] == e;
-    if (!reads_e) continue;
-    T pn[12], lw[12];
-    load12(p.P, p.nc, n, pn);
-    load12(p.lamW, p.nc, n, lw);
-#pragma unroll 1
-    for (int k = 0; k < 12; ++k) {
-      // the mean slot of coefficient k (-1: a gradient, read by the own limiter only)
-      const int ks = k % 3 == 0 ? k / 3 : -1;
-      if (n != e && ks < 0) continue;
-      Dual<T> q[12], hi[4], lo[4], al[4];
+  for (int v = 0; v < 4; ++v) {
+    hi[v] = lo[v] = q[3 * v];
+    ihi[v] = ilo[v] = -1;
+  }
+  // incidences kBatch at a time with their loads in flight, as k_fl_lim does
+  constexpr int kBatch = 8;
+  const int i0 = p.inc0[e], i1 = p.inc0[e + 1];
+  for (int b0 = i0; b0 < i1; b0 += kBatch) {
+    int nb[kBatch];
 #pragma unroll
-      for (int j = 0; j < 12; ++j) q[j] = Dual<T>(pn[j], T(n == e && j == k ? 1 : 0));
+    for (int u = 0; u < kBatch; ++u) nb[u] = b0 + u < i1 ? p.nbr[b0 + u] : e;
+    T m[kBatch][4];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        hi[v] = lo[v] = q[3 * v];
-        al[v] = Dual<T>(1.0);
-      }
-      for (int i = n0; i < n1; ++i) {
-        const int m = p.nbr[i];
+    for (int u = 0; u < kBatch; ++u)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const Dual<T> mv(p.P[(size_t)(3 * v) * p.nc + m], T(m == e && v == ks ? 1 : 0));
-          hi[v] = fmax(hi[v], mv);
-          lo[v] = fmin(lo[v], mv);
-        }
-      }
-      for (int i = n0; i < n1; ++i) {
-        const Dual<T> rx(p.lim_geo[2 * (size_t)i], T(0)), ry(p.lim_geo[2 * (size_t)i + 1], T(0));
+      for (int v = 0; v < 4; ++v) m[u][v] = p.P[(3 * v) * p.nc + nb[u]];
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          al[v] = fmin(al[v], psi_of(q[3 * v + 1] * rx + q[3 * v + 2] * ry, q[3 * v], hi[v], lo[v]));
-      }
-      T acc = T(0);
+    for (int u = 0; u < kBatch; ++u)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        acc = fma(lw[3 * v], q[3 * v].d, acc);
-        acc = fma(lw[3 * v + 1], (al[v] * q[3 * v + 1]).d, acc);
-        acc = fma(lw[3 * v + 2], (al[v] * q[3 * v + 2]).d, acc);
+        ihi[v] = m[u][v] > hi[v] ? b0 + u : ihi[v];
+        ilo[v] = m[u][v] < lo[v] ? b0 + u : ilo[v];
+        hi[v] = fmax(hi[v], m[u][v]);
+        lo[v] = fmin(lo[v], m[u][v]);
       }
-      out[k] += acc;
+  }
+  // alpha and the increment d = g . r of the face that sets it (d = 0: none)
+  T al[4], da[4], rx[4], ry[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    al[v] = T(1);
+    da[v] = rx[v] = ry[v] = T(0);
+  }
+  for (int b0 = i0; b0 < i1; b0 += kBatch) {
+    T ox[kBatch], oy[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = b0 + u < i1 ? b0 + u : b0;
+      ox[u] = p.lim_geo[2 * (size_t)i];
+      oy[u] = p.lim_geo[2 * (size_t)i + 1];
     }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const T d = q[3 * v + 1] * ox[u] + q[3 * v + 2] * oy[u];
+        const T psi = psi_of(d, q[3 * v], hi[v], lo[v]);
+        const bool set = psi < al[v];
+        al[v] = set ? psi : al[v];
+        da[v] = set ? d : da[v];
+        rx[v] = set ? ox[u] : rx[v];
+        ry[v] = set ? oy[u] : ry[v];
+      }
   }
 #pragma unroll
-  for (int k = 0; k < 12; ++k) p.out[(size_t)k * p.nc + e] = out[k];
+  for (int v = 0; v < 4; ++v) {
+    // psi = (bound - phi) / d: bound with cotangent ab / d, d with -psi ab / d
+    const bool act = da[v] != T(0), up = da[v] > T(0);
+    const T ab = lw[3 * v + 1] * q[3 * v + 1] + lw[3 * v + 2] * q[3 * v + 2];
+    const T ad = fabs(da[v]);
+    const T w = act ? div_small(up ? ab : -ab, ad) : T(0);
+    const int to = up ? ihi[v] : ilo[v];
+    const bool send = act && to >= 0;
+    p.out[(size_t)(3 * v) * p.nc + e] = lw[3 * v] - (send ? w : T(0));
+    p.out[(size_t)(3 * v + 1) * p.nc + e] = al[v] * (lw[3 * v + 1] - w * rx[v]);
+    p.out[(size_t)(3 * v + 2) * p.nc + e] = al[v] * (lw[3 * v + 2] - w * ry[v]);
+    p.msg[(size_t)v * p.nc + e] = w;
+    p.to[(size_t)v * p.nc + e] = send ? p.inc_face[to] : -1;
+  }
+}
+
+// Adds to each mean adjoint the messages of its face neighbours: the neighbour
+// across incidence (face << 1 | side) sees this cell through that code with the
+// side flipped (also where a cell is its own neighbour or shares two faces).
+template <typename T>
+__global__ __launch_bounds__(256) void k_adjfl_msg(PFA<T> p) {
+  const int e = xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+  if (e >= p.nc) return;
+  T add[4] = {T(0), T(0), T(0), T(0)};
+  constexpr int kBatch = 4;
+  const int i0 = p.inc0[e], i1 = p.inc0[e + 1];
+  for (int b0 = i0; b0 < i1; b0 += kBatch) {
+    int nb[kBatch], c[kBatch], to[kBatch][4];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = b0 + u < i1 ? b0 + u : i0;
+      nb[u] = p.nbr[i];
+      c[u] = b0 + u < i1 ? (p.inc_face[i] ^ 1) : -2;
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) to[u][v] = p.to[(size_t)v * p.nc + nb[u]];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (to[u][v] == c[u]) add[v] += p.msg[(size_t)v * p.nc + nb[u]];
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) p.out[(size_t)(3 * v) * p.nc + e] += add[v];
 }
 
 template <typename T>
@@ -1029,7 +1123,11 @@ hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const doub
     b.P = static_cast<const T*>(P);
     b.lamW = static_cast<const T*>(ws2);
     b.out = static_cast<T*>(out);
+    // W is no longer needed: its workspace takes the messages
+    b.msg = static_cast<T*>(ws1);
+    b.to = reinterpret_cast<int*>(b.msg + (size_t)4 * f.ncells);
     hipLaunchKernelGGL((k_adjfl_lim<T>), grid, block, 0, s, b);
+    hipLaunchKernelGGL((k_adjfl_msg<T>), grid, block, 0, s, b);
     return hipGetLastError();
   };
   // stage 2: lam_V1 = Pi_V1^T [lam'/2 + (dt/2) L^T lam'] (in lam_n with the

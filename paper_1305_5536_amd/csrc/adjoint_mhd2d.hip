@@ -11,30 +11,33 @@
 //   W = Pi(P),
 // stage 2: P = V1, lam = lam', c_id = 1/2, c_L = dt/2; stage 1: P = U,
 // lam = lam_V1, c_id = 1, c_L = dt, extra = lam' with c_extra = 1/2.  Each
-// runs the forward limiter (k_lim2m) into a workspace and two gather kernels,
+// runs the forward limiter (k_lim2m) into a workspace and three gather kernels,
 // one thread per cell, no atomics:
 //   k_adj2m_L    lamW of a cell from its four faces (two Gauss points each)
 //                and its four volume points.  The cotangent of a face flux is
 //                the transpose of the linear residual weights (the same
 //                algebra as the forward accumulation) applied to the adjoints
-//                of both adjacent cells; the Jacobian of the flux with respect
-//                to this cell's Gauss-point state comes from forward-mode dual
-//                numbers through the HLLD solver, one direction per state
-//                component; the extrapolation to the Gauss point is
+//                of both adjacent cells; one reverse sweep through the HLLD
+//                flux (hlld_vjp) gives the cotangent of this cell's
+//                Gauss-point state; the extrapolation to the Gauss point is
 //                transposed by hand (it is linear).
-//   k_adj2m_lim  the limiter transpose: the cell's own limiter differentiated
-//                in each of its 23 coefficients, plus what each neighbour's
-//                limiter takes from this cell's means (the bounds), by dual
-//                numbers.
-// Not tuned for speed: each face flux is differentiated from both sides (64
-// dual HLLD solves per cell and adjoint stage, against 4 HLLD solves per cell
-// in a forward stage).
+//   k_adj2m_lim  the transpose of the cell's own limiter: everything it hands
+//                back to its own coefficients, and a message per limited
+//                variable (a value and a direction) for the one neighbour whose
+//                mean set the bound.
+//   k_adj2m_msg  each cell adds the messages of its four neighbours.
+// FP64 instruction issue bounds k_adj2m_L (each face from both sides: eight
+// reverse sweeps a cell), memory traffic the other two.  Measured (512^2, FP64,
+// one adjoint stage): k_adj2m_L 0.168 ms; with one forward-mode solve per state
+// component it took 0.901 ms.  k_adj2m_lim 0.030 and k_adj2m_msg 0.011 ms;
+// differentiating every limiter that reads a cell, component by component, took
+// 0.410 ms.  The adjoint step 2.59 -> 0.44 ms.
 #include <hip/hip_runtime.h>
 
 #include "dg_internal.h"
 #include "dg_math.h"
-#include "dual.h"
-#include "mhd_hlld.h"
+#include "limiter_vjp.h"
+#include "mhd_hlld_vjp.h"
 
 namespace dg {
 
@@ -65,6 +68,8 @@ struct PJ {
   const T* extra;  // added to lamW with weight c_extra (may be NULL)
   const T* lamW;   // k_adj2m_lim input
   T* out;
+  T* msg;          // limiter messages: 6 values a cell
+  unsigned* code;  // and their directions
   const double* dt_dev;
   double dt_host;
   double c_id, c_L_over_dt, c_extra;
@@ -199,56 +204,14 @@ __device__ void face_adjoint(const T* ce, const AccBar<T>& ae, const T* cn, cons
     }
     flux_bar<T, D>(ae, s, sge, p, Fb);
     flux_bar<T, D>(an, s, -sge, p, Fb);
-    // the Jacobian of the flux on this cell's side, one direction at a time;
-    // the normal field enters through the average of both sides
-    T ub[8];
-#pragma unroll 1
-    for (int k = 0; k < 8; ++k) {
-      Dual<T> dL[8], dR[8], F[8];
+    const T bn = T(0.5) * (uL[5 + D] + uR[5 + D]);
+    uL[5 + D] = uR[5 + D] = bn;
+    T ub[8], bL[8], bR[8];
+    hlld_vjp<T, D>(uL, uR, p.gamma, p.eps, Fb, bL, bR);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        dL[j] = Dual<T>(uL[j], T(side == 0 && j == k ? 1 : 0));
-        dR[j] = Dual<T>(uR[j], T(side == 1 && j == k ? 1 : 0));
-      }
-      const Dual<T> bn = Dual<T>(0.5) * (dL[5 + D] + dR[5 + D]);
-      dL[5 + D] = bn;
-      dR[5 + D] = bn;
-      bool bad = false;
-      hlld_axis<Dual<T>, D>(dL, dR, Dual<T>(p.gamma, T(0)), Dual<T>(p.eps, T(0)), F, bad);
-      T acc = T(0);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) acc = fma(Fb[j], F[j].d, acc);
-      ub[k] = acc;
-    }
+    for (int k = 0; k < 8; ++k) ub[k] = side == 0 ? bL[k] : bR[k];
     point_state_bar<T, D>(ub, he, ht, g);
   }
-}
-
-// Volume fluxes at one point: fe[e][v] the hydro flux along axis e, and the
-// induction fluxes F_y(Bx) (= -F_x(By)), F_x(Bz), F_y(Bz).
-template <typename S>
-__device__ __forceinline__ void volume_flux(const S* u, const S* B, S gamma, S (*fe)[5],
-                                            S* ind) {
-  const S ir = rcp(u[0]);
-  const S vel[3] = {u[1] * ir, u[2] * ir, u[3] * ir};
-  const S pm = S(0.5) * (B[0] * B[0] + B[1] * B[1] + B[2] * B[2]);
-  const S pg =
-      (gamma - S(1)) * (u[4] - S(0.5) * (u[1] * vel[0] + u[2] * vel[1] + u[3] * vel[2]) - pm);
-  const S pT = pg + pm;
-  const S vB = vel[0] * B[0] + vel[1] * B[1] + vel[2] * B[2];
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    fe[e][0] = u[1 + e];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      fe[e][1 + k] = u[1 + k] * vel[e] - B[k] * B[e];
-      if (k == e) fe[e][1 + k] = fe[e][1 + k] + pT;
-    }
-    fe[e][4] = (u[4] + pT) * vel[e] - B[e] * vB;
-  }
-  ind[0] = B[0] * vel[1] - vel[0] * B[1];
-  ind[1] = B[2] * vel[0] - vel[2] * B[0];
-  ind[2] = B[2] * vel[1] - vel[2] * B[1];
 }
 
 // Volume term of cell e over the 2x2 Gauss points: adds its contribution to
@@ -269,26 +232,9 @@ __device__ void volume_adjoint(const T* ce, const AccBar<T>& ae, const PJ<T>& p,
   for (int gp = 0; gp < 4; ++gp) {
     const T o0 = (gp & 2) ? p.q[0] : -p.q[0];
     const T o1 = (gp & 1) ? p.q[1] : -p.q[1];
-    T u[8];
+    T u[8], ub[8];
     point_state<T, 0>(ce, o0, o1, u);
-    T ub[8];
-#pragma unroll 1
-    for (int k = 0; k < 8; ++k) {
-      Dual<T> du[5], dB[3], fe[2][5], ind[3];
-#pragma unroll
-      for (int j = 0; j < 5; ++j) du[j] = Dual<T>(u[j], T(j == k ? 1 : 0));
-#pragma unroll
-      for (int j = 0; j < 3; ++j) dB[j] = Dual<T>(u[5 + j], T(5 + j == k ? 1 : 0));
-      volume_flux(du, dB, Dual<T>(p.gamma, T(0)), fe, ind);
-      T acc = T(0);
-#pragma unroll
-      for (int e = 0; e < 2; ++e)
-#pragma unroll
-        for (int v = 0; v < 5; ++v) acc = fma(feb[e][v], fe[e][v].d, acc);
-#pragma unroll
-      for (int j = 0; j < 3; ++j) acc = fma(indb[j], ind[j].d, acc);
-      ub[k] = acc;
-    }
+    mhd_flux_vjp<T, 2>(u, p.gamma, feb, indb[0], -indb[1], -indb[2], ub);
     point_state_bar<T, 0>(ub, o0, o1, g);
   }
 }
@@ -331,95 +277,119 @@ __global__ __launch_bounds__(256) void k_adj2m_L(PJ<T> p) {
   }
 }
 
-// The limiter of Sec. 2.5 on one cell from its 23 coefficients c and the
-// means of its neighbours nbm (order -x, +x, -y, +y; rho, mx, my, mz, E, Bx,
-// By, Bz), in the forward kernels' arithmetic.
-template <typename S, typename T>
-__device__ __forceinline__ S alpha_of(S phi, S hi, S lo, S gx, S gy, T hx2, T hy2) {
-  const S D = fmin(hi - phi, phi - lo);
-  const S dm = fmax(fabs(gx) * S(hx2), fabs(gy) * S(hy2));
-  return (dm > D) ? div_small(D, dm) : S(1);
-}
-
-template <typename S, typename T>
-__device__ __forceinline__ void limit_cell(S* c, const S (*nbm)[8], T hx2, T hy2) {
-  S hi[8], lo[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) hi[k] = lo[k] = c[mean_index(k)];
-#pragma unroll
-  for (int f = 0; f < 4; ++f)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      hi[k] = fmax(hi[k], nbm[f][k]);
-      lo[k] = fmin(lo[k], nbm[f][k]);
-    }
-#pragma unroll
-  for (int v = 0; v < 5; ++v) {
-    const S a = alpha_of(c[3 * v], hi[v], lo[v], c[3 * v + 1], c[3 * v + 2], hx2, hy2);
-    c[3 * v + 1] = c[3 * v + 1] * a;
-    c[3 * v + 2] = c[3 * v + 2] * a;
-  }
-  S aB = S(1);
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-    aB = fmin(aB, alpha_of(c[15 + k], hi[5 + k], lo[5 + k], S(T(bs(k, 0))) * c[18 + bj(k, 0)],
-                           S(T(bs(k, 1))) * c[18 + bj(k, 1)], hx2, hy2));
-#pragma unroll
-  for (int j = 0; j < 5; ++j) c[18 + j] = c[18 + j] * aB;
-}
-
-// out_e = sum over the cells n whose limiter reads P_e (e itself and its face
-// neighbours, each counted once) of (d Pi_n / d P_e)^T lamW_n.
+// The limiter transpose Pi_P^T lamW of one cell's own limiter: writes the
+// adjoint of its gradients, field coefficients and the part its own mean takes,
+// and, for the six limited variables (rho .. E, the field), the message to the
+// neighbour whose mean set the bound: a value and the neighbour's direction.
+// msg[s * nc + e] holds slot s, the codes of a cell 4 bits a slot (0: none,
+// 1 + direction), the field component of slot 5 in bits 24 and 25.
 template <typename T>
 __global__ __launch_bounds__(256) void k_adj2m_lim(PJ<T> p) {
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= p.nc) return;
-  int cand[5];
-  cand[0] = e;
-  neighbours(e, p.nx, p.ny, cand + 1);
-  T out[23];
+  int nb[4];
+  neighbours(e, p.nx, p.ny, nb);
+  T c[23], lw[23];
+  load23(p.P, p.nc, e, c);
+  load23(p.lamW, p.nc, e, lw);
+  unsigned code = 0;
+  auto put = [&](int k, T x) { p.out[(size_t)k * p.nc + e] = x; };
 #pragma unroll
-  for (int k = 0; k < 23; ++k) out[k] = T(0);
-#pragma unroll 1
-  for (int ci = 0; ci < 5; ++ci) {
-    const int n = cand[ci];
-    bool seen = false;
-    for (int cj = 0; cj < ci; ++cj) seen |= cand[cj] == n;
-    if (seen) continue;
-    int nn[4];
-    neighbours(n, p.nx, p.ny, nn);
-    T cn[23], lw[23], nbm[4][8];
-    load23(p.P, p.nc, n, cn);
-    load23(p.lamW, p.nc, n, lw);
+  for (int v = 0; v < 5; ++v) {
+    T m[4];
 #pragma unroll
-    for (int f = 0; f < 4; ++f)
-#pragma unroll
-      for (int k = 0; k < 8; ++k) nbm[f][k] = p.P[(size_t)mean_index(k) * p.nc + nn[f]];
-#pragma unroll 1
-    for (int k = 0; k < 23; ++k) {
-      // the mean slot of coefficient k (-1: a gradient or field coefficient,
-      // which only the cell's own limiter reads)
-      const int ks = k < 15 ? (k % 3 == 0 ? k / 3 : -1) : (k < 18 ? k - 10 : -1);
-      bool any = n == e;
-      for (int f = 0; f < 4; ++f) any |= ks >= 0 && nn[f] == e;
-      if (!any) continue;
-      Dual<T> c[23], m[4][8];
-#pragma unroll
-      for (int j = 0; j < 23; ++j) c[j] = Dual<T>(cn[j], T(n == e && j == k ? 1 : 0));
-#pragma unroll
-      for (int f = 0; f < 4; ++f)
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          m[f][j] = Dual<T>(nbm[f][j], T(nn[f] == e && j == ks ? 1 : 0));
-      limit_cell(c, m, p.half[0], p.half[1]);
-      T acc = T(0);
-#pragma unroll
-      for (int j = 0; j < 23; ++j) acc = fma(lw[j], c[j].d, acc);
-      out[k] += acc;
+    for (int f = 0; f < 4; ++f) m[f] = p.P[(size_t)(3 * v) * p.nc + nb[f]];
+    const T* g = c + 3 * v + 1;
+    const auto r = limiter_decide<T, 2>(c[3 * v], m, g, p.half);
+    T gb[2] = {r.alpha * lw[3 * v + 1], r.alpha * lw[3 * v + 2]};
+    const T b = limiter_bar<T, 2>(r, lw[3 * v + 1] * g[0] + lw[3 * v + 2] * g[1], g, p.half, gb);
+    const bool send = r.act && r.nbr != 0;
+    put(3 * v, lw[3 * v] - (send ? b : T(0)));
+    put(3 * v + 1, gb[0]);
+    put(3 * v + 2, gb[1]);
+    if (send) {
+      code |= (unsigned)r.nbr << (4 * v);
+      p.msg[(size_t)v * p.nc + e] = b;
     }
   }
+  // the field: one alpha, the smallest of the components' (the first on ties)
+  LimDecision<T> rB{};
+  rB.alpha = T(1);
+  T gB[2] = {T(0), T(0)};
+  int cB = 0;
 #pragma unroll
-  for (int k = 0; k < 23; ++k) p.out[(size_t)k * p.nc + e] = out[k];
+  for (int k = 0; k < 3; ++k) {
+    T m[4];
+#pragma unroll
+    for (int f = 0; f < 4; ++f) m[f] = p.P[(size_t)(15 + k) * p.nc + nb[f]];
+    const T g[2] = {T(bs(k, 0)) * c[18 + bj(k, 0)], T(bs(k, 1)) * c[18 + bj(k, 1)]};
+    const auto r = limiter_decide<T, 2>(c[15 + k], m, g, p.half);
+    if (r.alpha < rB.alpha) {
+      rB = r;
+      gB[0] = g[0];
+      gB[1] = g[1];
+      cB = k;
+    }
+  }
+  T ab = T(0), fb[5];
+#pragma unroll
+  for (int j = 0; j < 5; ++j) {
+    ab = fma(lw[18 + j], c[18 + j], ab);
+    fb[j] = rB.alpha * lw[18 + j];
+  }
+  T gb[2] = {T(0), T(0)};
+  const T b = limiter_bar<T, 2>(rB, ab, gB, p.half, gb);
+#pragma unroll
+  for (int k = 0; k < 3; ++k)
+#pragma unroll
+    for (int d = 0; d < 2; ++d) fb[bj(k, d)] += k == cB ? T(bs(k, d)) * gb[d] : T(0);
+  const bool send = rB.act && rB.nbr != 0;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) put(15 + k, lw[15 + k] - (send && k == cB ? b : T(0)));
+#pragma unroll
+  for (int j = 0; j < 5; ++j) put(18 + j, fb[j]);
+  if (send) {
+    code |= ((unsigned)rB.nbr << 20) | ((unsigned)cB << 24);
+    p.msg[(size_t)5 * p.nc + e] = b;
+  }
+  p.code[e] = code;
+}
+
+// Adds to each mean adjoint the messages its face neighbours sent it.  A
+// message of cell n in direction g arrives at n's neighbour there, which sees n
+// in the opposite direction g ^ 1 (also where a cell is its own neighbour).
+template <typename T>
+__global__ __launch_bounds__(256) void k_adj2m_msg(PJ<T> p) {
+  const int e = blockIdx.x * 256 + threadIdx.x;
+  if (e >= p.nc) return;
+  int nb[4];
+  neighbours(e, p.nx, p.ny, nb);
+  unsigned code[4];
+#pragma unroll
+  for (int f = 0; f < 4; ++f) code[f] = p.code[nb[f]];
+  T add[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) add[k] = T(0);
+  unsigned hit = 0;
+#pragma unroll
+  for (int f = 0; f < 4; ++f)
+#pragma unroll
+    for (int s = 0; s < 6; ++s)
+      if (((code[f] >> (4 * s)) & 15u) == (unsigned)((f ^ 1) + 1)) {
+        const T x = p.msg[(size_t)s * p.nc + nb[f]];
+        const int cB = (int)(code[f] >> 24);
+        if (s < 5) {
+          add[s] += x;
+          hit |= 1u << s;
+        } else {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) add[5 + k] += k == cB ? x : T(0);
+          hit |= 32u << cB;
+        }
+      }
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (hit >> k & 1u) p.out[(size_t)mean_index(k) * p.nc + e] += add[k];
 }
 
 template <typename T>
@@ -481,7 +451,11 @@ hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const doub
     b.P = static_cast<const T*>(P);
     b.lamW = static_cast<const T*>(ws2);
     b.out = static_cast<T*>(out);
+    // W is no longer needed: its workspace takes the messages
+    b.msg = static_cast<T*>(ws1);
+    b.code = reinterpret_cast<unsigned*>(b.msg + (size_t)6 * m->ncells);
     hipLaunchKernelGGL((k_adj2m_lim<T>), grid, block, 0, s, b);
+    hipLaunchKernelGGL((k_adj2m_msg<T>), grid, block, 0, s, b);
     return hipGetLastError();
   };
   // stage 2: lam_V1 = Pi_V1^T [lam'/2 + (dt/2) L^T lam'] (in lam_n with the

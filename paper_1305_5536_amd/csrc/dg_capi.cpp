@@ -73,164 +73,160 @@ hipError_t launch_cart3d_cfl(const dg_mesh* m, const void* U, double cfl, double
 int64_t max_stage_waves3(const dg_mesh* m);
 int64_t stage_groups3(int tiles_x, int ny);
 
-// Rows (2D) or planes (3D) marched by one wave.  Chosen so a launch has
-// several waves per SIMD on 256 CUs.  The DG_TILE_ROWS environment variable
-// overrides this and every model-based default below for the whole process
-// (launch-shape experiments; dg_set_tiling, which the autotuner uses, takes
-// precedence over both).
-static int default_rows(int64_t ntiles_x, int64_t nrows) {
-  const char* env = std::getenv("DG_TILE_ROWS");
-  if (env) {
-    int r = std::atoi(env);
-    if (r > 0) return r;
+// Launch shapes of the row-marching kernels.  A wave that marches R rows (or
+// planes) takes R + c row times, c the rows it marches beyond its own plus the
+// fixed cost of a launch, and W waves over the chip's SIMDs put
+// w = ceil(W / SIMDs) on the fullest one.  Where the registers allow one wave
+// per SIMD these run one after the other, and the launch costs w (R + c); waves
+// that share a SIMD hide each other's latency, and the launch costs less than
+// that (the load functions below, fitted to sweeps of R).  So few long waves pay
+// on large meshes, where w is set by the mesh, and one row per wave on small
+// ones, which leave SIMDs idle.  The DG_TILE_ROWS environment variable replaces
+// every default below for the whole process (launch-shape experiments;
+// dg_set_tiling, which the autotuner uses, takes precedence over it).
+static int64_t simds() {
+  int dev = 0, cus = 256;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+      cus <= 0) {
+    (void)hipGetLastError();
+    cus = 256;
   }
-  // target >= 4096 waves when the mesh allows, rows in [4, 64]
-  int64_t want_tiles = 4096;
-  int64_t rows = (ntiles_x * nrows + want_tiles - 1) / want_tiles;
-  if (rows < 4) rows = 4;
-  if (rows > 64) rows = 64;
-  if (rows > nrows) rows = nrows;
+  return (int64_t)cus * 4;
+}
+
+static int env_rows() {
+  const char* env = std::getenv("DG_TILE_ROWS");
+  const int r = env ? std::atoi(env) : 0;
+  return r > 0 ? r : 0;
+}
+
+// Relative cost of w waves on one SIMD: `pair` for two that run together, the
+// pairs one after the other; or each further wave at `more` of the first.
+static double load_pairs(int64_t w, double pair) { return (double)(w / 2) * pair + (double)(w % 2); }
+static double load_shared(int64_t w, double more) { return 1.0 + more * (double)(w - 1); }
+
+// The R in [1, most] with the least (R + c) load(waves(R)).
+template <typename Waves, typename Load>
+static int best_rows(int64_t nrows, int64_t most, double c, Waves waves, Load load) {
+  double best = 1e300;
+  int64_t rows = 1;
+  for (int64_t r = 1; r <= std::min(nrows, most); ++r) {
+    const double cost = load(waves(r)) * ((double)r + c);
+    if (cost < best - 1e-9) {
+      best = cost;
+      rows = r;
+    }
+  }
   return (int)rows;
 }
 
-// Rows per tile of every instance of a batch: 16 (DG_TILE_ROWS overrides).
-static int default_batch_rows() {
-  const char* env = std::getenv("DG_TILE_ROWS");
-  return env && std::atoi(env) > 0 ? std::atoi(env) : 16;
+static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Waves of the stage kernels, stage 1 + stage 2 in FP64 (two waves per SIMD and
+// one, by registers), two per SIMD in FP32.
+static double load_stages(int64_t waves, bool f64) {
+  const int64_t n = simds();
+  return f64 ? (double)(ceil_div(waves, 2 * n) + ceil_div(waves, n))
+             : load_shared(ceil_div(waves, n), 0.42);
 }
 
-// Planes per workgroup of the 3D stage kernel (DG_TILE_ROWS overrides): one
-// workgroup per CU in FP64 and two in FP32 (set by the LDS), so P in [4, 64]
-// minimises rounds x (P + 1), a workgroup of P planes costing about P + 1
+// Rows per tile of every instance of a batch (stage kernels).  Measured (RK2
+// step, against the fixed 16 rows of before): 24 instances of 64..512 cells a
+// side FP32 10 rows 125 against 129 us, FP64 16 rows either way; 64 such FP32
+// 10 rows 308 against 313 us; 12 of 60..300 FP32 4 rows 48 against 95 us, FP64
+// 8 rows 72 against 116; 3 of 64..128 one row 18 against 88 us.
+static int default_batch_rows(const BatchDesc& d, bool f64) {
+  if (env_rows()) return env_rows();
+  int64_t ny = 1;
+  for (int i = 0; i < d.ninst; ++i) ny = std::max<int64_t>(ny, d.ny[i]);
+  auto waves = [&](int64_t r) {
+    int64_t n = 0;
+    for (int i = 0; i < d.ninst; ++i)
+      n += ceil_div(d.nx[i], 60) * ceil_div(d.ny[i], std::min<int64_t>(r, d.ny[i]));
+    return n;
+  };
+  return best_rows(ny, 64, 2.2, waves, [&](int64_t w) { return load_stages(w, f64); });
+}
+
+// Rows per wave of the 2D Euler adjoint kernel over all instances: four rows
+// beyond its own; FP64 one wave per SIMD, FP32 two, which cost 1.5 times one.
+// Measured (adjoint step, against 16 rows): 3 instances of 64..128 cells a side
+// one row, FP32 53 against 232 us, FP64 70 against 293; 12 of 60..300 FP32 4 rows
+// 134 against 249, FP64 8 rows 199 against 313; 24 of 64..512 FP32 16 rows, FP64
+// 32 rows 625 against 676; 64 of 64..512 FP32 40 rows 806 against 923 us.
+static int default_adjoint_rows(const BatchDesc& d, bool f64) {
+  int64_t ny = 1;
+  for (int i = 0; i < d.ninst; ++i) ny = std::max<int64_t>(ny, d.ny[i]);
+  auto waves = [&](int64_t r) {
+    int64_t n = 0;
+    for (int i = 0; i < d.ninst; ++i)
+      n += ceil_div(d.nx[i], kAdjCols) * ceil_div(d.ny[i], std::min<int64_t>(r, d.ny[i]));
+    return n;
+  };
+  const int64_t n = simds();
+  return best_rows(ny, kAdjRowsMax, 3.4, waves, [&](int64_t w) {
+    return f64 ? (double)ceil_div(w, n) : load_pairs(ceil_div(w, n), 1.5);
+  });
+}
+
+// Planes per workgroup of the 3D stage kernel: one workgroup per CU in FP64 and
+// two in FP32 (set by the LDS), a workgroup of P planes costing about P + 1
 // plane times (its prologue solves one extra z-face) (256^3: FP64 64 planes,
 // five rounds of 256; FP32 32 planes, five rounds of 512, 8.81 against 9.19 ms
-// per step at 64).
+// per step at 64; 32^3: one plane, 0.093 against 0.222 ms at 4 planes FP64, 0.062
+// against 0.150 FP32; 45^3 FP64 three planes, 0.194 against 0.238).
 static int default_planes3d(int tiles_x, int ny, int64_t nz, bool f64) {
-  const char* env = std::getenv("DG_TILE_ROWS");
-  if (env && std::atoi(env) > 0) return (int)std::min<int64_t>(std::atoi(env), nz);
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus <= 0) {
-    (void)hipGetLastError();
-    cus = 256;
-  }
-  const int64_t slots = (int64_t)cus * (f64 ? 1 : 2);
+  if (env_rows()) return (int)std::min<int64_t>(env_rows(), nz);
+  const int64_t slots = simds() / 4 * (f64 ? 1 : 2);
   const int64_t groups = stage_groups3(tiles_x, ny);
-  double best = 1e300;
-  int64_t planes = 4;
-  for (int64_t r = 4; r <= 64; ++r) {
-    const int64_t pp = std::min(r, nz);
-    const int64_t wgs = groups * ((nz + pp - 1) / pp);
-    const double cost = (double)((wgs + slots - 1) / slots) * ((double)pp + 1.0);
-    if (cost < best - 1e-9) {
-      best = cost;
-      planes = pp;
-    }
-  }
-  return (int)std::min<int64_t>(planes, nz);
+  return best_rows(
+      nz, 64, 1.0, [&](int64_t p) { return groups * ceil_div(nz, p); },
+      [&](int64_t wgs) { return (double)ceil_div(wgs, slots); });
 }
 
-// Rows per wave of the 2D Euler stage kernels and the MUSCL-Hancock step.
-// FP64: stage 1 runs two waves per SIMD, stage 2 and the MUSCL-Hancock kernel
-// one (registers); a wave of R rows costs about R + 2 row times, so R in
-// [4, 128] minimises (rounds at two waves per SIMD + rounds at one) x (R + 2)
-// (2048^2: 36 rows, 1995 waves, one round of stage 1 and two of stage 2).
-// FP32 runs several waves per SIMD, which hide each other's latency: the
-// generic rule (about 4096 waves).  DG_TILE_ROWS overrides both.
+// Rows per wave of the 2D Euler stage kernels and the MUSCL-Hancock step
+// (2048^2 FP64: 36 rows, 1995 waves, one round of stage 1 and two of stage 2.
+// MUSCL-Hancock with the exact flux and WENO: 64^2 one row, 37 against 90 us at
+// the 4 rows that were the least before, FP32 17 against 34; 512^2 FP32 5 rows
+// 41 against 49 us; 1000x750 FP32 7 rows, 74 us at 5 against 82 at 4).
 static int default_rows_euler2d(int64_t ntiles_x, int64_t nrows, bool f64) {
-  if (!f64 || std::getenv("DG_TILE_ROWS")) return default_rows(ntiles_x, nrows);
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus <= 0) {
-    (void)hipGetLastError();
-    cus = 256;
-  }
-  const int64_t one = (int64_t)cus * 4;
-  double best = 1e300;
-  int64_t rows = 4;
-  for (int64_t r = 4; r <= 128; ++r) {
-    const int64_t rr = std::min(r, nrows);
-    const int64_t waves = ntiles_x * ((nrows + rr - 1) / rr);
-    const int64_t rounds = (waves + 2 * one - 1) / (2 * one) + (waves + one - 1) / one;
-    const double cost = (double)rounds * ((double)rr + 2.0);
-    if (cost < best - 1e-9) {
-      best = cost;
-      rows = rr;
-    }
-  }
-  return (int)std::min<int64_t>(rows, nrows);
+  if (env_rows()) return (int)std::min<int64_t>(env_rows(), nrows);
+  return best_rows(
+      nrows, f64 ? 128 : 64, 2.0, [&](int64_t r) { return ntiles_x * ceil_div(nrows, r); },
+      [&](int64_t w) { return load_stages(w, f64); });
 }
 
-// Rows per wave of the fused 2D Euler step (DG_STEP_ROWS overrides).  A wave
-// of R rows costs about R + 1.85 stage-2 row times (its four extra stage-1
-// rows are a little cheaper than stage-2 rows), and the waves run in rounds of
-// one per SIMD (FP64: one wave per SIMD by registers; FP32: two), so R in
-// [8, 128] minimises rounds x (R + 1.85): the last round should be nearly full
-// (2048^2: FP64 76 rows, one round of 999 waves; FP32 38 rows).
+// Rows per wave of the fused 2D Euler step (DG_STEP_ROWS overrides): four rows
+// beyond its own, one wave per SIMD in FP64, two in FP32, which cost 1.45 times
+// one (2048^2: FP64 76 rows, one round of 999 waves; FP32 38 rows; 64^2: one row,
+// 26 against 63 us at the 8 rows that were the least before, FP32 21 against 48;
+// 512^2 FP64 5 rows, 58 us at 6 against 69).
 static int default_step_rows(int64_t ntiles_x, int64_t nrows, bool f64) {
   const char* env = std::getenv("DG_STEP_ROWS");
-  int64_t rows = env ? std::atoi(env) : 0;
-  if (rows <= 0) {
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0) {
-      (void)hipGetLastError();
-      cus = 256;
-    }
-    const int64_t slots = (int64_t)cus * 4 * (f64 ? 1 : 2);
-    double best = 1e300;
-    for (int64_t r = 8; r <= 128; ++r) {
-      const int64_t rr = std::min(r, nrows);
-      const int64_t waves = ntiles_x * ((nrows + rr - 1) / rr);
-      const double cost = (double)((waves + slots - 1) / slots) * ((double)rr + 1.85);
-      if (cost < best - 1e-9) {
-        best = cost;
-        rows = rr;
-      }
-    }
-  }
-  return (int)std::min<int64_t>(rows, nrows);
+  const int64_t rows = env ? std::atoi(env) : 0;
+  if (rows > 0) return (int)std::min<int64_t>(rows, nrows);
+  const int64_t n = simds();
+  return best_rows(
+      nrows, 128, 4.0, [&](int64_t r) { return ntiles_x * ceil_div(nrows, r); },
+      [&](int64_t w) { return f64 ? (double)ceil_div(w, n) : load_pairs(ceil_div(w, n), 1.45); });
 }
 
-// Rows per wave of the 2D MHD stage kernel.  FP64 runs one wave per SIMD (by
-// registers): a wave of R rows costs about R + 3 row times (the prologue loads
-// and limits two rows and solves one extra y-face row) and the waves run in
-// rounds of one per SIMD, so R in [2, 32] minimises rounds x (R + 3) (512^2:
-// 5 rows, one round of 927 waves, 0.117 ms per step against 0.152 at 2 rows
-// in three rounds; 2048^2: 24 rows, 1.39 against 1.43 ms).  FP32 runs three
-// waves per SIMD, which hide each other's latency: about 8192 waves over the
-// mesh, 2 to 16 rows, measured best (2048^2: 9 rows, 0.760 ms against 0.773
-// with the FP64 model's 24).
+// Rows per wave of the 2D MHD stage kernel.  FP64 one wave per SIMD, three rows
+// beyond its own (the prologue loads and limits two rows and solves one extra
+// y-face row) (512^2: 5 rows, one round of 927 waves, 0.111 ms per step against
+// 0.148 at 2 rows; 2048^2: 24 rows, 1.39 against 1.43 ms; 128^2: one row, 34
+// against 47 us at 2).  FP32 three waves per SIMD, which hide each other's
+// latency (2048^2: 9 rows, 0.760 ms against 0.773 with 24; 128^2: one row, 27
+// against 37 us at 2).
 static int default_rows_mhd2d(int64_t ntiles_x, int64_t nrows, bool f64) {
-  if (std::getenv("DG_TILE_ROWS")) return default_rows(ntiles_x, nrows);
-  if (!f64) {
-    int64_t rows = (ntiles_x * nrows + 8191) / 8192;
-    rows = std::max<int64_t>(2, std::min<int64_t>(16, rows));
-    return (int)std::min<int64_t>(rows, nrows);
-  }
-  int dev = 0, cus = 256;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      cus <= 0) {
-    (void)hipGetLastError();
-    cus = 256;
-  }
-  const int64_t slots = (int64_t)cus * 4;
-  double best = 1e300;
-  int64_t rows = 2;
-  for (int64_t r = 2; r <= 32; ++r) {
-    const int64_t rr = std::min(r, nrows);
-    const int64_t waves = ntiles_x * ((nrows + rr - 1) / rr);
-    const double cost = (double)((waves + slots - 1) / slots) * ((double)rr + 3.0);
-    if (cost < best - 1e-9) {
-      best = cost;
-      rows = rr;
-    }
-  }
-  return (int)std::min<int64_t>(rows, nrows);
+  if (env_rows()) return (int)std::min<int64_t>(env_rows(), nrows);
+  const int64_t n = simds();
+  return best_rows(
+      nrows, 32, f64 ? 3.0 : 1.2, [&](int64_t r) { return ntiles_x * ceil_div(nrows, r); },
+      [&](int64_t w) {
+        return f64 ? (double)ceil_div(w, n) : load_shared(ceil_div(w, n), 0.5);
+      });
 }
 
 // Meshes that keep Pi(U) of stage 1 in ws_a for stage 2 (3D MHD limits in
@@ -290,13 +286,7 @@ static dg_status adjoint_tables(dg_mesh* m, const BatchDesc& d, bool batched) {
   std::vector<AdjInst> ai(d.ninst);
   std::vector<int> ti;
   int tile0 = 0;
-  // rows per wave: about kAdjWaves waves over the whole set, within
-  // [kAdjRowsMin, kAdjRowsMax] (each wave marches 4 rows beyond its own)
-  int64_t strips = 0;
-  for (int i = 0; i < d.ninst; ++i)
-    strips += (int64_t)((d.nx[i] + kAdjCols - 1) / kAdjCols) * d.ny[i];
-  const int rows = (int)std::min<int64_t>(
-      kAdjRowsMax, std::max<int64_t>(kAdjRowsMin, (strips + kAdjWaves - 1) / kAdjWaves));
+  const int rows = default_adjoint_rows(d, m->cfg.precision == DG_FP64);
   for (int i = 0; i < d.ninst; ++i) {
     AdjInst a{};
     a.nx = d.nx[i];
@@ -523,7 +513,7 @@ dg_status dg_mesh_create(const dg_mesh_desc* d, const dg_config* cfg, dg_mesh_t*
       return einval("dg_mesh_create: batch too large for 32-bit indexing");
     }
     m->bt.ninst = d->ninst;
-    m->bt.rows = default_batch_rows();
+    m->bt.rows = default_batch_rows(bd, cfg->precision == DG_FP64);
     const bool f64 = cfg->precision == DG_FP64;
     hipError_t e2 = hipMalloc(&m->bt.inst, batch_record_size(f64) * d->ninst);
     if (e2 == hipSuccess) e2 = hipMalloc(&m->bt.tile_inst, sizeof(int) * maxtiles);
@@ -1012,7 +1002,7 @@ dg_status dg_set_tiling(dg_mesh_t m, int rows) {
   if (m->kind == 2) {
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(e, "dg_set_tiling: synchronise");
-    m->bt.rows = rows ? rows : default_batch_rows();
+    m->bt.rows = rows ? rows : default_batch_rows(m->bt.d, m->cfg.precision == DG_FP64);
     return batch_upload(m);
   }
   if (m->kind != 0) return DG_OK;

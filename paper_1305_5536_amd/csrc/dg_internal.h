@@ -53,9 +53,7 @@ struct MVDev;  // moving Voronoi mesh (moving2d.hip)
 // (kAdjCols columns x `rows` rows, one wave each) start at tile `tx0` of the
 // tile list.
 constexpr int kAdjCols = 58;
-constexpr int kAdjRowsMin = 16;
 constexpr int kAdjRowsMax = 64;
-constexpr int kAdjWaves = 2048;
 struct AdjInst {
   int nx, ny, off, tx0;
   int tiles_x, tiles_y, rows, pad;

@@ -11,28 +11,33 @@
 //   W = Pi(P),
 // stage 2: P = V1, lam = lam', c_id = 1/2, c_L = dt/2; stage 1: P = U,
 // lam = lam_V1, c_id = 1, c_L = dt, extra = lam' with c_extra = 1/2.  Each
-// runs the forward limiter (k_lim2m) into a workspace and three gather kernels,
-// one thread per cell, no atomics:
-//   k_adj2m_L    lamW of a cell from its four faces (two Gauss points each)
-//                and its four volume points.  The cotangent of a face flux is
-//                the transpose of the linear residual weights (the same
-//                algebra as the forward accumulation) applied to the adjoints
-//                of both adjacent cells; one reverse sweep through the HLLD
-//                flux (hlld_vjp) gives the cotangent of this cell's
-//                Gauss-point state; the extrapolation to the Gauss point is
-//                transposed by hand (it is linear).
-//   k_adj2m_lim  the transpose of the cell's own limiter: everything it hands
-//                back to its own coefficients, and a message per limited
-//                variable (a value and a direction) for the one neighbour whose
-//                mean set the bound.
+// runs the forward limiter (k_lim2m) into a workspace, then, chunk of rows by
+// chunk of rows, without atomics:
+//   k_adj2m_face one thread per face, each face once, both Gauss points.  The
+//                cotangent of its flux is the transpose of the linear residual
+//                weights (the same algebra as the forward accumulation) applied to
+//                the adjoints of both adjacent cells; one reverse sweep through
+//                the HLLD flux (hlld_vjp) gives the cotangents of both sides'
+//                point states, which go to a face table (64 values a cell);
+//   k_adj2m_cell lamW of a cell from its four faces' entries (the extrapolation
+//                to the Gauss points is linear, transposed by hand) and its volume
+//                points, then the transpose of its own limiter: all it hands back
+//                to its own coefficients, and a message per limited variable (a
+//                value and a direction) for the neighbour whose mean set the bound;
+// and at last
 //   k_adj2m_msg  each cell adds the messages of its four neighbours.
-// FP64 instruction issue bounds k_adj2m_L (each face from both sides: eight
-// reverse sweeps a cell), memory traffic the other two.  Measured (512^2, FP64,
-// one adjoint stage): k_adj2m_L 0.168 ms; with one forward-mode solve per state
-// component it took 0.901 ms.  k_adj2m_lim 0.030 and k_adj2m_msg 0.011 ms;
-// differentiating every limiter that reads a cell, component by component, took
-// 0.410 ms.  The adjoint step 2.59 -> 0.44 ms.
+// FP64 instruction issue at one wave per SIMD bounds k_adj2m_face (about 1,050
+// vector instructions a sweep, 47% of the issue slots; waves of their own
+// workgroup, since four to a workgroup wait for the slowest: 0.080 against 0.099
+// ms; a two-wave budget spills 300 B a lane, 0.15 ms); memory traffic bounds
+// k_adj2m_cell (400 MB at 5.7 TB/s).  Measured (512^2, FP64, one adjoint stage):
+// faces 0.089, cells 0.070, messages 0.015 ms; one thread per cell solving each
+// face from both sides 0.168 + 0.030 + 0.011 ms; with a forward-mode solve per
+// state component and every limiter that reads a cell differentiated, component
+// by component, 0.901 + 0.410 ms.  The adjoint step 2.59 -> 0.37 ms.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "dg_internal.h"
 #include "dg_math.h"
@@ -57,6 +62,8 @@ __device__ __forceinline__ int bj(int c, int d) {
 }
 __device__ __forceinline__ int bs(int c, int d) { return (c == 1 && d == 1) ? -1 : 1; }
 
+constexpr size_t kFaceVals = 64;  // face table: 2 axes, 2 sides, 2 Gauss points, 8 variables
+
 // Coefficient index of conserved mean k (rho, mx, my, mz, E, Bx, By, Bz).
 __device__ __forceinline__ int mean_index(int k) { return k < 5 ? 3 * k : 10 + k; }
 
@@ -64,16 +71,17 @@ template <typename T>
 struct PJ {
   const T* W;      // Pi(P), the state the stage's operator sees
   const T* P;      // the stage input (limiter transpose)
-  const T* lam;    // adjoint of the stage output (k_adj2m_L)
+  const T* lam;    // adjoint of the stage output
   const T* extra;  // added to lamW with weight c_extra (may be NULL)
-  const T* lamW;   // k_adj2m_lim input
   T* out;
+  T* F;            // face table of the rows at hand: [64][nF]
   T* msg;          // limiter messages: 6 values a cell
   unsigned* code;  // and their directions
   const double* dt_dev;
   double dt_host;
   double c_id, c_L_over_dt, c_extra;
   int nx, ny, nc;
+  int row0, rows, nF;  // rows at hand, nF = nx (rows + 1)
   T gamma, eps;
   T c2h[2], c3[2], cs, pt[2], half[2], q[2], imu[3];
 };
@@ -122,29 +130,6 @@ __device__ __forceinline__ void acc_bar(const T* lam, const PJ<T>& p, AccBar<T>&
   a.P[2][1] = lam[22] * p.imu[1];
 }
 
-// Cotangent of a Gauss-point flux F of a face of axis D (tangential sign s)
-// from one adjacent cell (sigma = +1 when it is the R cell, -1 the L cell):
-// the transpose of the forward accumulation
-//   mean_k += sigma F_k/(2 h_D)           (k other than the normal field)
-//   grad_v[D] -= 3 F_v / h_D^2,  grad_v[t] += s sigma sqrt3 F_v / (h_D h_t)
-//   P[c][D] -= F_Bc / 4,  P[c][t] += s sigma h_t F_Bc / (4 sqrt3 h_D)  (c != D).
-template <typename T, int D>
-__device__ __forceinline__ void flux_bar(const AccBar<T>& a, T s, T sigma, const PJ<T>& p,
-                                         T* Fb) {
-  constexpr int t = 1 - D;
-  const T cm = sigma * p.c2h[D], ct = s * sigma * p.cs, cp = s * sigma * p.pt[D];
-#pragma unroll
-  for (int k = 0; k < 8; ++k)
-    if (k != 5 + D) Fb[k] = fma(cm, a.m[k], Fb[k]);
-#pragma unroll
-  for (int v = 0; v < 5; ++v) Fb[v] = fma(-p.c3[D], a.g[v][D], fma(ct, a.g[v][t], Fb[v]));
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (c == D) continue;
-    Fb[5 + c] = fma(T(-0.25), a.P[c][D], fma(cp, a.P[c][t], Fb[5 + c]));
-  }
-}
-
 // State of a cell's polynomial at the point (hn along axis D, ht along the
 // other axis) from its centroid: hydro Taylor terms and the field basis.
 template <typename T, int D>
@@ -177,40 +162,125 @@ __device__ __forceinline__ void point_state_bar(const T* ub, T hn, T ht, T* g) {
   }
 }
 
-// Face of axis D of cell e (side 0: e is L, i.e. the face is e's +D face;
-// side 1: e is R) with neighbour coefficients cn and adjoint an: adds the
-// face's contribution to (dL/dW_e)^T lam to g.
+// The -D face of cell eR, both Gauss points (offsets -+ q_t along the face): the
+// cotangents of both sides' point states, to the face table.  The cotangent of a flux F is
+// the transpose of the forward accumulation, for the R cell (sigma = +1) and the
+// L cell (sigma = -1):
+//   mean_k += sigma F_k/(2 h_D)           (k other than the normal field)
+//   grad_v[D] -= 3 F_v / h_D^2,  grad_v[t] += s sigma sqrt3 F_v / (h_D h_t)
+//   P[c][D] -= F_Bc / 4,  P[c][t] += s sigma h_t F_Bc / (4 sqrt3 h_D)  (c != D),
+// F0 its part common to both points and F1 the part that changes sign.
 template <typename T, int D>
-__device__ void face_adjoint(const T* ce, const AccBar<T>& ae, const T* cn, const AccBar<T>& an,
-                             int side, const PJ<T>& p, T* g) {
+__device__ __forceinline__ void face_adjoint(const PJ<T>& p, int eL, int eR, int le) {
   constexpr int t = 1 - D;
-  // e's side of the face: normal offset +h_D/2 as L, -h_D/2 as R; the residual
-  // sign sigma -1 as L, +1 as R (values are selected element by element: an
-  // array picked through a pointer would leave the registers)
-  const T he = side == 0 ? p.half[D] : -p.half[D];
-  const T sge = side == 0 ? T(-1) : T(1);
+  // every load first: one latency for the thread's two solves
+  T cL[23], cR[23];
+  load23(p.W, p.nc, eL, cL);
+  load23(p.W, p.nc, eR, cR);
+  T F0[8], F1[8];
+  {
+    T lam[23];
+    AccBar<T> a;
+    load23(p.lam, p.nc, eR, lam);
+    acc_bar(lam, p, a);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      F0[k] = p.c2h[D] * a.m[k];
+      F1[k] = T(0);
+    }
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      F0[v] = fma(-p.c3[D], a.g[v][D], F0[v]);
+      F1[v] = p.cs * a.g[v][t];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (c == D) continue;
+      F0[5 + c] = fma(T(-0.25), a.P[c][D], F0[5 + c]);
+      F1[5 + c] = p.pt[D] * a.P[c][t];
+    }
+    load23(p.lam, p.nc, eL, lam);
+    acc_bar(lam, p, a);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) F0[k] = fma(-p.c2h[D], a.m[k], F0[k]);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      F0[v] = fma(-p.c3[D], a.g[v][D], F0[v]);
+      F1[v] = fma(-p.cs, a.g[v][t], F1[v]);
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (c == D) continue;
+      F0[5 + c] = fma(T(-0.25), a.P[c][D], F0[5 + c]);
+      F1[5 + c] = fma(-p.pt[D], a.P[c][t], F1[5 + c]);
+    }
+  }
 #pragma unroll 1
   for (int gp = 0; gp < 2; ++gp) {
     const T s = gp ? T(1) : T(-1);
     const T ht = s * p.q[t];
-    T ue[8], un[8], uL[8], uR[8], Fb[8];
-    point_state<T, D>(ce, he, ht, ue);
-    point_state<T, D>(cn, -he, ht, un);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      uL[k] = side == 0 ? ue[k] : un[k];
-      uR[k] = side == 0 ? un[k] : ue[k];
-      Fb[k] = T(0);
-    }
-    flux_bar<T, D>(ae, s, sge, p, Fb);
-    flux_bar<T, D>(an, s, -sge, p, Fb);
+    T uL[8], uR[8], Fb[8], bL[8], bR[8];
+    point_state<T, D>(cL, p.half[D], ht, uL);
+    point_state<T, D>(cR, -p.half[D], ht, uR);
     const T bn = T(0.5) * (uL[5 + D] + uR[5 + D]);
     uL[5 + D] = uR[5 + D] = bn;
-    T ub[8], bL[8], bR[8];
-    hlld_vjp<T, D>(uL, uR, p.gamma, p.eps, Fb, bL, bR);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) ub[k] = side == 0 ? bL[k] : bR[k];
-    point_state_bar<T, D>(ub, he, ht, g);
+    for (int k = 0; k < 8; ++k) Fb[k] = fma(s, F1[k], F0[k]);
+    hlld_vjp<T, D>(uL, uR, p.gamma, p.eps, Fb, bL, bR);
+    T* F = p.F + (size_t)(32 * D + 8 * gp) * p.nF + le;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      F[(size_t)k * p.nF] = bL[k];
+      F[(size_t)(16 + k) * p.nF] = bR[k];
+    }
+  }
+}
+
+// Both lower faces of the cells of rows [row0, row0 + rows), and the -y faces of
+// the row above them.
+template <typename T>
+__global__ __launch_bounds__(64) void k_adj2m_face(PJ<T> p) {
+  const int nb = gridDim.x >> 1;
+  const int b = blockIdx.x;
+  const int le = (b < nb ? b : b - nb) * 64 + threadIdx.x;
+  if (le >= p.nF) return;
+  const int lr = le / p.nx, i = le - lr * p.nx;
+  int j = p.row0 + lr;
+  if (j >= p.ny) j -= p.ny;
+  const int e = j * p.nx + i;
+  if (b < nb) {
+    if (lr == p.rows) return;
+    face_adjoint<T, 0>(p, j * p.nx + (i == 0 ? p.nx - 1 : i - 1), e, le);
+  } else {
+    face_adjoint<T, 1>(p, (j == 0 ? p.ny - 1 : j - 1) * p.nx + i, e, le);
+  }
+}
+
+// Adds one face's entry of the face table to the coefficient adjoint g: side 0
+// (the cell is L, its normal offset +h_D/2) or 1 (R, -h_D/2).
+template <typename T, int D, int SIDE>
+__device__ __forceinline__ void add_face(const PJ<T>& p, int le, T* g) {
+  constexpr int t = 1 - D;
+  const T hn = SIDE == 0 ? p.half[D] : -p.half[D];
+  T S[8], Tt[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const T u0 = p.F[(size_t)(32 * D + 16 * SIDE + k) * p.nF + le];
+    const T u1 = p.F[(size_t)(32 * D + 16 * SIDE + 8 + k) * p.nF + le];
+    S[k] = u0 + u1;
+    Tt[k] = u1 - u0;
+  }
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    g[3 * v] += S[v];
+    g[3 * v + 1 + D] = fma(hn, S[v], g[3 * v + 1 + D]);
+    g[3 * v + 1 + t] = fma(p.q[t], Tt[v], g[3 * v + 1 + t]);
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    g[15 + k] += S[5 + k];
+    g[18 + bj(k, D)] = fma(T(bs(k, D)) * hn, S[5 + k], g[18 + bj(k, D)]);
+    g[18 + bj(k, t)] = fma(T(bs(k, t)) * p.q[t], Tt[5 + k], g[18 + bj(k, t)]);
   }
 }
 
@@ -239,61 +309,53 @@ __device__ void volume_adjoint(const T* ce, const AccBar<T>& ae, const PJ<T>& p,
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_adj2m_L(PJ<T> p) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= p.nc) return;
-  int nb[4];
-  neighbours(e, p.nx, p.ny, nb);
-  T ce[23], le[23], g[23];
-  load23(p.W, p.nc, e, ce);
-  load23(p.lam, p.nc, e, le);
+// lamW of one cell from the face table, its volume term and its own lam, then the
+// transpose of the cell's own limiter: the adjoint of its gradients, field
+// coefficients and the part its own mean takes are written out, and, for the six
+// limited variables (rho .. E, the field), a message to the neighbour whose mean
+// set the bound: a value and the neighbour's direction.  msg[s * nc + e] holds
+// slot s, the codes of a cell 4 bits a slot (0: none, 1 + direction), the field
+// component of slot 5 in bits 24 and 25.  Without a limiter lamW is the result.
+template <typename T, bool LIM>
+__global__ __launch_bounds__(256) void k_adj2m_cell(PJ<T> p) {
+  const int le = blockIdx.x * 256 + threadIdx.x;
+  if (le >= p.nx * p.rows) return;
+  const int e = p.row0 * p.nx + le;
+  const int lr = le / p.nx, i = le - lr * p.nx;
+  T lw[23];
+  {
+    T ce[23], le_[23], g[23];
+    load23(p.W, p.nc, e, ce);
+    load23(p.lam, p.nc, e, le_);
 #pragma unroll
-  for (int k = 0; k < 23; ++k) g[k] = T(0);
-  AccBar<T> ae;
-  acc_bar(le, p, ae);
-#pragma unroll 1
-  for (int f = 0; f < 4; ++f) {
-    T cn[23], ln[23];
-    load23(p.W, p.nc, nb[f], cn);
-    load23(p.lam, p.nc, nb[f], ln);
-    AccBar<T> an;
-    acc_bar(ln, p, an);
-    // -x: e is R; +x: e is L; -y: e is R; +y: e is L
-    const int side = (f & 1) ? 0 : 1;
-    if (f < 2)
-      face_adjoint<T, 0>(ce, ae, cn, an, side, p, g);
-    else
-      face_adjoint<T, 1>(ce, ae, cn, an, side, p, g);
-  }
-  volume_adjoint(ce, ae, p, g);
-  const double dt = p.dt_dev ? *p.dt_dev : p.dt_host;
-  const T cid = (T)p.c_id, cL = (T)(p.c_L_over_dt * dt), cx = (T)p.c_extra;
+    for (int k = 0; k < 23; ++k) g[k] = T(0);
+    add_face<T, 0, 1>(p, le, g);
+    add_face<T, 0, 0>(p, i == p.nx - 1 ? le - i : le + 1, g);
+    add_face<T, 1, 1>(p, le, g);
+    add_face<T, 1, 0>(p, le + p.nx, g);
+    AccBar<T> ae;
+    acc_bar(le_, p, ae);
+    volume_adjoint(ce, ae, p, g);
+    const double dt = p.dt_dev ? *p.dt_dev : p.dt_host;
+    const T cid = (T)p.c_id, cL = (T)(p.c_L_over_dt * dt), cx = (T)p.c_extra;
 #pragma unroll
-  for (int k = 0; k < 23; ++k) {
-    T o = fma(cL, g[k], cid * le[k]);
-    if (p.extra) o = fma(cx, p.extra[(size_t)k * p.nc + e], o);
-    p.out[(size_t)k * p.nc + e] = o;
+    for (int k = 0; k < 23; ++k) {
+      T o = fma(cL, g[k], cid * le_[k]);
+      if (p.extra) o = fma(cx, p.extra[(size_t)k * p.nc + e], o);
+      lw[k] = o;
+    }
   }
-}
-
-// The limiter transpose Pi_P^T lamW of one cell's own limiter: writes the
-// adjoint of its gradients, field coefficients and the part its own mean takes,
-// and, for the six limited variables (rho .. E, the field), the message to the
-// neighbour whose mean set the bound: a value and the neighbour's direction.
-// msg[s * nc + e] holds slot s, the codes of a cell 4 bits a slot (0: none,
-// 1 + direction), the field component of slot 5 in bits 24 and 25.
-template <typename T>
-__global__ __launch_bounds__(256) void k_adj2m_lim(PJ<T> p) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= p.nc) return;
-  int nb[4];
-  neighbours(e, p.nx, p.ny, nb);
-  T c[23], lw[23];
-  load23(p.P, p.nc, e, c);
-  load23(p.lamW, p.nc, e, lw);
-  unsigned code = 0;
   auto put = [&](int k, T x) { p.out[(size_t)k * p.nc + e] = x; };
+  if (!LIM) {
+#pragma unroll
+    for (int k = 0; k < 23; ++k) put(k, lw[k]);
+    return;
+  }
+  int nb[4];
+  neighbours(e, p.nx, p.ny, nb);
+  T c[23];
+  load23(p.P, p.nc, e, c);
+  unsigned code = 0;
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     T m[4];
@@ -419,18 +481,27 @@ PJ<T> make_adj_params(const dg_mesh* m, const double* dt_dev, double dt) {
   return p;
 }
 
+// Rows whose face table fits the budget (at least one), shared evenly.
+int chunk_rows(const dg_mesh* m) {
+  const int ny = m->c2.ny;
+  const size_t row = kFaceVals * m->elem * (size_t)m->c2.nx;
+  const int most = (int)std::min<size_t>((size_t)ny, std::max<size_t>(kAdjFaceBudget / row, 2) - 1);
+  const int chunks = (ny + most - 1) / most;
+  return (ny + chunks - 1) / chunks;
+}
+
 template <typename T>
 hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const double* dt_dev,
                      double dt, const void* lam_np1, void* lam_n, void* ws1, void* ws2,
-                     hipStream_t s) {
+                     void* scratch, hipStream_t s) {
   const bool lim = m->cfg.limiter == DG_LIMITER_MINMOD;
-  const dim3 grid((unsigned)((m->ncells + 255) / 256)), block(256);
-  PJ<T> p = make_adj_params<T>(m, dt_dev, dt);
+  const dim3 block(256);
+  const PJ<T> p = make_adj_params<T>(m, dt_dev, dt);
+  const int chunk = chunk_rows(m);
   hipError_t e = hipSuccess;
   auto adj_stage = [&](const void* P, const void* lam, const void* extra, double c_id,
                        double c_L_over_dt, double c_extra, void* out) -> hipError_t {
-    // W = Pi(P) into ws1; lamW into ws2 (or straight into out without a
-    // limiter); out = Pi_P^T lamW
+    // W = Pi(P) into ws1; out = Pi_P^T lamW
     const void* W = P;
     if (lim) {
       hipError_t r = launch_mhd2d(m, kLimit, P, nullptr, ws1, nullptr, 0.0, 0.0, nullptr, s);
@@ -439,42 +510,49 @@ hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const doub
     }
     PJ<T> a = p;
     a.W = static_cast<const T*>(W);
+    a.P = static_cast<const T*>(P);
     a.lam = static_cast<const T*>(lam);
     a.extra = static_cast<const T*>(extra);
     a.c_id = c_id;
     a.c_L_over_dt = c_L_over_dt;
     a.c_extra = c_extra;
-    a.out = static_cast<T*>(lim ? ws2 : out);
-    hipLaunchKernelGGL((k_adj2m_L<T>), grid, block, 0, s, a);
-    if (!lim) return hipGetLastError();
-    PJ<T> b = p;
-    b.P = static_cast<const T*>(P);
-    b.lamW = static_cast<const T*>(ws2);
-    b.out = static_cast<T*>(out);
-    // W is no longer needed: its workspace takes the messages
-    b.msg = static_cast<T*>(ws1);
-    b.code = reinterpret_cast<unsigned*>(b.msg + (size_t)6 * m->ncells);
-    hipLaunchKernelGGL((k_adj2m_lim<T>), grid, block, 0, s, b);
-    hipLaunchKernelGGL((k_adj2m_msg<T>), grid, block, 0, s, b);
+    a.out = static_cast<T*>(out);
+    a.msg = static_cast<T*>(scratch);
+    a.code = reinterpret_cast<unsigned*>(a.msg + (size_t)6 * m->ncells);
+    a.F = a.msg + (size_t)7 * m->ncells;
+    for (a.row0 = 0; a.row0 < p.ny; a.row0 += chunk) {
+      a.rows = std::min(chunk, p.ny - a.row0);
+      a.nF = p.nx * (a.rows + 1);
+      hipLaunchKernelGGL((k_adj2m_face<T>), dim3(2 * ((a.nF + 63) / 64)), dim3(64), 0, s, a);
+      const dim3 cells((p.nx * a.rows + 255) / 256);
+      if (lim)
+        hipLaunchKernelGGL((k_adj2m_cell<T, true>), cells, block, 0, s, a);
+      else
+        hipLaunchKernelGGL((k_adj2m_cell<T, false>), cells, block, 0, s, a);
+    }
+    if (lim)
+      hipLaunchKernelGGL((k_adj2m_msg<T>), dim3((p.nc + 255) / 256), block, 0, s, a);
     return hipGetLastError();
   };
-  // stage 2: lam_V1 = Pi_V1^T [lam'/2 + (dt/2) L^T lam'] (in lam_n with the
-  // limiter, else in ws2)
-  void* lam_v1 = lim ? lam_n : ws2;
-  e = adj_stage(V1, lam_np1, nullptr, 0.5, 0.5, 0.0, lam_v1);
+  // stage 2: ws2 = lam_V1 = Pi_V1^T [lam'/2 + (dt/2) L^T lam']
+  e = adj_stage(V1, lam_np1, nullptr, 0.5, 0.5, 0.0, ws2);
   if (e != hipSuccess) return e;
   // stage 1: lam_n = Pi_U^T [lam_V1 + dt L^T lam_V1 + lam'/2]
-  return adj_stage(U, lam_v1, lam_np1, 1.0, 1.0, 0.5, lam_n);
+  return adj_stage(U, ws2, lam_np1, 1.0, 1.0, 0.5, lam_n);
 }
 
 }  // namespace
 
+size_t adjoint_mhd2d_scratch(const dg_mesh* m) {
+  return (7 * (size_t)m->ncells + kFaceVals * (size_t)m->c2.nx * (chunk_rows(m) + 1)) * m->elem;
+}
+
 hipError_t launch_adjoint_mhd2d(const dg_mesh* m, const void* U, const void* V1,
                                 const double* dt_dev, double dt, const void* lam_np1,
-                                void* lam_n, void* ws1, void* ws2, hipStream_t s) {
+                                void* lam_n, void* ws1, void* ws2, void* scratch, hipStream_t s) {
   if (m->cfg.precision == DG_FP64)
-    return adjoint_t<double>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, s);
-  return adjoint_t<float>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, s);
+    return adjoint_t<double>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, scratch, s);
+  return adjoint_t<float>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, scratch, s);
 }
 
 }  // namespace dg

@@ -8,22 +8,29 @@
 // The same two adjoint stages as in two dimensions (stage 2: P = V1,
 // lam = lam', c_id = 1/2, c_L = dt/2; stage 1: P = U, lam = lam_V1, c_id = 1,
 // c_L = dt, extra = lam' with weight 1/2), each the forward limiter (k_lim3d)
-// into a workspace and three gathers, one thread per cell, no atomics:
-//   k_adj3m_L    lamW of a cell from its six faces (four Gauss points each)
-//                and its eight volume points; flux cotangents from the
-//                transposed residual weights of both adjacent cells, one
-//                reverse sweep through the HLLD flux per Gauss point
-//                (hlld_vjp), the Gauss-point extrapolation and the map from
-//                residual moments to a4..a11 transposed by hand;
-//   k_adj3m_lim  the transpose of the cell's own limiter, with a message per
-//                limited variable for the neighbour whose mean set the bound;
-//   k_adj3m_msg  each cell adds the messages of its six neighbours.
-// FP64 instruction issue bounds k_adj3m_L (24 reverse sweeps a cell, each face
-// from both sides).  Measured (64^3, FP64, one adjoint stage): k_adj3m_L 0.98 ms
-// against 3.55 ms with one forward-mode solve per state component; k_adj3m_lim
-// 0.042 and k_adj3m_msg 0.011 ms against 0.77 ms for differentiating every
-// limiter that reads a cell.  The adjoint step 8.77 -> 2.12 ms.
+// into a workspace, then, chunk of planes by chunk of planes, without atomics:
+//   k_adj3m_face one thread per half face (two of the four Gauss points), each
+//                face once: flux cotangents from the transposed residual weights
+//                of both adjacent cells, one reverse sweep through the HLLD flux
+//                per Gauss point (hlld_vjp), both sides' point cotangents to a
+//                face table (192 values a cell);
+//   k_adj3m_cell lamW of a cell from its six faces' entries (the Gauss-point
+//                extrapolation and the map from residual moments to a4..a11
+//                transposed by hand) and its eight volume points, then the
+//                transpose of its own limiter, with a message per limited variable
+//                for the neighbour whose mean set the bound;
+// and at last k_adj3m_msg, in which each cell adds its neighbours' messages.
+// FP64 instruction issue at one wave per SIMD bounds k_adj3m_face, the traffic of
+// the face table k_adj3m_cell (two waves per SIMD at 84 B spilled a lane: 0.144
+// against 0.162 ms without).  The chunks' tables take 256 MiB (64^3, one stage:
+// two chunks 0.45 ms; five of 96 MiB 0.49; one of 600 MiB 0.46).  Measured (64^3,
+// FP64, one adjoint stage): faces 0.28, cells 0.14, messages 0.013 ms; one thread
+// per cell solving each face from both sides 0.98 + 0.05 ms; with a forward-mode
+// solve per state component and every limiter that reads a cell differentiated
+// 3.55 + 0.77 ms.  The adjoint step 8.77 -> 0.92 ms.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "dg_internal.h"
 #include "dg_math.h"
@@ -39,6 +46,7 @@ hipError_t launch_cart3d(const dg_mesh* m, int mode, const void* in, const void*
 namespace {
 
 constexpr int kNC3 = 31;
+constexpr size_t kFaceVals3 = 192;  // face table: 3 axes, 4 Gauss points, 2 sides, 8 variables
 
 // Coefficient layout (31 values): 4v the mean and 4v+1+d the gradient along d
 // of rho, mx, my, mz, E (v = 0..4); 20..22 the means of Bx, By, Bz; 23..30
@@ -83,14 +91,15 @@ struct PJ3 {
   const T* P;
   const T* lam;
   const T* extra;
-  const T* lamW;
   T* out;
+  T* F;            // face table of the planes at hand: [192][nF]
   T* msg;          // limiter messages: 6 values a cell
   unsigned* code;  // and their directions
   const double* dt_dev;
   double dt_host;
   double c_id, c_L_over_dt, c_extra;
   int nx, ny, nz, nc;
+  int plane0, planes, nF;  // planes at hand, nF = nx ny (planes + 1)
   T gamma, eps;
   T c4h[3], c15[3], cs[3][3], pt[3][3], half[3], q[3], imu[3], ib[4];
 };
@@ -144,31 +153,6 @@ __device__ __forceinline__ void acc_bar3(const T* lam, const PJ3<T>& p, AccBar3<
   a.P[2][2] = -r11;
 }
 
-// Cotangent of a Gauss-point flux of a face of axis D (tangential signs s1,
-// s2) from one adjacent cell (sigma +1 as R, -1 as L): the transpose of
-//   mean_k += sigma F_k/(4 h_D)  (k not the normal field),
-//   grad_v[D] -= 1.5 F_v/h_D^2,  grad_v[t_i] += sigma s_i (sqrt3/2) F_v/(h_D h_ti),
-//   P[c][D] -= F_Bc/8 (c != D),  P[c][t_i] += sigma s_i h_ti F_Bc/(8 sqrt3 h_D).
-template <typename T, int D>
-__device__ __forceinline__ void flux_bar3(const AccBar3<T>& a, T s1, T s2, T sigma,
-                                          const PJ3<T>& p, T* Fb) {
-  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
-  const T cm = sigma * p.c4h[D];
-  const T g1 = sigma * s1 * p.cs[D][t1], g2 = sigma * s2 * p.cs[D][t2];
-  const T b1 = sigma * s1 * p.pt[D][t1], b2 = sigma * s2 * p.pt[D][t2];
-#pragma unroll
-  for (int k = 0; k < 8; ++k)
-    if (k != 5 + D) Fb[k] = fma(cm, a.m[k], Fb[k]);
-#pragma unroll
-  for (int v = 0; v < 5; ++v)
-    Fb[v] = fma(-p.c15[D], a.g[v][D], fma(g1, a.g[v][t1], fma(g2, a.g[v][t2], Fb[v])));
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-    if (c == D) continue;
-    Fb[5 + c] = fma(T(-0.125), a.P[c][D], fma(b1, a.P[c][t1], fma(b2, a.P[c][t2], Fb[5 + c])));
-  }
-}
-
 // State of a cell's polynomial at offset o from its centroid, and the
 // transpose (the cotangent ub of the state added to the coefficient adjoint g).
 template <typename T>
@@ -198,41 +182,127 @@ __device__ __forceinline__ void point3_bar(const T* ub, const T* o, T* g) {
   }
 }
 
-// Face of axis D of cell e (side 0: e is L, its +D face; side 1: e is R):
-// adds the face's contribution to (dL/dW_e)^T lam to g.
+// Half of the -D face of cell eR: the two Gauss points at tangential offset
+// s1 q_t1, s2 = -+ along t2 (t1 < t2 the other two axes): the cotangents of both
+// sides' point states, to the face table.  The cotangent of a flux is the
+// transpose of the forward accumulation, for the R cell (sigma +1) and L (-1):
+//   mean_k += sigma F_k/(4 h_D)  (k not the normal field),
+//   grad_v[D] -= 1.5 F_v/h_D^2,  grad_v[t_i] += sigma s_i (sqrt3/2) F_v/(h_D h_ti),
+//   P[c][D] -= F_Bc/8 (c != D),  P[c][t_i] += sigma s_i h_ti F_Bc/(8 sqrt3 h_D),
+// F0 its part common to both points and F1 the part that changes sign with s2.
 template <typename T, int D>
-__device__ void face_adjoint3(const T* ce, const AccBar3<T>& ae, const T* cn,
-                              const AccBar3<T>& an, int side, const PJ3<T>& p, T* g) {
-  constexpr int t1 = (D + 1) % 3, t2 = (D + 2) % 3;
-  const T he = side == 0 ? p.half[D] : -p.half[D];
-  const T sge = side == 0 ? T(-1) : T(1);
-#pragma unroll 1
-  for (int gp = 0; gp < 4; ++gp) {
-    const T s1 = (gp & 2) ? T(1) : T(-1);
-    const T s2 = (gp & 1) ? T(1) : T(-1);
-    T oe[3], on[3];
-    oe[D] = he;
-    on[D] = -he;
-    oe[t1] = on[t1] = s1 * p.q[t1];
-    oe[t2] = on[t2] = s2 * p.q[t2];
-    T ue[8], un[8], uL[8], uR[8], Fb[8];
-    point3(ce, oe, ue);
-    point3(cn, on, un);
+__device__ __forceinline__ void face_adjoint3(const PJ3<T>& p, int eL, int eR, int half1, int le) {
+  constexpr int t1 = D == 0 ? 1 : 0, t2 = D == 2 ? 1 : 2;
+  const T s1 = half1 ? T(1) : T(-1);
+  T F0[8], F1[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      uL[k] = side == 0 ? ue[k] : un[k];
-      uR[k] = side == 0 ? un[k] : ue[k];
-      Fb[k] = T(0);
+  for (int k = 0; k < 8; ++k) F0[k] = F1[k] = T(0);
+#pragma unroll
+  for (int side = 0; side < 2; ++side) {
+    const T sg = side == 0 ? T(-1) : T(1);
+    T lam[kNC3];
+    AccBar3<T> a;
+    load31(p.lam, p.nc, side == 0 ? eL : eR, lam);
+    acc_bar3(lam, p, a);
+    const T g1 = sg * s1 * p.cs[D][t1], g2 = sg * p.cs[D][t2];
+    const T b1 = sg * s1 * p.pt[D][t1], b2 = sg * p.pt[D][t2];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (k != 5 + D) F0[k] = fma(sg * p.c4h[D], a.m[k], F0[k]);
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+      F0[v] = fma(-p.c15[D], a.g[v][D], fma(g1, a.g[v][t1], F0[v]));
+      F1[v] = fma(g2, a.g[v][t2], F1[v]);
     }
-    flux_bar3<T, D>(ae, s1, s2, sge, p, Fb);
-    flux_bar3<T, D>(an, s1, s2, -sge, p, Fb);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (c == D) continue;
+      F0[5 + c] = fma(T(-0.125), a.P[c][D], fma(b1, a.P[c][t1], F0[5 + c]));
+      F1[5 + c] = fma(b2, a.P[c][t2], F1[5 + c]);
+    }
+  }
+  T cL[kNC3], cR[kNC3];
+  load31(p.W, p.nc, eL, cL);
+  load31(p.W, p.nc, eR, cR);
+#pragma unroll 1
+  for (int half2 = 0; half2 < 2; ++half2) {
+    const T s2 = half2 ? T(1) : T(-1);
+    T oL[3], oR[3];
+    oL[D] = p.half[D];
+    oR[D] = -p.half[D];
+    oL[t1] = oR[t1] = s1 * p.q[t1];
+    oL[t2] = oR[t2] = s2 * p.q[t2];
+    T uL[8], uR[8], Fb[8], bL[8], bR[8];
+    point3(cL, oL, uL);
+    point3(cR, oR, uR);
     const T bn = T(0.5) * (uL[5 + D] + uR[5 + D]);
     uL[5 + D] = uR[5 + D] = bn;
-    T ub[8], bL[8], bR[8];
-    hlld_vjp<T, D>(uL, uR, p.gamma, p.eps, Fb, bL, bR);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) ub[k] = side == 0 ? bL[k] : bR[k];
-    point3_bar(ub, oe, g);
+    for (int k = 0; k < 8; ++k) Fb[k] = fma(s2, F1[k], F0[k]);
+    hlld_vjp<T, D>(uL, uR, p.gamma, p.eps, Fb, bL, bR);
+    T* F = p.F + (size_t)(64 * D + 32 * half1 + 8 * half2) * p.nF + le;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      F[(size_t)k * p.nF] = bL[k];
+      F[(size_t)(16 + k) * p.nF] = bR[k];
+    }
+  }
+}
+
+// The lower faces of the cells of planes [plane0, plane0 + planes), and the -z
+// faces of the plane above them.  One thread per half face; six half faces of 64
+// consecutive cells are neighbouring workgroups (they share the cells' rows).
+template <typename T>
+__global__ __launch_bounds__(64) void k_adj3m_face(PJ3<T> p) {
+  const int b = blockIdx.x, part = b % 6;
+  const int le = (b / 6) * 64 + threadIdx.x;
+  if (le >= p.nF) return;
+  const int nxy = p.nx * p.ny;
+  const int lp = le / nxy, r = le - lp * nxy;
+  const int j = r / p.nx, i = r - j * p.nx;
+  int k = p.plane0 + lp;
+  if (k >= p.nz) k -= p.nz;
+  const int e = k * nxy + r;
+  const int axis = part >> 1, half1 = part & 1;
+  if (axis < 2 && lp == p.planes) return;
+  if (axis == 0)
+    face_adjoint3<T, 0>(p, i == 0 ? e + p.nx - 1 : e - 1, e, half1, le);
+  else if (axis == 1)
+    face_adjoint3<T, 1>(p, j == 0 ? e + nxy - p.nx : e - p.nx, e, half1, le);
+  else
+    face_adjoint3<T, 2>(p, k == 0 ? e + (p.nz - 1) * nxy : e - nxy, e, half1, le);
+}
+
+// Adds one face's entry of the face table to the coefficient adjoint g: side 0
+// (the cell is L, its normal offset +h_D/2) or 1 (R, -h_D/2).
+template <typename T, int D, int SIDE>
+__device__ __forceinline__ void add_face3(const PJ3<T>& p, int le, T* g) {
+  constexpr int t1 = D == 0 ? 1 : 0, t2 = D == 2 ? 1 : 2;
+  const T hn = SIDE == 0 ? p.half[D] : -p.half[D];
+  const T* F = p.F + (size_t)(64 * D + 16 * SIDE) * p.nF + le;
+  T S[8], A[8], B[8];  // sums over the four points, weighted 1, s1, s2
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const T f00 = F[(size_t)k * p.nF], f01 = F[(size_t)(8 + k) * p.nF];
+    const T f10 = F[(size_t)(32 + k) * p.nF], f11 = F[(size_t)(40 + k) * p.nF];
+    const T lo = f00 + f01, hi = f10 + f11;
+    S[k] = lo + hi;
+    A[k] = hi - lo;
+    B[k] = (f01 - f00) + (f11 - f10);
+  }
+#pragma unroll
+  for (int v = 0; v < 5; ++v) {
+    g[4 * v] += S[v];
+    g[4 * v + 1 + D] = fma(hn, S[v], g[4 * v + 1 + D]);
+    g[4 * v + 1 + t1] = fma(p.q[t1], A[v], g[4 * v + 1 + t1]);
+    g[4 * v + 1 + t2] = fma(p.q[t2], B[v], g[4 * v + 1 + t2]);
+  }
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    g[20 + k] += S[5 + k];
+    dB3_bar(k, D, hn * S[5 + k], g + 23);
+    dB3_bar(k, t1, p.q[t1] * A[5 + k], g + 23);
+    dB3_bar(k, t2, p.q[t2] * B[5 + k], g + 23);
   }
 }
 
@@ -260,63 +330,58 @@ __device__ void volume_adjoint3(const T* ce, const AccBar3<T>& ae, const PJ3<T>&
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_adj3m_L(PJ3<T> p) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= p.nc) return;
-  int nb[6];
-  neighbours3(e, p.nx, p.ny, p.nz, nb);
-  T ce[kNC3], le[kNC3], g[kNC3];
-  load31(p.W, p.nc, e, ce);
-  load31(p.lam, p.nc, e, le);
+// lamW of one cell from the face table, its volume term and its own lam, then the
+// transpose of the cell's own limiter: the adjoint of its gradients, field
+// coefficients and the part its own mean takes are written out, and, for the six
+// limited variables (rho .. E, the field), a message to the neighbour whose mean
+// set the bound: a value and the neighbour's direction.  msg[s * nc + e] holds
+// slot s, the codes of a cell 4 bits a slot (0: none, 1 + direction), the field
+// component of slot 5 in bits 24 and 25.  Without a limiter lamW is the result.
+template <typename T, bool LIM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
+void k_adj3m_cell(PJ3<T> p) {
+  const int le = blockIdx.x * 256 + threadIdx.x;
+  const int nxy = p.nx * p.ny;
+  if (le >= nxy * p.planes) return;
+  const int e = p.plane0 * nxy + le;
+  T lw[kNC3];
+  {
+    const int i = le % p.nx, j = (le / p.nx) % p.ny;
+    T g[kNC3];
 #pragma unroll
-  for (int k = 0; k < kNC3; ++k) g[k] = T(0);
-  AccBar3<T> ae;
-  acc_bar3(le, p, ae);
-#pragma unroll 1
-  for (int f = 0; f < 6; ++f) {
-    T cn[kNC3], ln[kNC3];
-    load31(p.W, p.nc, nb[f], cn);
-    load31(p.lam, p.nc, nb[f], ln);
-    AccBar3<T> an;
-    acc_bar3(ln, p, an);
-    // the -D face: e is R (side 1); the +D face: e is L (side 0)
-    const int side = (f & 1) ? 0 : 1;
-    if (f < 2)
-      face_adjoint3<T, 0>(ce, ae, cn, an, side, p, g);
-    else if (f < 4)
-      face_adjoint3<T, 1>(ce, ae, cn, an, side, p, g);
-    else
-      face_adjoint3<T, 2>(ce, ae, cn, an, side, p, g);
-  }
-  volume_adjoint3(ce, ae, p, g);
-  const double dt = p.dt_dev ? *p.dt_dev : p.dt_host;
-  const T cid = (T)p.c_id, cL = (T)(p.c_L_over_dt * dt), cx = (T)p.c_extra;
+    for (int k = 0; k < kNC3; ++k) g[k] = T(0);
+    add_face3<T, 0, 1>(p, le, g);
+    add_face3<T, 0, 0>(p, i == p.nx - 1 ? le - i : le + 1, g);
+    add_face3<T, 1, 1>(p, le, g);
+    add_face3<T, 1, 0>(p, j == p.ny - 1 ? le - j * p.nx : le + p.nx, g);
+    add_face3<T, 2, 1>(p, le, g);
+    add_face3<T, 2, 0>(p, le + nxy, g);
+    T ce[kNC3], la[kNC3];
+    load31(p.W, p.nc, e, ce);
+    load31(p.lam, p.nc, e, la);
+    AccBar3<T> ae;
+    acc_bar3(la, p, ae);
+    volume_adjoint3(ce, ae, p, g);
+    const double dt = p.dt_dev ? *p.dt_dev : p.dt_host;
+    const T cid = (T)p.c_id, cL = (T)(p.c_L_over_dt * dt), cx = (T)p.c_extra;
 #pragma unroll
-  for (int k = 0; k < kNC3; ++k) {
-    T o = fma(cL, g[k], cid * le[k]);
-    if (p.extra) o = fma(cx, p.extra[(size_t)k * p.nc + e], o);
-    p.out[(size_t)k * p.nc + e] = o;
+    for (int k = 0; k < kNC3; ++k) {
+      T o = fma(cL, g[k], cid * la[k]);
+      if (p.extra) o = fma(cx, p.extra[(size_t)k * p.nc + e], o);
+      lw[k] = o;
+    }
   }
-}
-
-// The limiter transpose Pi_P^T lamW of one cell's own limiter: writes the
-// adjoint of its gradients, field coefficients and the part its own mean takes,
-// and, for the six limited variables (rho .. E, the field), the message to the
-// neighbour whose mean set the bound: a value and the neighbour's direction.
-// msg[s * nc + e] holds slot s, the codes of a cell 4 bits a slot (0: none,
-// 1 + direction), the field component of slot 5 in bits 24 and 25.
-template <typename T>
-__global__ __launch_bounds__(256) void k_adj3m_lim(PJ3<T> p) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= p.nc) return;
-  int nb[6];
-  neighbours3(e, p.nx, p.ny, p.nz, nb);
-  T c[kNC3], lw[kNC3];
-  load31(p.P, p.nc, e, c);
-  load31(p.lamW, p.nc, e, lw);
-  unsigned code = 0;
   auto put = [&](int k, T x) { p.out[(size_t)k * p.nc + e] = x; };
+  if (!LIM) {
+#pragma unroll
+    for (int k = 0; k < kNC3; ++k) put(k, lw[k]);
+    return;
+  }
+  int nb[6];
+  neighbours3(e, p.nx, p.ny, p.nz, nb);
+  T c[kNC3];
+  load31(p.P, p.nc, e, c);
+  unsigned code = 0;
 #pragma unroll
   for (int v = 0; v < 5; ++v) {
     T m[6];
@@ -450,15 +515,26 @@ PJ3<T> make_adj3_params(const dg_mesh* m, const double* dt_dev, double dt) {
   return p;
 }
 
+// Planes whose face table fits the budget (at least one), shared evenly.
+int chunk_planes(const dg_mesh* m) {
+  const int nz = m->c3.nz;
+  const size_t plane = kFaceVals3 * m->elem * (size_t)m->c3.nx * (size_t)m->c3.ny;
+  const int most =
+      (int)std::min<size_t>((size_t)nz, std::max<size_t>(kAdjFaceBudget / plane, 2) - 1);
+  const int chunks = (nz + most - 1) / most;
+  return (nz + chunks - 1) / chunks;
+}
+
 template <typename T>
 hipError_t adjoint3_t(const dg_mesh* m, const void* U, const void* V1, const double* dt_dev,
                       double dt, const void* lam_np1, void* lam_n, void* ws1, void* ws2,
-                      hipStream_t s) {
+                      void* scratch, hipStream_t s) {
   const bool lim = m->cfg.limiter == DG_LIMITER_MINMOD;
-  const dim3 grid((unsigned)((m->ncells + 255) / 256)), block(256);
   const PJ3<T> p = make_adj3_params<T>(m, dt_dev, dt);
+  const int chunk = chunk_planes(m), nxy = p.nx * p.ny;
   auto adj_stage = [&](const void* P, const void* lam, const void* extra, double c_id,
                        double c_L_over_dt, double c_extra, void* out) -> hipError_t {
+    // W = Pi(P) into ws1; out = Pi_P^T lamW
     const void* W = P;
     if (lim) {
       hipError_t r = launch_cart3d(m, kLimit, P, nullptr, ws1, nullptr, 0.0, 0.0, nullptr, s);
@@ -467,40 +543,49 @@ hipError_t adjoint3_t(const dg_mesh* m, const void* U, const void* V1, const dou
     }
     PJ3<T> a = p;
     a.W = static_cast<const T*>(W);
+    a.P = static_cast<const T*>(P);
     a.lam = static_cast<const T*>(lam);
     a.extra = static_cast<const T*>(extra);
     a.c_id = c_id;
     a.c_L_over_dt = c_L_over_dt;
     a.c_extra = c_extra;
-    a.out = static_cast<T*>(lim ? ws2 : out);
-    hipLaunchKernelGGL((k_adj3m_L<T>), grid, block, 0, s, a);
-    if (!lim) return hipGetLastError();
-    PJ3<T> b = p;
-    b.P = static_cast<const T*>(P);
-    b.lamW = static_cast<const T*>(ws2);
-    b.out = static_cast<T*>(out);
-    // W is no longer needed: its workspace takes the messages
-    b.msg = static_cast<T*>(ws1);
-    b.code = reinterpret_cast<unsigned*>(b.msg + (size_t)6 * m->ncells);
-    hipLaunchKernelGGL((k_adj3m_lim<T>), grid, block, 0, s, b);
-    hipLaunchKernelGGL((k_adj3m_msg<T>), grid, block, 0, s, b);
+    a.out = static_cast<T*>(out);
+    a.msg = static_cast<T*>(scratch);
+    a.code = reinterpret_cast<unsigned*>(a.msg + (size_t)6 * m->ncells);
+    a.F = a.msg + (size_t)7 * m->ncells;
+    for (a.plane0 = 0; a.plane0 < p.nz; a.plane0 += chunk) {
+      a.planes = std::min(chunk, p.nz - a.plane0);
+      a.nF = nxy * (a.planes + 1);
+      hipLaunchKernelGGL((k_adj3m_face<T>), dim3(6 * ((a.nF + 63) / 64)), dim3(64), 0, s, a);
+      const dim3 cells((nxy * a.planes + 255) / 256);
+      if (lim)
+        hipLaunchKernelGGL((k_adj3m_cell<T, true>), cells, dim3(256), 0, s, a);
+      else
+        hipLaunchKernelGGL((k_adj3m_cell<T, false>), cells, dim3(256), 0, s, a);
+    }
+    if (lim)
+      hipLaunchKernelGGL((k_adj3m_msg<T>), dim3((p.nc + 255) / 256), dim3(256), 0, s, a);
     return hipGetLastError();
   };
-  // stage 2 into lam_n (limiter) or ws2, then stage 1 into lam_n
-  void* lam_v1 = lim ? lam_n : ws2;
-  hipError_t e = adj_stage(V1, lam_np1, nullptr, 0.5, 0.5, 0.0, lam_v1);
+  // stage 2: ws2 = lam_V1, then stage 1: lam_n
+  hipError_t e = adj_stage(V1, lam_np1, nullptr, 0.5, 0.5, 0.0, ws2);
   if (e != hipSuccess) return e;
-  return adj_stage(U, lam_v1, lam_np1, 1.0, 1.0, 0.5, lam_n);
+  return adj_stage(U, ws2, lam_np1, 1.0, 1.0, 0.5, lam_n);
 }
 
 }  // namespace
 
+size_t adjoint_mhd3d_scratch(const dg_mesh* m) {
+  return (7 * (size_t)m->ncells +
+          kFaceVals3 * (size_t)m->c3.nx * (size_t)m->c3.ny * (chunk_planes(m) + 1)) * m->elem;
+}
+
 hipError_t launch_adjoint_mhd3d(const dg_mesh* m, const void* U, const void* V1,
                                 const double* dt_dev, double dt, const void* lam_np1,
-                                void* lam_n, void* ws1, void* ws2, hipStream_t s) {
+                                void* lam_n, void* ws1, void* ws2, void* scratch, hipStream_t s) {
   if (m->cfg.precision == DG_FP64)
-    return adjoint3_t<double>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, s);
-  return adjoint3_t<float>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, s);
+    return adjoint3_t<double>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, scratch, s);
+  return adjoint3_t<float>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, scratch, s);
 }
 
 }  // namespace dg

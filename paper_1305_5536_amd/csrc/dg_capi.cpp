@@ -53,7 +53,8 @@ hipError_t launch_facelist_cfl(const dg_mesh* m, const void* U, double cfl, doub
                                hipStream_t s);
 hipError_t launch_adjoint_mhd3d(const dg_mesh* m, const void* U, const void* V1,
                                 const double* dt_dev, double dt, const void* lam_np1,
-                                void* lam_n, void* ws1, void* ws2, hipStream_t s);
+                                void* lam_n, void* ws1, void* ws2, void* scratch, hipStream_t s);
+size_t adjoint_mhd3d_scratch(const dg_mesh* m);
 hipError_t launch_adjoint_facelist(const dg_mesh* m, const void* U, const void* V1,
                                    const double* dt_dev, double dt, const void* lam_np1,
                                    void* lam_n, void* ws1, void* ws2, hipStream_t s);
@@ -65,7 +66,8 @@ hipError_t launch_mhd2d(const dg_mesh* m, int mode, const void* in, const void* 
                         hipStream_t s);
 hipError_t launch_adjoint_mhd2d(const dg_mesh* m, const void* U, const void* V1,
                                 const double* dt_dev, double dt, const void* lam_np1,
-                                void* lam_n, void* ws1, void* ws2, hipStream_t s);
+                                void* lam_n, void* ws1, void* ws2, void* scratch, hipStream_t s);
+size_t adjoint_mhd2d_scratch(const dg_mesh* m);
 hipError_t launch_mhd2d_cfl(const dg_mesh* m, const void* U, double cfl, double* dt_dev,
                             hipStream_t s);
 hipError_t launch_cart3d_cfl(const dg_mesh* m, const void* U, double cfl, double* dt_dev,
@@ -609,6 +611,7 @@ void dg_mesh_destroy(dg_mesh_t m) {
   (void)hipFree(m->adj_inst);
   (void)hipFree(m->adj_ws1);
   (void)hipFree(m->adj_ws2);
+  (void)hipFree(m->adj_scratch);
   (void)hipFree(m->ws_b);
   (void)hipFree(m->status);
   (void)hipFree(m->dtpart);
@@ -791,6 +794,8 @@ dg_status dg_adjoint_step(dg_mesh_t m, const void* U, const void* V1, double dt,
   hipError_t e = hipSuccess;
   if (!m->adj_ws1) e = hipMalloc(&m->adj_ws1, bytes);
   if (e == hipSuccess && !m->adj_ws2) e = hipMalloc(&m->adj_ws2, bytes);
+  if (e == hipSuccess && (mhd2 || mhd3) && !m->adj_scratch)
+    e = hipMalloc(&m->adj_scratch, mhd2 ? adjoint_mhd2d_scratch(m) : adjoint_mhd3d_scratch(m));
   if (e != hipSuccess) return hip_fail(e, "dg_adjoint_step: workspace allocation");
   if (!V1) {
     dg_status st = dispatch(m, kStage1, U, nullptr, m->v1, dt_dev, dt, s);
@@ -799,9 +804,9 @@ dg_status dg_adjoint_step(dg_mesh_t m, const void* U, const void* V1, double dt,
   }
   if (mhd2 || mhd3 || flist) {
     e = mhd2   ? launch_adjoint_mhd2d(m, U, V1, dt_dev, dt, lam_np1, lam_n, m->adj_ws1,
-                                      m->adj_ws2, s)
+                                      m->adj_ws2, m->adj_scratch, s)
         : mhd3 ? launch_adjoint_mhd3d(m, U, V1, dt_dev, dt, lam_np1, lam_n, m->adj_ws1,
-                                      m->adj_ws2, s)
+                                      m->adj_ws2, m->adj_scratch, s)
                : launch_adjoint_facelist(m, U, V1, dt_dev, dt, lam_np1, lam_n, m->adj_ws1,
                                          m->adj_ws2, s);
     if (e != hipSuccess) return hip_fail(e, "dg_adjoint_step launch");

@@ -54,6 +54,9 @@ struct MVDev;  // moving Voronoi mesh (moving2d.hip)
 // tile list.
 constexpr int kAdjCols = 58;
 constexpr int kAdjRowsMax = 64;
+// Face table of the MHD adjoints: rows (planes) are taken in chunks whose table
+// fits this many bytes.
+constexpr size_t kAdjFaceBudget = (size_t)256 << 20;
 struct AdjInst {
   int nx, ny, off, tx0;
   int tiles_x, tiles_y, rows, pad;
@@ -124,6 +127,7 @@ struct dg_mesh {
   int adj_tiles = 0;
   void* adj_ws1 = nullptr;          // adjoint workspaces (lazy)
   void* adj_ws2 = nullptr;
+  void* adj_scratch = nullptr;      // MHD: face table of a chunk and limiter messages
   dg::Batch bt;                     // kind 2
   void* run_ws = nullptr;           // dg_run: second ping-pong buffer (lazy)
   hipStream_t cap_stream = nullptr; // dg_run: capture stream (lazy)

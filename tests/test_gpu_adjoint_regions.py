@@ -1,0 +1,118 @@
+"""Adjoint face sweeps where they can go wrong: states that reach every region of the HLL and
+HLLD fans (supersonic both ways, between the Alfven waves, outside them), fields along the face
+normal (nearly degenerate star states, which take the forward mode), and MHD meshes whose faces
+are processed in several chunks.  Against the oracle's dual-number products.
+"""
+import numpy as np
+import pytest
+
+import workloads as W
+from workloads.voronoi import periodic_voronoi
+
+pytestmark = pytest.mark.gpu
+G53 = 5.0 / 3.0
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def _rough(ncells, dim, mhd, seed, mach, aligned=False):
+    """Independent random cells (sound speed about 1.3, speeds up to `mach`), slopes a few per
+    cent of the means; `aligned`: a strong field along x with a transverse part of a few per cent."""
+    rng = np.random.default_rng(seed)
+    U01 = lambda a, b: rng.uniform(a, b, ncells)  # noqa: E731
+    rho, p = U01(0.8, 1.2), U01(0.8, 1.2)
+    v = [mach * U01(-1, 1) for _ in range(3 if mhd else dim)]
+    E = p / (G53 - 1) + 0.5 * rho * sum(c * c for c in v)
+    hydro = [rho] + [rho * c for c in v]
+    rows = []
+    if mhd:
+        B = [np.full(ncells, 3.0), 0.05 * U01(-1, 1), 0.05 * U01(-1, 1)] if aligned else \
+            [U01(-1, 1) for _ in range(3)]
+        E = E + 0.5 * sum(b * b for b in B)
+    for q in hydro + [E]:
+        rows += [q] + [0.05 * q * U01(-1, 1) for _ in range(dim)]
+    if mhd:
+        rows += B + [0.02 * U01(-1, 1) for _ in range(5 if dim == 2 else 8)]
+    return np.concatenate(rows)
+
+
+def _entries(oracle, om, U, dt, w, idx, mhd, lim):
+    out = np.empty(len(idx))
+    for j, i in enumerate(idx):
+        e = np.zeros_like(U)
+        e[i] = 1.0
+        out[j] = oracle.step_jvp(om, U, e, dt, G53, lim, mhd=mhd)[1] @ w
+    return out
+
+
+def _error(got, want, dim, mhd):
+    """Largest error over the largest entry, means and slopes apart."""
+    nc = 12 if not mhd else (23 if dim == 2 else 31)
+    nh = 5 * (1 + dim) if mhd else 12
+    a, b = got.reshape(nc, -1), want.reshape(nc, -1)
+    mean = [k for k in range(nh) if k % (1 + dim) == 0] + (list(range(nh, nh + 3)) if mhd else [])
+    rest = [k for k in range(nc) if k not in mean]
+    return max(np.abs(a[k] - b[k]).max() / np.abs(b[k]).max() for k in (mean, rest))
+
+
+# the Jacobian's entries carry about eps (scale/den)^2; den/scale of 100 random faces stays above
+# 1e-3 where the field has no preferred direction (2e-10), and reaches 1e-5 where it is aligned
+@pytest.mark.parametrize("limiter", [False, True])
+@pytest.mark.parametrize("mach,aligned,bar", [(0.2, False, 1e-9), (4.0, False, 1e-9),
+                                              (0.1, True, 1e-4)])
+@pytest.mark.parametrize("n", [(5, 4), (3, 3, 2)])
+def test_hlld_regions(oracle, torch_cuda, n, mach, aligned, bar, limiter):
+    from paper_1305_5536_amd.solver import Solver, cartesian
+    dim = len(n)
+    lo, hi = (0.0,) * dim, (1.0,) * dim
+    om = oracle.Mesh.cartesian(n, lo, hi)
+    U = _rough(int(np.prod(n)), dim, True, 7 + dim, mach, aligned)
+    dt = oracle.cfl_dt(om, U, G53, 0.02, mhd=True)
+    w = np.random.default_rng(5).standard_normal(U.size)
+    s = Solver(cartesian(n, lo, hi), physics="mhd", limiter=limiter, gamma=G53)
+    got = s.adjoint_step(s.to_device(U), dt, s.to_device(w)).cpu().numpy()
+    want = _entries(oracle, om, U, dt, w, range(U.size), True, limiter)
+    err = _error(got, want, dim, True)
+    print(f"HLLD {n} mach {mach} aligned {aligned} limiter {limiter}: {err:.2e}")
+    assert err < bar
+
+
+@pytest.mark.parametrize("limiter", [False, True])
+@pytest.mark.parametrize("mach", [0.2, 4.0])
+def test_hll_regions_voronoi(oracle, torch_cuda, mach, limiter):
+    from paper_1305_5536_amd.solver import Solver
+    mesh = periodic_voronoi(24, seed=3)
+    om = oracle.Mesh.facelist(mesh)
+    U = _rough(24, 2, False, 19, mach)
+    dt = oracle.cfl_dt(om, U, G53, 0.02)
+    w = np.random.default_rng(5).standard_normal(U.size)
+    s = Solver(mesh, limiter=limiter, gamma=G53)
+    got = s.adjoint_step(s.to_device(U), dt, s.to_device(w)).cpu().numpy()
+    want = _entries(oracle, om, U, dt, w, range(U.size), False, limiter)
+    err = _error(got, want, 2, False)
+    print(f"HLL Voronoi mach {mach} limiter {limiter}: {err:.2e}")
+    assert err < 1e-12
+
+
+@pytest.mark.parametrize("n", [(1031, 523), (66, 61, 47)])
+def test_mhd_adjoint_in_chunks(oracle, torch_cuda, n):
+    """Face tables above 256 MiB are processed chunk by chunk of rows (planes): <J v, w> = <v, J^T w>
+    with v on the rows at chunk borders, everywhere else and at the periodic edges."""
+    from paper_1305_5536_amd.solver import Solver, cartesian
+    dim = len(n)
+    lo, hi = (0.0,) * dim, (1.0,) * dim
+    om = oracle.Mesh.cartesian(n, lo, hi)
+    U = W.random_p1_state(n, lo, hi, G53, seed=3, amp=0.2, mhd=True)
+    dt = oracle.cfl_dt(om, U, G53, 0.3, mhd=True)
+    rng = np.random.default_rng(11)
+    v, w = rng.standard_normal(U.size), rng.standard_normal(U.size)
+    _, Jv = oracle.step_jvp(om, U, v, dt, G53, True, mhd=True)
+    s = Solver(cartesian(n, lo, hi), physics="mhd", gamma=G53)
+    lam = s.adjoint_step(s.to_device(U), dt, s.to_device(w)).cpu().numpy()
+    assert abs(Jv @ w - v @ lam) <= 1e-12 * np.abs(Jv * w).sum()

@@ -8,8 +8,10 @@
 //   * the cell of generator i is the intersection of the half-planes closer to
 //     i than to each candidate j; the candidates are i's neighbours and their
 //     neighbours in the previous mesh (a cell's new neighbours over one CFL
-//     step were among them).  Its faces are found by walking around it
-//     counter-clockwise from the nearest candidate: the next face is the
+//     step were among them).  Over one step most cells keep their neighbours:
+//     the previous ring is kept where its vertices lie in the half-plane of every
+//     candidate.  The faces of the other cells are found by walking around the
+//     cell counter-clockwise from the nearest candidate: the next face is the
 //     candidate whose bisector first cuts the current face's bisector (no
 //     polygon is stored, only the ring of neighbours);
 //   * each Voronoi vertex is then recomputed as the circumcentre of its three
@@ -33,7 +35,7 @@
 //              conserved coefficients, or the WENO-type limiter on primitive
 //              variables with a least-squares stencil slope), and the
 //              generator positions at t^{n+1/2} and t^{n+1};
-//   k_mv_walk, k_mv_geom  the mesh of the half-step generators;
+//   k_mv_check, k_mv_walk, k_mv_geom  the mesh of the half-step generators;
 //   k_mv_upd   per cell of the half-step mesh: for each face and Gauss point,
 //              both cells' half-step primitive predictions (centred at the
 //              t^n centroids) at the point, boosted into the frame of the face
@@ -43,14 +45,13 @@
 //              cell's 4-point rule; out: the conserved totals V^n ubar +
 //              dt (...) and the first moments about the cell's origin carried
 //              along with w_e (c^n + t w_e);
-//   k_mv_walk, k_mv_geom  the mesh of t^{n+1}, then the new state: means = totals /
+//   k_mv_check, k_mv_walk, k_mv_geom  the mesh of t^{n+1}, then the new state: means = totals /
 //              V^{n+1}, gradients = (M^{n+1})^-1 (moments - (c^{n+1} - c^n -
 //              dt w_e) totals), and the cell's CFL bound.
 // Geometry is FP64 (absolute positions in a box); the state is T.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstdlib>
 #include <cmath>
 #include <cstring>
 #include <string>
@@ -63,11 +64,9 @@
 namespace dg {
 
 constexpr int kRing = 16;  // neighbours a cell may have
-constexpr int kPoly = kRing + 1;  // ring entries during the walk
+constexpr int kFast = 8;   // neighbours of a cell whose ring k_mv_check can keep
 constexpr int kGeo = 6;    // V, centroid - generator (2), Mxx, Mxy, Myy
-constexpr int kChunk = 4;  // candidates gathered together in the walk
-constexpr int kCand = 40;  // distinct candidates of one cell's walk kept in LDS
-constexpr int kWalkThreads = 128;  // threads per block of the walk (LDS: kCand ints each)
+constexpr int kWalkBlocks = 2048;  // most workgroups of the walk (four cells at a time each)
 
 struct MVDev {
   int n = 0;
@@ -81,7 +80,7 @@ struct MVDev {
   int* deg[3] = {nullptr, nullptr, nullptr};     // [n]
   double* geo[3] = {nullptr, nullptr, nullptr};  // [kGeo][n]
   void* ua = nullptr;                            // limited state
-  int cand_cap = kCand;                          // LDS list length of the walk (<= kCand)
+  int* list = nullptr;                           // [n + 1]: cells to walk, their count last
   bool timing = false;                           // record events around each kernel
   std::vector<hipEvent_t> ev;                    // 5 per timed step
 };
@@ -116,12 +115,18 @@ struct PM {
   double Lx, Ly;
   T gamma;
   int motion;
-  int cand_cap;   // k_mv_walk: candidates kept in LDS before streaming them
+  int* list;      // cells whose ring k_mv_check could not keep
+  int* count;     // and their number
   int write_pos;  // k_mv_lim: write the half-step and next positions
   MSet s0;        // t^n
   MSet sh;        // half step
   double* xh;     // positions written by k_mv_lim
   double* x1;
+};
+
+// The periodic box and its inverse sides.
+struct PM_box {
+  double Lx, Ly, iLx, iLy;
 };
 
 __device__ __forceinline__ double mimg(double d, double L) { return d - L * rint(d / L); }
@@ -468,158 +473,263 @@ __global__ __launch_bounds__(256) void k_mv_lim(PM<T> p) {
 }
 
 // ----------------------------------------------------------------- mesh --
-// The mesh of the positions dst.x in two launches.  k_mv_walk: the ring of
-// every cell from the 2-ring of the mesh `src` (written to dst.ring, dst.deg).
-// k_mv_geom: the cell geometry from the ring (canonical vertices, polygon
-// moments); with FINISH also the new state from the totals and moments in
-// p.out (the mesh of t^n in p.s0, the limited state p.ua for w_e) and the
-// cell's CFL bound in the per-wave minima when p.dtpart is set.  Split in two
-// so that the walk, a chain of dependent gathers, runs at a higher occupancy
-// than the register-heavy geometry and update.
+// The mesh of the positions dst.x from the mesh `src`, in three launches.
+// k_mv_check keeps the ring of every cell whose neighbours did not change and
+// lists the others; k_mv_walk finds the rings of the listed cells from the 2-ring
+// of `src`; k_mv_geom computes the cell geometry from the ring (canonical
+// vertices, polygon moments); with FINISH also the new state from the totals and
+// moments in p.out (the mesh of t^n in p.s0, the limited state p.ua for w_e) and
+// the cell's CFL bound in the per-wave minima when p.dtpart is set.  The
+// candidates of a cell are its previous neighbours and the entries of their rings.
+
+__device__ __forceinline__ void nearest_image(const PM_box& b, double& dx, double& dy) {
+  dx -= b.Lx * rint(dx * b.iLx);
+  dy -= b.Ly * rint(dy * b.iLy);
+}
+
+// One thread per cell.  The previous ring is still the cell's ring exactly when
+// the vertices it gives at the new positions (circumcentres of the cell and two
+// neighbours that follow each other) lie in the half-plane of every candidate:
+// then each is a vertex of the cell, and the walk from the nearest neighbour
+// would visit the same faces in the same order.  The test keeps a distance from
+// rounding (sine of the angle between neighbours above 1e-2, vertices inside by
+// 1e-9 of the candidate's distance); cells that miss it, that have more than
+// kFast neighbours, or whose ring changed, go to the list.  The vertices and
+// neighbours stay in registers; a candidate costs kFast comparisons of its index
+// and kFast half-plane tests, no list and no dependent scan.  The latency of its
+// three gathers (ring, neighbours' rings, positions) bounds it.  Measured (262144
+// cells, FP64): 0.066 ms, and 0.015 ms for the walk of the listed cells; walking
+// every cell, one thread each over a list of its candidates in LDS, took 0.177
+// ms, its dependent scans (one of all candidates per face) bound by latency.
 template <typename T>
-__global__ __launch_bounds__(kWalkThreads) void k_mv_walk(PM<T> p, MSet src, MOut dst) {
-  // each thread's distinct candidates, in a column of its own (no barrier)
-  __shared__ int cl[kCand * kWalkThreads];
-  const int tl = threadIdx.x;
-  const int e = xcd_remap(blockIdx.x, gridDim.x) * kWalkThreads + tl;
-  if (e < p.n) {
+__global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
+  const int e = xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+  const bool live = e < p.n;
+  bool ok = false;
+  if (live) {
     const int n = p.n;
     const double2* XY = reinterpret_cast<const double2*>(dst.x + 2 * (size_t)n);
+    const PM_box box{p.Lx, p.Ly, 1.0 / p.Lx, 1.0 / p.Ly};
     const double2 pe = XY[e];
-    const double xe = pe.x, ye = pe.y;
-    bool bad = false;
-    const int d0 = min(src.deg[e], kRing);
-    const double iLx = 1.0 / p.Lx, iLy = 1.0 / p.Ly;
-    // The candidates (the previous neighbours and the entries of their
-    // rings) are listed once, without repeats, in LDS; a cell with more than
-    // kCand of them streams them from the rings instead (repeats included:
-    // they give equal values and the index tie-break makes them harmless).
-    int nc = 0;
-    bool stream = false;
-    for (int a = 0; a < d0 && !stream; ++a) {
-      const int j = src.ring[e * kRing + a];
-      const int dj = min(src.deg[j], kRing);
-      for (int b = -1; b < dj; ++b) {
-        const int k = b < 0 ? j : src.ring[j * kRing + b];
-        if (k == e) continue;
-        bool seen = false;
-        for (int c = 0; c < nc; ++c) seen |= cl[c * kWalkThreads + tl] == k;
-        if (seen) continue;
-        if (nc == p.cand_cap) {
-          stream = true;
-          break;
-        }
-        cl[nc++ * kWalkThreads + tl] = k;
-      }
+    const int d = src.deg[e];
+    ok = d >= 3 && d <= kFast;
+    const int4* R4 = reinterpret_cast<const int4*>(src.ring);
+    int r[kFast];
+    {
+      const int4 lo = R4[4 * (size_t)e], hi = R4[4 * (size_t)e + 1];
+      r[0] = lo.x, r[1] = lo.y, r[2] = lo.z, r[3] = lo.w;
+      r[4] = hi.x, r[5] = hi.y, r[6] = hi.z, r[7] = hi.w;
     }
-    auto offset = [&](int k, double& dx, double& dy) {
-      const double2 pk = XY[k];
-      dx = pk.x - xe;
-      dy = pk.y - ye;
-      dx -= p.Lx * rint(dx * iLx);
-      dy -= p.Ly * rint(dy * iLy);
-    };
-    // f(k, dx, dy) for every candidate: its offset from this generator; the
-    // positions of kChunk candidates are loaded together so that the gathers
-    // overlap.
-    auto visit = [&](auto&& f) {
-      if (stream) {
-        for (int a = 0; a < d0; ++a) {
-          const int j = src.ring[e * kRing + a];
-          const int dj = min(src.deg[j], kRing);
-          for (int b = -1; b < dj; ++b) {
-            const int k = b < 0 ? j : src.ring[j * kRing + b];
-            if (k == e) continue;
-            double dx, dy;
-            offset(k, dx, dy);
-            f(k, dx, dy);
+    double dx[kFast], dy[kFast], n2[kFast], vx[kFast], vy[kFast];
+#pragma unroll
+    for (int k = 0; k < kFast; ++k) {
+      r[k] = ok && k < d ? r[k] : e;
+      const double2 q = XY[r[k]];
+      dx[k] = q.x - pe.x;
+      dy[k] = q.y - pe.y;
+      nearest_image(box, dx[k], dy[k]);
+      n2[k] = dx[k] * dx[k] + dy[k] * dy[k];
+    }
+    constexpr double kIn = 1.0 - 1e-9;
+#pragma unroll
+    for (int k = 0; k < kFast; ++k) {
+      const bool wrap = k + 1 == kFast || k + 1 >= d;
+      const double x1 = wrap ? dx[0] : dx[(k + 1) % kFast], y1 = wrap ? dy[0] : dy[(k + 1) % kFast];
+      const double m1 = wrap ? n2[0] : n2[(k + 1) % kFast];
+      const double den = dx[k] * y1 - dy[k] * x1;
+      if (k < d) ok &= den > 0.0 && den * den > 1e-4 * n2[k] * m1;
+      // 2 x the vertex: d_k + t perp(d_k), t = (|d_k1|^2 - d_k . d_k1) / den
+      const double t = (m1 - (dx[k] * x1 + dy[k] * y1)) * rcp(den);
+      vx[k] = dx[k] - t * dy[k];
+      vy[k] = dy[k] + t * dx[k];
+    }
+    // the cell's other neighbours, then every candidate further out
+#pragma unroll
+    for (int c = 0; c < kFast; ++c)
+#pragma unroll
+      for (int k = 0; k < kFast; ++k) {
+        const bool own = c == k || c == (k + 1 < d ? k + 1 : 0);
+        if (c < d && k < d && !own) ok &= vx[k] * dx[c] + vy[k] * dy[c] < kIn * n2[c];
+      }
+    if (ok) {
+      for (int a = 0; a < d; ++a) {
+        const int j = src.ring[(size_t)e * kRing + a];
+        const int dj = min(src.deg[j], kRing);
+        for (int b = 0; b < dj; b += 8) {
+          const int4 lo = R4[4 * (size_t)j + (b >> 2)], hi = R4[4 * (size_t)j + (b >> 2) + 1];
+          const int c[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+          double2 q[8];
+          bool out[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            out[u] = b + u < dj && c[u] != e;
+#pragma unroll
+            for (int k = 0; k < kFast; ++k) out[u] &= c[u] != r[k];
+            q[u] = XY[out[u] ? c[u] : e];
+          }
+#pragma unroll
+          for (int u = 0; u < 8; ++u) {
+            double cx = q[u].x - pe.x, cy = q[u].y - pe.y;
+            nearest_image(box, cx, cy);
+            const double m = kIn * (cx * cx + cy * cy);
+            bool in = true;
+#pragma unroll
+            for (int k = 0; k < kFast; ++k)
+              in &= k >= d || vx[k] * cx + vy[k] * cy < m;
+            ok &= in || !out[u];
           }
         }
-        return;
       }
-      for (int c0 = 0; c0 < nc; c0 += kChunk) {
-        int kk[kChunk];
-        double kx[kChunk], ky[kChunk];
+    }
+    if (ok) {
+      // the ring from the nearest neighbour on, as the walk gives it
+      int s = 0;
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) kk[q] = c0 + q < nc ? cl[(c0 + q) * kWalkThreads + tl] : e;
+      for (int k = 1; k < kFast; ++k) {
+        double best = n2[0];
+        int rb = r[0];
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) {
-          const double2 pk = XY[kk[q]];
-          kx[q] = pk.x;
-          ky[q] = pk.y;
+        for (int q = 1; q < k; ++q) {
+          best = q == s ? n2[q] : best;
+          rb = q == s ? r[q] : rb;
         }
+        if (k < d && (n2[k] < best || (n2[k] == best && r[k] < rb))) s = k;
+      }
+      int* out = dst.ring + (size_t)e * kRing;
 #pragma unroll
-        for (int q = 0; q < kChunk; ++q) {
-          if (c0 + q >= nc) continue;
-          double dx = kx[q] - xe, dy = ky[q] - ye;
-          dx -= p.Lx * rint(dx * iLx);
-          dy -= p.Ly * rint(dy * iLy);
-          f(kk[q], dx, dy);
+      for (int k = 0; k < kFast; ++k)
+        if (k < d) out[k >= s ? k - s : k - s + d] = r[k];
+      for (int k = d; k < kRing; ++k) out[k] = -1;
+      dst.deg[e] = d;
+    }
+  }
+  // list the others, one counter update per wave
+  const unsigned long long todo = __ballot(live && !ok);
+  if (todo) {
+    const int lane = threadIdx.x & 63;
+    int base = 0;
+    if (lane == __ffsll((long long)todo) - 1) base = atomicAdd(p.count, __popcll(todo));
+    base = __shfl(base, __ffsll((long long)todo) - 1);
+    if (live && !ok) p.list[base + __popcll(todo & ((1ull << lane) - 1))] = e;
+  }
+}
+
+// One wave per listed cell, the candidates spread over its lanes (an entry that
+// several neighbours list appears several times: equal values, harmless).  The
+// cell is walked counter-clockwise, one face at a time.  The nearest candidate is
+// a neighbour (the midpoint of the two generators lies on their common face).
+// The face of neighbour j lies on the bisector x(t) = d_j/2 + t perp(d_j),
+// perp(d) = (-d_y, d_x); candidate k bounds it from the counter-clockwise side at
+// t_k = (|d_k|^2 - d_j . d_k) / (2 perp(d_j) . d_k) when perp(d_j) . d_k > 0, and
+// the next neighbour is the candidate with the smallest t_k (compared by
+// cross-multiplication; ties to the smaller index).  The walk ends back at the
+// first neighbour; nothing but the ring is stored.
+template <typename T>
+__global__ __launch_bounds__(256) void k_mv_walk(PM<T> p, MSet src, MOut dst) {
+  const int lane = threadIdx.x & 63;
+  const int count = *p.count, nw = gridDim.x * 4;
+  const int n = p.n;
+  const double2* XY = reinterpret_cast<const double2*>(dst.x + 2 * (size_t)n);
+  const PM_box box{p.Lx, p.Ly, 1.0 / p.Lx, 1.0 / p.Ly};
+  constexpr int kSlots = (kRing * (kRing + 1) + 63) / 64;
+  for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < count; i += nw) {
+    const int e = __builtin_amdgcn_readfirstlane(p.list[i]);
+    const double2 pe = XY[e];
+    const int d0 = min(src.deg[e], kRing);
+    int id[kSlots];
+    double kx[kSlots], ky[kSlots];
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) {
+      const int t = lane + 64 * q, a = t / (kRing + 1), b = t - a * (kRing + 1) - 1;
+      id[q] = -1;
+      kx[q] = ky[q] = 0.0;
+      if (a < d0) {
+        const int j = src.ring[(size_t)e * kRing + a];
+        const int k = b < 0 ? j : (b < min(src.deg[j], kRing) ? src.ring[(size_t)j * kRing + b] : e);
+        if (k != e) {
+          const double2 pk = XY[k];
+          id[q] = k;
+          kx[q] = pk.x - pe.x;
+          ky[q] = pk.y - pe.y;
+          nearest_image(box, kx[q], ky[q]);
         }
       }
-    };
-    // The cell is walked counter-clockwise, one face at a time.  The nearest
-    // candidate is a neighbour (the midpoint of the two generators lies on
-    // their common face).  The face of neighbour j lies on the bisector
-    // x(t) = d_j/2 + t perp(d_j), perp(d) = (-d_y, d_x); candidate k bounds it
-    // from the counter-clockwise side at t_k = (|d_k|^2 - d_j . d_k) / (2
-    // perp(d_j) . d_k) when perp(d_j) . d_k > 0, and the next neighbour is the
-    // candidate with the smallest t_k.  The walk ends back at the first
-    // neighbour; nothing but the ring is stored.
+    }
+    // the nearest candidate
+    double best = 1e300, bx = 0.0, by = 0.0;
     int j0 = -1;
-    double best = 1e300;
-    visit([&](int k, double dx, double dy) {
-      const double dd = dx * dx + dy * dy;
-      if (dd < best || (dd == best && k < j0)) {
+#pragma unroll
+    for (int q = 0; q < kSlots; ++q) {
+      const double dd = kx[q] * kx[q] + ky[q] * ky[q];
+      if (id[q] >= 0 && (j0 < 0 || dd < best || (dd == best && id[q] < j0))) {
         best = dd;
-        j0 = k;
+        j0 = id[q];
+        bx = kx[q];
+        by = ky[q];
       }
-    });
-    bad |= j0 < 0;
-    int ring[kPoly];
-    int d = 0;
-    int cur = j0;
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      const double ob = __shfl_xor(best, o), ox = __shfl_xor(bx, o), oy = __shfl_xor(by, o);
+      const int oj = __shfl_xor(j0, o);
+      if (oj >= 0 && (j0 < 0 || ob < best || (ob == best && oj < j0))) {
+        best = ob;
+        j0 = oj;
+        bx = ox;
+        by = oy;
+      }
+    }
+    // (one lane's winner for all: near ties may round differently across lanes)
+    j0 = __builtin_amdgcn_readfirstlane(j0);
+    bool bad = j0 < 0;
+    int mine = -1;  // ring entry `lane`
+    int d = 0, cur = j0;
+    double cx = __shfl(bx, 0), cy = __shfl(by, 0);
     while (!bad) {
       if (d > kRing) {
         bad = true;
         break;
       }
-      ring[d++] = cur;
-      const double2 pc = XY[cur];
-      double cx = pc.x - xe, cy = pc.y - ye;
-      cx -= p.Lx * rint(cx * iLx);
-      cy -= p.Ly * rint(cy * iLy);
-      // smallest t_k = num_k / (2 den_k), compared as num_k den_b < num_b den_k
+      mine = lane == d ? cur : mine;
+      ++d;
       int nxt = -1;
-      double nb_ = 1.0, db_ = 0.0;
-      visit([&](int k, double kx, double ky) {
-        if (k == cur) return;
-        const double den = cx * ky - cy * kx;  // perp(d_cur) . d_k
-        if (!(den > 0.0)) return;
-        const double num = kx * kx + ky * ky - (cx * kx + cy * ky);
+      double nb_ = 1.0, db_ = 0.0, nx = 0.0, ny = 0.0;
+      auto take = [&](int k, double num, double den, double x, double y) {
         const double l = num * db_, r = nb_ * den;
         if (nxt < 0 || l < r || (l == r && k < nxt)) {
           nb_ = num;
           db_ = den;
           nxt = k;
+          nx = x;
+          ny = y;
         }
-      });
+      };
+#pragma unroll
+      for (int q = 0; q < kSlots; ++q) {
+        const double den = cx * ky[q] - cy * kx[q];  // perp(d_cur) . d_k
+        if (id[q] >= 0 && id[q] != cur && den > 0.0)
+          take(id[q], kx[q] * kx[q] + ky[q] * ky[q] - (cx * kx[q] + cy * ky[q]), den, kx[q], ky[q]);
+      }
+      for (int o = 32; o > 0; o >>= 1) {
+        const int ok = __shfl_xor(nxt, o);
+        const double on = __shfl_xor(nb_, o), od = __shfl_xor(db_, o);
+        const double ox = __shfl_xor(nx, o), oy = __shfl_xor(ny, o);
+        if (ok >= 0) take(ok, on, od, ox, oy);
+      }
+      nxt = __builtin_amdgcn_readfirstlane(nxt);
       if (nxt < 0) {
         bad = true;
         break;
       }
       if (nxt == j0) break;
       cur = nxt;
+      cx = __shfl(nx, 0);
+      cy = __shfl(ny, 0);
     }
     bad |= d > kRing;
-    if (!bad) {
-      for (int k = 0; k < d; ++k) dst.ring[e * kRing + k] = ring[k];
-      for (int k = d; k < kRing; ++k) dst.ring[e * kRing + k] = -1;
-      dst.deg[e] = d;
-    } else {
-      dst.deg[e] = 0;
-      for (int k = 0; k < kRing; ++k) dst.ring[e * kRing + k] = -1;
-      atomicOr(p.status, 2);
+    if (lane < kRing) dst.ring[(size_t)e * kRing + lane] = !bad && lane < d ? mine : -1;
+    if (lane == 0) {
+      dst.deg[e] = bad ? 0 : d;
+      if (bad) atomicOr(p.status, 2);
     }
   }
 }
@@ -628,6 +738,7 @@ template <typename T, bool FINISH>
 __global__ __launch_bounds__(256) void k_mv_geom(PM<T> p, MOut dst) {
   const int e = xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
   double dtb = 1e300;
+  if (e == 0) *p.count = 0;  // the walk that read it is done; the next check counts from zero
   if (e < p.n) {
     const int n = p.n;
     const double* X = dst.x;
@@ -1018,7 +1129,8 @@ PM<T> make_params(const dg_mesh* m, const void* in, void* out) {
   p.Ly = v.box[1];
   p.gamma = (T)m->cfg.gamma;
   p.motion = v.motion;
-  p.cand_cap = v.cand_cap;
+  p.list = v.list;
+  p.count = v.list + v.n;
   p.s0 = MSet{v.pos[v.cur], v.ring[v.cur], v.deg[v.cur], v.geo[v.cur]};
   p.sh = MSet{v.pos[1], v.ring[1], v.deg[1], v.geo[1]};
   p.xh = v.pos[1];
@@ -1063,8 +1175,9 @@ hipError_t step_t(dg_mesh* m, const void* in, void* out, const double* dt_dev, d
   if (e != hipSuccess) return e;
   // mesh of the half-step generators (candidates from t^n)
   const MOut half{v.pos[1], v.ring[1], v.deg[1], v.geo[1]};
-  const dim3 gw((p.n + kWalkThreads - 1) / kWalkThreads), bw(kWalkThreads);
-  hipLaunchKernelGGL((k_mv_walk<T>), gw, bw, 0, s, p, p.s0, half);
+  const dim3 gw(std::min((p.n + 3) / 4, kWalkBlocks));
+  hipLaunchKernelGGL((k_mv_check<T>), g, b, 0, s, p, p.s0, half);
+  hipLaunchKernelGGL((k_mv_walk<T>), gw, b, 0, s, p, p.s0, half);
   hipLaunchKernelGGL((k_mv_geom<T, false>), g, b, 0, s, p, half);
   e = mark();
   if (e != hipSuccess) return e;
@@ -1077,7 +1190,8 @@ hipError_t step_t(dg_mesh* m, const void* in, void* out, const double* dt_dev, d
   // mesh of t^{n+1} (candidates from the half step) and the new state
   if (want_dt) p.dtpart = m->dtpart;
   const MOut next{v.pos[v.nxt], v.ring[v.nxt], v.deg[v.nxt], v.geo[v.nxt]};
-  hipLaunchKernelGGL((k_mv_walk<T>), gw, bw, 0, s, p, p.sh, next);
+  hipLaunchKernelGGL((k_mv_check<T>), g, b, 0, s, p, p.sh, next);
+  hipLaunchKernelGGL((k_mv_walk<T>), gw, b, 0, s, p, p.sh, next);
   hipLaunchKernelGGL((k_mv_geom<T, true>), g, b, 0, s, p, next);
   e = hipGetLastError();
   if (e == hipSuccess) std::swap(v.cur, v.nxt);
@@ -1154,6 +1268,7 @@ void moving_destroy(dg_mesh* m) {
     (void)hipFree(v.geo[k]);
   }
   (void)hipFree(v.ua);
+  (void)hipFree(v.list);
   delete m->mvd;
   m->mvd = nullptr;
 }
@@ -1230,10 +1345,6 @@ dg_status moving_create(dg_mesh* m, const dg_mesh_desc* d) {
   v.motion = 1;
   v.cur = 0;
   v.nxt = 2;
-  // DG_MOVING_CANDIDATES caps the walk's LDS candidate list (tests use it to
-  // drive every cell through the streaming path)
-  if (const char* env = std::getenv("DG_MOVING_CANDIDATES"))
-    v.cand_cap = std::max(0, std::min(kCand, std::atoi(env)));
   hipError_t e = hipSuccess;
   for (int k = 0; k < 3 && e == hipSuccess; ++k) {
     e = hipMalloc((void**)&v.pos[k], sizeof(double) * 4 * n);
@@ -1242,6 +1353,8 @@ dg_status moving_create(dg_mesh* m, const dg_mesh_desc* d) {
     if (e == hipSuccess) e = hipMalloc((void**)&v.geo[k], sizeof(double) * kGeo * n);
   }
   if (e == hipSuccess) e = hipMalloc(&v.ua, m->elem * 12 * n);
+  if (e == hipSuccess) e = hipMalloc((void**)&v.list, sizeof(int) * (n + 1));
+  if (e == hipSuccess) e = hipMemset(v.list + n, 0, sizeof(int));
   if (e == hipSuccess)
     e = hipMemcpy(v.pos[0], pos.data(), sizeof(double) * 4 * n, hipMemcpyHostToDevice);
   if (e == hipSuccess)
@@ -1261,16 +1374,18 @@ hipError_t moving_init(dg_mesh* m) {
   PM<double> p;
   std::memset(&p, 0, sizeof(p));
   p.status = m->status;
-  p.cand_cap = v.cand_cap;
+  p.list = v.list;
+  p.count = v.list + v.n;
   p.n = v.n;
   p.Lx = v.box[0];
   p.Ly = v.box[1];
   p.gamma = m->cfg.gamma;
   const dim3 g((v.n + 255) / 256), b(256);
   const MOut first{v.pos[0], v.ring[0], v.deg[0], v.geo[0]};
-  const dim3 gw((v.n + kWalkThreads - 1) / kWalkThreads), bw(kWalkThreads);
-  hipLaunchKernelGGL((k_mv_walk<double>), gw, bw, 0, nullptr, p,
-                     MSet{v.pos[0], v.ring[1], v.deg[1], v.geo[1]}, first);
+  const dim3 gw(std::min((v.n + 3) / 4, kWalkBlocks));
+  const MSet given{v.pos[0], v.ring[1], v.deg[1], v.geo[1]};
+  hipLaunchKernelGGL((k_mv_check<double>), g, b, 0, nullptr, p, given, first);
+  hipLaunchKernelGGL((k_mv_walk<double>), gw, b, 0, nullptr, p, given, first);
   hipLaunchKernelGGL((k_mv_geom<double, false>), g, b, 0, nullptr, p, first);
   return hipGetLastError();
 }

@@ -1,0 +1,91 @@
+"""Moving mesh: which cells keep their ring.  A cell with 8 neighbours is the largest the check
+handles, one with 9 goes to the walk; a mesh at rest keeps every ring, one whose generators jump
+across their neighbours walks them.  Against the oracle's mesh, built from scratch.
+"""
+import math
+
+import numpy as np
+import pytest
+
+from workloads.voronoi import periodic_voronoi, random_voronoi_state
+
+pytestmark = pytest.mark.gpu
+G53 = 5.0 / 3.0
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+@pytest.fixture(scope="module")
+def mv():
+    from oracle import moving
+    return moving
+
+
+def _solver(d, limiter="weno", flux="exact"):
+    from paper_1305_5536_amd.solver import Solver, moving
+    return Solver(moving(d), gamma=G53, limiter=limiter, flux=flux)
+
+
+def _rings(s, d, mv):
+    got = s.geometry()
+    want = mv.neighbours(d)
+    for i in range(len(want)):
+        ring = got["ring"][i, :got["degree"][i]]
+        assert set(ring.tolist()) == set(want[i]), i
+        # counter-clockwise from the nearest neighbour
+        g = got["generators"]
+        o = g[ring] - g[i]
+        o -= np.round(o / np.asarray(d["box"])) * np.asarray(d["box"])
+        a = np.unwrap(np.arctan2(o[:, 1], o[:, 0]))
+        assert (np.diff(a) > 0).all() and a[-1] - a[0] < 2 * math.pi
+        assert np.argmin((o ** 2).sum(1)) == 0
+    return got
+
+
+@pytest.mark.parametrize("m", [7, 8, 9, 12])
+def test_ring_sizes(mv, torch_cuda, m):
+    rng = np.random.default_rng(m)
+    n0 = 500
+    P = periodic_voronoi(n0, seed=24)["generators"]
+    c, h = np.array([0.02, 0.97]), 1.0 / math.sqrt(n0)  # across the corner of the box
+    o = P - c
+    o -= np.round(o)
+    ang = 2 * math.pi * (np.arange(m) + rng.uniform(-0.05, 0.05, m)) / m
+    ring = c + h * np.stack([np.cos(ang), np.sin(ang)], 1)
+    P = np.mod(np.concatenate([P[np.linalg.norm(o, axis=1) > 2.2 * h], c[None], ring]), 1.0)
+    d = mv.voronoi(P, (1.0, 1.0))
+    assert len(mv.neighbours(d)[len(P) - m - 1]) == m
+    s = _solver(d)
+    _rings(s, d, mv)
+    U0 = random_voronoi_state(d, G53, seed=25, amp=0.2)
+    U, dt = s.to_device(U0), mv.cfl_dt(d, U0, G53, 0.3)
+    for _ in range(3):
+        ref, d = mv.step(d, U.cpu().numpy(), dt, G53, "weno", "exact")
+        U = s.step_mh(U, dt)
+        s.check()
+        assert np.abs(U.cpu().numpy() - ref).max() < 1e-11 * np.abs(ref).max()
+        _rings(s, d, mv)
+
+
+@pytest.mark.parametrize("dt_factor", [0.0, 1.0])
+def test_rest_and_motion(mv, torch_cuda, dt_factor):
+    """A step of size zero keeps every ring; a full step over a shear changes some."""
+    d = mv.voronoi(periodic_voronoi(900, seed=8)["generators"], (1.0, 1.0))
+    U0 = random_voronoi_state(d, G53, seed=5, amp=0.4)
+    s = _solver(d)
+    first = _rings(s, d, mv)
+    dt = dt_factor * mv.cfl_dt(d, U0, G53, 0.3)
+    U, changed = s.to_device(U0), 0
+    for _ in range(4):
+        _, d = mv.step(d, U.cpu().numpy(), dt, G53, "weno", "exact")
+        U = s.step_mh(U, dt)
+        got = _rings(s, d, mv)
+        changed += int((got["ring"] != first["ring"]).any(axis=1).sum())
+    s.check()
+    assert (changed > 0) == (dt_factor > 0)

@@ -64,6 +64,7 @@
 namespace dg {
 
 constexpr int kRing = 16;  // neighbours a cell may have
+constexpr int kTwice = 64;  // k_mv_walk to k_mv_geom: a neighbour appears twice in the ring
 constexpr int kFast = 8;   // neighbours of a cell whose ring k_mv_check can keep
 constexpr int kGeo = 6;    // V, centroid - generator (2), Mxx, Mxy, Myy
 constexpr int kWalkBlocks = 2048;  // most workgroups of the walk (four cells at a time each)
@@ -80,6 +81,9 @@ struct MVDev {
   int* deg[3] = {nullptr, nullptr, nullptr};     // [n]
   double* geo[3] = {nullptr, nullptr, nullptr};  // [kGeo][n]
   void* ua = nullptr;                            // limited state
+  double2* mid = nullptr;                        // [kRing][n]: face midpoints of t^n
+  void* pred = nullptr;                          // [14][n]: predictions and velocities
+  double2* shift = nullptr;                      // [n]: half-step generator - t^n centroid
   int* list = nullptr;                           // [n + 1]: cells to walk, their count last
   bool timing = false;                           // record events around each kernel
   std::vector<hipEvent_t> ev;                    // 5 per timed step
@@ -120,6 +124,12 @@ struct PM {
   int write_pos;  // k_mv_lim: write the half-step and next positions
   MSet s0;        // t^n
   MSet sh;        // half step
+  const double2* mid;    // [kRing][n] face midpoints of t^n from the generators
+  double2* mid_out;      // k_mv_geom: those of the mesh it finishes (NULL: not kept)
+  const T* pred;         // [14][n] half-step prediction (12) and velocity of each cell
+  T* pred_out;
+  const double2* shift;  // [n] half-step generator - t^n centroid
+  double2* shift_out;
   double* xh;     // positions written by k_mv_lim
   double* x1;
 };
@@ -140,55 +150,68 @@ __device__ __forceinline__ double advance(double x, double s, double w, double L
   return y;
 }
 
-// Circumcentre of generators a, b, c as an offset from generator f.  Worked
-// in the frame of the smallest of the three indices from minimum-image
-// offsets, without contraction, so that every cell sharing the vertex gets the
-// same bits before the final shift.
-__device__ __forceinline__ void circumcentre(const double* __restrict__ X, int n, double Lx,
-                                          double Ly, int a, int b, int c, int f, double& ox,
-                                          double& oy) {
+// Voronoi vertex of generators a, b, c (their circumcentre) as an offset from
+// the smallest of the three indices, which is returned in f.  Worked from
+// minimum-image offsets in that frame, without contraction, so that every cell
+// sharing the vertex gets the same bits.
+struct Vertex {
+  double x, y;
+  double2 origin;  // position of generator f
+  int f;
+};
+
+__device__ __forceinline__ Vertex vertex(const double2* __restrict__ P, double Lx, double Ly,
+                                         int a, int b, int c) {
 #pragma clang fp contract(off)
   int t;
   if (a > b) { t = a; a = b; b = t; }
   if (b > c) { t = b; b = c; c = t; }
   if (a > b) { t = a; a = b; b = t; }
-  // the interleaved copy of the positions: one 16-byte load per generator
-  const double2* P = reinterpret_cast<const double2*>(X + 2 * (size_t)n);
   const double2 pa = P[a], pb = P[b], pc = P[c];
   const double px = mimg(pb.x - pa.x, Lx), py = mimg(pb.y - pa.y, Ly);
   const double qx = mimg(pc.x - pa.x, Lx), qy = mimg(pc.y - pa.y, Ly);
   const double D = 2.0 * (px * qy - py * qx);
   const double pp = px * px + py * py, qq = qx * qx + qy * qy;
-  double ux = (qy * pp - py * qq) / D;
-  double uy = (px * qq - qx * pp) / D;
-  if (a != f) {
-    const double2 pf = P[f];
-    ux += mimg(pa.x - pf.x, Lx);
-    uy += mimg(pa.y - pf.y, Ly);
-  }
-  ox = ux;
-  oy = uy;
+  return Vertex{(qy * pp - py * qq) / D, (px * qq - qx * pp) / D, pa, a};
 }
 
-// Face between cells L < R whose Voronoi edge ends at the circumcentres of
-// (L, R, ka) and (L, R, kb): endpoints (from L's generator) ordered so that
-// the normal (e_y, -e_x)/|e| points from L towards R, the generator offset
-// dLR, and the length.  Every argument order gives the same bits.
+// The vertex as an offset from generator g at position pg.
+__device__ __forceinline__ void vertex_from(const Vertex& v, double Lx, double Ly, int g, double2 pg,
+                                            double& ox, double& oy) {
+#pragma clang fp contract(off)
+  ox = v.x;
+  oy = v.y;
+  if (v.f != g) {
+    ox += mimg(v.origin.x - pg.x, Lx);
+    oy += mimg(v.origin.y - pg.y, Ly);
+  }
+}
+
+// Circumcentre of generators a, b, c as an offset from generator f.
+__device__ __forceinline__ void circumcentre(const double* __restrict__ X, int n, double Lx,
+                                          double Ly, int a, int b, int c, int f, double& ox,
+                                          double& oy) {
+  // the interleaved copy of the positions: one 16-byte load per generator
+  const double2* P = reinterpret_cast<const double2*>(X + 2 * (size_t)n);
+  vertex_from(vertex(P, Lx, Ly, a, b, c), Lx, Ly, f, P[f], ox, oy);
+}
+
+// Face between cells L < R whose Voronoi edge ends at the vertices va and vb:
+// endpoints (from L's generator) ordered so that the normal (e_y, -e_x)/|e|
+// points from L towards R, the generator offset dLR, and the length.  Every
+// argument order gives the same bits.
 struct FaceG {
   double ax, ay, bx, by;  // endpoints
   double dx, dy;          // R's generator - L's generator
   double A, nx, ny;
 };
 
-__device__ __forceinline__ void face_geometry(const double* __restrict__ X, int n, double Lx,
-                                              double Ly, int L, int R, int ka, int kb,
-                                              FaceG& g) {
+__device__ __forceinline__ void face_geometry(double Lx, double Ly, int L, double2 pL, double2 pR,
+                                              const Vertex& va, const Vertex& vb, FaceG& g) {
 #pragma clang fp contract(off)
   double ax, ay, bx, by;
-  circumcentre(X, n, Lx, Ly, L, R, ka, L, ax, ay);
-  circumcentre(X, n, Lx, Ly, L, R, kb, L, bx, by);
-  const double2* P = reinterpret_cast<const double2*>(X + 2 * (size_t)n);
-  const double2 pL = P[L], pR = P[R];
+  vertex_from(va, Lx, Ly, L, pL, ax, ay);
+  vertex_from(vb, Lx, Ly, L, pL, bx, by);
   const double dx = mimg(pR.x - pL.x, Lx), dy = mimg(pR.y - pL.y, Ly);
   double ex = bx - ax, ey = by - ay;
   if (ey * dx - ex * dy < 0.0) {
@@ -208,14 +231,11 @@ __device__ __forceinline__ void face_geometry(const double* __restrict__ X, int 
   g.ny = -ex / g.A;
 }
 
-// Polygon moments about the generator from vertex offsets v[0..m): area,
-// first and second moments (fan triangles from the generator).
-__device__ __forceinline__ void polygon_moments(const double* vx, const double* vy, int m,
-                                                double* geo) {
+// Polygon moments about the generator, one edge of the polygon at a time: area,
+// first and second moments of the fan triangles from the generator.
+struct Moments {
   double V = 0, m1x = 0, m1y = 0, mxx = 0, mxy = 0, myy = 0;
-  for (int k = 0; k < m; ++k) {
-    const int k1 = k + 1 == m ? 0 : k + 1;
-    const double e0x = vx[k], e0y = vy[k], e1x = vx[k1], e1y = vy[k1];
+  __device__ __forceinline__ void add(double e0x, double e0y, double e1x, double e1y) {
     const double ar = 0.5 * (e0x * e1y - e0y * e1x);
     const double sx = e0x + e1x, sy = e0y + e1y;
     V += ar;
@@ -226,14 +246,16 @@ __device__ __forceinline__ void polygon_moments(const double* vx, const double* 
     mxy += w * (e0x * e0y + e1x * e1y + sx * sy);
     myy += w * (e0y * e0y + e1y * e1y + sy * sy);
   }
-  const double cx = m1x / V, cy = m1y / V;
-  geo[0] = V;
-  geo[1] = cx;
-  geo[2] = cy;
-  geo[3] = mxx - V * cx * cx;
-  geo[4] = mxy - V * cx * cy;
-  geo[5] = myy - V * cy * cy;
-}
+  __device__ __forceinline__ void geometry(double* geo) const {
+    const double cx = m1x / V, cy = m1y / V;
+    geo[0] = V;
+    geo[1] = cx;
+    geo[2] = cy;
+    geo[3] = mxx - V * cx * cx;
+    geo[4] = mxy - V * cx * cy;
+    geo[5] = myy - V * cy * cy;
+  }
+};
 
 // Vertices of cell e of a mesh set (offsets from its generator): vertex k is
 // the circumcentre of (e, ring[k-1], ring[k]).
@@ -267,6 +289,41 @@ __device__ __forceinline__ void prim4(const T* m, T gm1, T* w) {
   w[3] = gm1 * (m[3] - T(0.5) * (m[1] * w[1] + m[2] * w[2]));
 }
 
+// Half-step primitive prediction of a limited cell (Sec. 2.4): values at
+// the centroid advanced by h in w[0..3], primitive gradients in gx, gy.
+template <typename T>
+struct Pred {
+  T w[4], gx[4], gy[4];
+};
+
+template <typename T>
+__device__ __forceinline__ Pred<T> predict(const T* q, T gamma, T h) {
+  const T gm1 = gamma - T(1);
+  const T rho = q[0], ir = rcp(rho);
+  const T vx = q[3] * ir, vy = q[6] * ir;
+  const T v2 = vx * vx + vy * vy;
+  const T pr = gm1 * (q[9] - T(0.5) * rho * v2);
+  Pred<T> o;
+  o.gx[0] = q[1];
+  o.gy[0] = q[2];
+  o.gx[1] = (q[4] - vx * q[1]) * ir;
+  o.gy[1] = (q[5] - vx * q[2]) * ir;
+  o.gx[2] = (q[7] - vy * q[1]) * ir;
+  o.gy[2] = (q[8] - vy * q[2]) * ir;
+  o.gx[3] = gm1 * (q[10] - T(0.5) * v2 * q[1] - rho * (vx * o.gx[1] + vy * o.gx[2]));
+  o.gy[3] = gm1 * (q[11] - T(0.5) * v2 * q[2] - rho * (vx * o.gy[1] + vy * o.gy[2]));
+  const T div = o.gx[1] + o.gy[2];
+  const T rho_t = -(vx * o.gx[0] + vy * o.gy[0] + rho * div);
+  const T vx_t = -(vx * o.gx[1] + vy * o.gy[1] + o.gx[3] * ir);
+  const T vy_t = -(vx * o.gx[2] + vy * o.gy[2] + o.gy[3] * ir);
+  const T p_t = -(gamma * pr * div + vx * o.gx[3] + vy * o.gy[3]);
+  o.w[0] = rho + h * rho_t;
+  o.w[1] = vx + h * vx_t;
+  o.w[2] = vy + h * vy_t;
+  o.w[3] = pr + h * p_t;
+  return o;
+}
+
 // ------------------------------------------------------------- limiter --
 // Per cell of the mesh of t^n.  LIM 0 copies, 1 the Arepo limiter on the
 // conserved coefficients, 2 the WENO-type limiter on (rho, v, p) with the
@@ -284,32 +341,29 @@ __global__ __launch_bounds__(256) void k_mv_lim(PM<T> p) {
   const int* re = s.ring + e * kRing;
   const int d = min(s.deg[e], kRing);
   bool meshbad = s.deg[e] > kRing || s.deg[e] < 3;
+  const int4* R4 = reinterpret_cast<const int4*>(s.ring);
   for (int k = 0; k < d; ++k) {
+    // (entries beyond a ring's degree are -1)
     const int j = re[k];
-    bool back = false;
-    const int dj = min(s.deg[j], kRing);
-    for (int a = 0; a < dj; ++a) back |= s.ring[j * kRing + a] == e;
+    const int4 a = R4[4 * (size_t)j], b = R4[4 * (size_t)j + 1];
+    bool back = a.x == e || a.y == e || a.z == e || a.w == e || b.x == e || b.y == e ||
+                b.z == e || b.w == e;
+    if (!back && s.deg[j] > 8) {
+      const int4 c = R4[4 * (size_t)j + 2], f = R4[4 * (size_t)j + 3];
+      back = c.x == e || c.y == e || c.z == e || c.w == e || f.x == e || f.y == e || f.z == e ||
+             f.w == e;
+    }
     meshbad |= !back;
   }
   if (meshbad) atomicOr(p.status, 2);
   const double dcx = s.geo[1 * n + e], dcy = s.geo[2 * n + e];
-  // The faces are visited in passes that recompute what they need (the face
-  // centroid from the two circumcentres that end the face, the neighbour's
-  // centroid offset and means) instead of keeping per-face arrays, which
-  // would live in per-lane scratch memory.
-  // Face centroids, in order: vertex k is the circumcentre of (e, ring[k-1],
-  // ring[k]); face k runs from vertex k to vertex k+1.
+  // The faces are visited in passes that read the face midpoints k_mv_geom left
+  // and the neighbours' means, instead of keeping per-face arrays, which would
+  // live in per-lane scratch memory.
   auto faces = [&](auto&& f) {
-    if (d < 3) return;
-    double ax, ay;
-    circumcentre(s.x, n, p.Lx, p.Ly, e, re[d - 1], re[0], e, ax, ay);
-    const double a0x = ax, a0y = ay;
     for (int k = 0; k < d; ++k) {
-      double bx = a0x, by = a0y;
-      if (k + 1 < d) circumcentre(s.x, n, p.Lx, p.Ly, e, re[k], re[k + 1], e, bx, by);
-      f(k, re[k], (T)(0.5 * (ax + bx) - dcx), (T)(0.5 * (ay + by) - dcy));
-      ax = bx;
-      ay = by;
+      const double2 m = p.mid[(size_t)k * n + e];
+      f(k, re[k], (T)(m.x - dcx), (T)(m.y - dcy));
     }
   };
   if (LIM != 0) {
@@ -462,6 +516,19 @@ __global__ __launch_bounds__(256) void k_mv_lim(PM<T> p) {
     }
     const double x = s.x[e], y = s.x[n + e];
     const double hx = advance(x, 0.5 * dt, wx, p.Lx), hy = advance(y, 0.5 * dt, wy, p.Ly);
+    // what both cells of every face need of this one in the update: its half-step
+    // prediction, its velocity and where its t^n centroid lies from its half-step
+    // generator
+    const Pred<T> w = predict(q, p.gamma, T(0.5 * dt));
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      p.pred_out[(size_t)v * n + e] = w.w[v];
+      p.pred_out[(size_t)(4 + v) * n + e] = w.gx[v];
+      p.pred_out[(size_t)(8 + v) * n + e] = w.gy[v];
+    }
+    p.pred_out[(size_t)12 * n + e] = p.motion ? q[3] / q[0] : T(0);
+    p.pred_out[(size_t)13 * n + e] = p.motion ? q[6] / q[0] : T(0);
+    p.shift_out[e] = make_double2(mimg(hx - x, p.Lx) - dcx, mimg(hy - y, p.Ly) - dcy);
     const double nx1 = advance(x, dt, wx, p.Lx), ny1 = advance(y, dt, wy, p.Ly);
     p.xh[e] = hx;
     p.xh[n + e] = hy;
@@ -726,9 +793,12 @@ __global__ __launch_bounds__(256) void k_mv_walk(PM<T> p, MSet src, MOut dst) {
       cy = __shfl(ny, 0);
     }
     bad |= d > kRing;
+    bool twice = false;
+    for (int t = 1; t < kRing; ++t) twice |= lane + t < d && __shfl_down(mine, t) == mine;
+    const bool flag = __any(twice);
     if (lane < kRing) dst.ring[(size_t)e * kRing + lane] = !bad && lane < d ? mine : -1;
     if (lane == 0) {
-      dst.deg[e] = bad ? 0 : d;
+      dst.deg[e] = bad ? 0 : d + (flag ? kTwice : 0);
       if (bad) atomicOr(p.status, 2);
     }
   }
@@ -741,47 +811,81 @@ __global__ __launch_bounds__(256) void k_mv_geom(PM<T> p, MOut dst) {
   if (e == 0) *p.count = 0;  // the walk that read it is done; the next check counts from zero
   if (e < p.n) {
     const int n = p.n;
-    const double* X = dst.x;
-    const double xe = X[e], ye = X[n + e];
+    const double2* P = reinterpret_cast<const double2*>(dst.x + 2 * (size_t)n);
+    const double2 pe = P[e];
+    const double xe = pe.x, ye = pe.y;
+    int* ring = dst.ring + (size_t)e * kRing;
+    // (k_mv_walk adds kTwice to the degree where a neighbour appears twice)
     int d = dst.deg[e];
+    bool look = d >= kTwice;
+    d &= kTwice - 1;
     bool bad = d < 3 || d > kRing;
-    int ring[kRing];
-    for (int k = 0; k < kRing; ++k) ring[k] = dst.ring[e * kRing + k];
-    if (!bad) {
+    Moments mom;
+    // f(k, a, b) for every edge of the polygon: face k runs from vertex k, the one
+    // of (e, ring[k-1], ring[k]), to vertex k + 1
+    auto edges = [&](auto&& f) {
+      const int last = ring[d - 1], first = ring[0];
+      double ax, ay;
+      vertex_from(vertex(P, p.Lx, p.Ly, e, last, first), p.Lx, p.Ly, e, pe, ax, ay);
+      const double a0x = ax, a0y = ay;
+      int j = first;
+      for (int k = 0; k < d; ++k) {
+        double bx = a0x, by = a0y;
+        int jn = first;
+        if (k + 1 < d) {
+          jn = ring[k + 1];
+          vertex_from(vertex(P, p.Lx, p.Ly, e, j, jn), p.Lx, p.Ly, e, pe, bx, by);
+        }
+        f(k, j, ax, ay, bx, by);
+        ax = bx;
+        ay = by;
+        j = jn;
+      }
+    };
+    double perim = 0.0;
+    auto measure = [&]() {
+      mom = Moments();
+      perim = 0.0;
+      edges([&](int k, int j, double ax, double ay, double bx, double by) {
+        const double ex = bx - ax, ey = by - ay, l2 = ex * ex + ey * ey;
+        const double2 pj = P[j];
+        const double gx = mimg(pj.x - xe, p.Lx), gy = mimg(pj.y - ye, p.Ly);
+        look |= !(l2 > 1e-16 * (gx * gx + gy * gy));
+        mom.add(ax, ay, bx, by);
+        if (FINISH) perim += sqrt(l2);
+        if (p.mid_out) p.mid_out[(size_t)k * n + e] = make_double2(0.5 * (ax + bx), 0.5 * (ay + by));
+      });
+    };
+    if (!bad) measure();
+    if (!bad && look) {
       // drop the faces shorter than 1e-10 of their generators' distance (their
       // existence is decided by rounding); both cells of such a face decide it
-      // from the same canonical operands
-      int keep[kRing];
-      int dk = 0;
+      // from the same canonical operands.  Only a cell with a face near that
+      // length comes here.
+      const int first = ring[0];
+      int prev = ring[d - 1], dk = 0;
       for (int k = 0; k < d; ++k) {
-        const int j = ring[k];
+        const int j = ring[k], next = k + 1 == d ? first : ring[k + 1];
         const int L = min(e, j), Rr = max(e, j);
         FaceG g;
-        face_geometry(X, n, p.Lx, p.Ly, L, Rr, ring[k == 0 ? d - 1 : k - 1],
-                      ring[k + 1 == d ? 0 : k + 1], g);
-        if (g.A >= 1e-10 * sqrt(g.dx * g.dx + g.dy * g.dy)) keep[dk++] = j;
+        face_geometry(p.Lx, p.Ly, L, P[L], P[Rr], vertex(P, p.Lx, p.Ly, L, Rr, prev),
+                      vertex(P, p.Lx, p.Ly, L, Rr, next), g);
+        if (g.A >= 1e-10 * sqrt(g.dx * g.dx + g.dy * g.dy)) ring[dk++] = j;
+        prev = j;
       }
       for (int k = 0; k < dk; ++k)
-        for (int k2 = k + 1; k2 < dk; ++k2) bad |= keep[k] == keep[k2];
+        for (int k2 = k + 1; k2 < dk; ++k2) bad |= ring[k] == ring[k2];
       bad |= dk < 3;
-      if (dk != d && !bad) {
-        for (int k = 0; k < dk; ++k) dst.ring[e * kRing + k] = keep[k];
-        for (int k = dk; k < kRing; ++k) dst.ring[e * kRing + k] = -1;
-        dst.deg[e] = dk;
-      }
+      for (int k = dk; k < kRing; ++k) ring[k] = -1;
+      dst.deg[e] = bad ? 0 : dk;
+      if (bad) atomicOr(p.status, 2);
+      const bool fewer = dk != d;
       d = dk;
-      for (int k = 0; k < d; ++k) ring[k] = keep[k];
-      if (bad) {
-        dst.deg[e] = 0;
-        atomicOr(p.status, 2);
-      }
+      if (!bad && fewer) measure();
     }
     double geo[kGeo] = {0, 0, 0, 0, 0, 0};
-    double vx[kRing], vy[kRing];
     if (!bad) {
-      for (int k = 0; k < d; ++k)
-        circumcentre(X, n, p.Lx, p.Ly, e, ring[k == 0 ? d - 1 : k - 1], ring[k], e, vx[k], vy[k]);
-      polygon_moments(vx, vy, d, geo);
+      mom.geometry(geo);
       bad |= !(geo[0] > 0.0) || !(geo[3] * geo[5] - geo[4] * geo[4] > 0.0);
       if (bad) atomicOr(p.status, 2);
     }
@@ -792,8 +896,6 @@ __global__ __launch_bounds__(256) void k_mv_geom(PM<T> p, MOut dst) {
       geo[3] = geo[5] = 1.0;
     }
     for (int k = 0; k < kGeo; ++k) dst.geo[(size_t)k * n + e] = geo[k];
-    (void)xe;
-    (void)ye;
     if (FINISH) {
       const double dt = step_size(p);
       T Q[12];
@@ -829,13 +931,11 @@ __global__ __launch_bounds__(256) void k_mv_geom(PM<T> p, MOut dst) {
         const double pr =
             ((double)p.gamma - 1.0) * ((double)u[9] - 0.5 * rho * (ux * ux + uy * uy));
         const double cs = sqrt((double)p.gamma * pr * ir);
-        double s = 0.0;
-        for (int k = 0; k < d; ++k) {
-          const int k1 = k + 1 == d ? 0 : k + 1;
-          const double ex = vx[k1] - vx[k], ey = vy[k1] - vy[k];
-          s += cs * sqrt(ex * ex + ey * ey);
-          if (!p.motion) s += fabs(ux * ey - uy * ex);  // A |v . n|, n = (e_y, -e_x) / A
-        }
+        double s = cs * perim;
+        if (!p.motion)  // A |v . n|, n = (e_y, -e_x) / A
+          edges([&](int, int, double ax, double ay, double bx, double by) {
+            s += fabs(ux * (by - ay) - uy * (bx - ax));
+          });
         dtb = 2.0 * V / s;
       }
     }
@@ -847,41 +947,6 @@ __global__ __launch_bounds__(256) void k_mv_geom(PM<T> p, MOut dst) {
 }
 
 // ------------------------------------------------------------- update --
-// Half-step primitive prediction of a limited cell (Sec. 2.4): values at
-// the centroid advanced by h in w[0..3], primitive gradients in gx, gy.
-template <typename T>
-struct Pred {
-  T w[4], gx[4], gy[4];
-};
-
-template <typename T>
-__device__ __forceinline__ Pred<T> predict(const T* q, T gamma, T h) {
-  const T gm1 = gamma - T(1);
-  const T rho = q[0], ir = rcp(rho);
-  const T vx = q[3] * ir, vy = q[6] * ir;
-  const T v2 = vx * vx + vy * vy;
-  const T pr = gm1 * (q[9] - T(0.5) * rho * v2);
-  Pred<T> o;
-  o.gx[0] = q[1];
-  o.gy[0] = q[2];
-  o.gx[1] = (q[4] - vx * q[1]) * ir;
-  o.gy[1] = (q[5] - vx * q[2]) * ir;
-  o.gx[2] = (q[7] - vy * q[1]) * ir;
-  o.gy[2] = (q[8] - vy * q[2]) * ir;
-  o.gx[3] = gm1 * (q[10] - T(0.5) * v2 * q[1] - rho * (vx * o.gx[1] + vy * o.gx[2]));
-  o.gy[3] = gm1 * (q[11] - T(0.5) * v2 * q[2] - rho * (vx * o.gy[1] + vy * o.gy[2]));
-  const T div = o.gx[1] + o.gy[2];
-  const T rho_t = -(vx * o.gx[0] + vy * o.gy[0] + rho * div);
-  const T vx_t = -(vx * o.gx[1] + vy * o.gy[1] + o.gx[3] * ir);
-  const T vy_t = -(vx * o.gx[2] + vy * o.gy[2] + o.gy[3] * ir);
-  const T p_t = -(gamma * pr * div + vx * o.gx[3] + vy * o.gy[3]);
-  o.w[0] = rho + h * rho_t;
-  o.w[1] = vx + h * vx_t;
-  o.w[2] = vy + h * vy_t;
-  o.w[3] = pr + h * p_t;
-  return o;
-}
-
 // Conserved state, boosted into the frame moving with (wx, wy), of the
 // predicted primitive polynomial at offset (rx, ry) from the centroid.
 template <typename T>
@@ -948,6 +1013,18 @@ __device__ __forceinline__ void riemann_n(const T* uL, const T* uR, T nx, T ny, 
   F[3] = G[3];
 }
 
+template <typename T>
+__device__ __forceinline__ void load_pred(const PM<T>& p, int e, Pred<T>& w, T& vx, T& vy) {
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    w.w[v] = p.pred[(size_t)v * p.n + e];
+    w.gx[v] = p.pred[(size_t)(4 + v) * p.n + e];
+    w.gy[v] = p.pred[(size_t)(8 + v) * p.n + e];
+  }
+  vx = p.pred[(size_t)12 * p.n + e];
+  vy = p.pred[(size_t)13 * p.n + e];
+}
+
 // The register budget of two waves per SIMD: with the exact solver in FP64
 // the kernel needs ~280 registers, and one wave per SIMD cannot hide the
 // neighbour gathers behind the divergent Newton loops; under the cap it spills
@@ -964,43 +1041,45 @@ void k_mv_upd(PM<T> p) {
   const T gamma = p.gamma, igm1 = rcp(gamma - T(1));
   const MSet& s0 = p.s0;
   const MSet& sh = p.sh;
-  const double* Xh = sh.x;
-  // interleaved (x, y) positions of the half step and of t^n
-  const double2* PH = reinterpret_cast<const double2*>(Xh + 2 * (size_t)n);
-  const double2* P0 = reinterpret_cast<const double2*>(s0.x + 2 * (size_t)n);
+  // interleaved (x, y) positions of the half step
+  const double2* PH = reinterpret_cast<const double2*>(sh.x + 2 * (size_t)n);
   bool bad = false;
-  T qe[12];
-  load12(p.ua, n, e, qe);
-  const T wex = p.motion ? qe[3] / qe[0] : T(0), wey = p.motion ? qe[6] / qe[0] : T(0);
+  Pred<T> pe;
+  T wex, wey;
+  load_pred(p, e, pe, wex, wey);
+  const double2 he = PH[e], oe = p.shift[e];
   T S0[4] = {T(0), T(0), T(0), T(0)}, Sx[4] = {T(0), T(0), T(0), T(0)},
     Sy[4] = {T(0), T(0), T(0), T(0)};
   const int d = min(sh.deg[e], kRing);
   constexpr double kG = 0.28867513459481288225;  // 1/(2 sqrt 3)
+  const int* ring = sh.ring + (size_t)e * kRing;
+  // vertex k, of (e, ring[k-1], ring[k]), ends faces k - 1 and k
+  Vertex va{};
+  if (d > 0) va = vertex(PH, p.Lx, p.Ly, e, ring[d - 1], ring[0]);
+  const Vertex v0 = va;
   for (int k = 0; k < d; ++k) {
-    const int j = sh.ring[e * kRing + k];
-    const int jp = sh.ring[e * kRing + (k == 0 ? d - 1 : k - 1)];
-    const int jn = sh.ring[e * kRing + (k + 1 == d ? 0 : k + 1)];
-    const int L = min(e, j), R = max(e, j);
+    const int j = ring[k];
+    const bool low = e < j;  // e is the face's L cell
+    const double2 hj = PH[j], oj = p.shift[j];
+    Vertex vb = v0;
+    if (k + 1 < d) vb = vertex(PH, p.Lx, p.Ly, e, j, ring[k + 1]);
     FaceG g;
-    face_geometry(Xh, n, p.Lx, p.Ly, L, R, jp, jn, g);
-    // both cells' limited polynomials, predicted half a step
-    T qL[12], qR[12];
-    load12(p.ua, n, L, qL);
-    load12(p.ua, n, R, qR);
-    const Pred<T> pL = predict(qL, gamma, half), pR = predict(qR, gamma, half);
-    const T wLx = p.motion ? qL[3] / qL[0] : T(0), wLy = p.motion ? qL[6] / qL[0] : T(0);
-    const T wRx = p.motion ? qR[3] / qR[0] : T(0), wRy = p.motion ? qR[6] / qR[0] : T(0);
-    // offsets of L's half-step generator from its t^n centroid, and R's
-    const double2 hL = PH[L], hR = PH[R], zL = P0[L], zR = P0[R];
-    const double oLx = mimg(hL.x - zL.x, p.Lx) - s0.geo[1 * n + L];
-    const double oLy = mimg(hL.y - zL.y, p.Ly) - s0.geo[2 * n + L];
-    const double oRx = mimg(hR.x - zR.x, p.Lx) - s0.geo[1 * n + R] - g.dx;
-    const double oRy = mimg(hR.y - zR.y, p.Ly) - s0.geo[2 * n + R] - g.dy;
+    face_geometry(p.Lx, p.Ly, low ? e : j, low ? he : hj, low ? hj : he, va, vb, g);
+    va = vb;
+    // the neighbour's half-step prediction; offsets from both t^n centroids
+    Pred<T> pj;
+    T wjx, wjy;
+    load_pred(p, j, pj, wjx, wjy);
+    const T wLx = low ? wex : wjx, wLy = low ? wey : wjy;
+    const T wRx = low ? wjx : wex, wRy = low ? wjy : wey;
+    // (R's generator lies at g.d from L's)
+    const double oex = low ? oe.x : oe.x - g.dx, oey = low ? oe.y : oe.y - g.dy;
+    const double ojx = low ? oj.x - g.dx : oj.x, ojy = low ? oj.y - g.dy : oj.y;
     const double dd = g.dx * g.dx + g.dy * g.dy;
     const T nx = (T)g.nx, ny = (T)g.ny, wq = (T)(0.5 * g.A);
     const double mx = 0.5 * (g.ax + g.bx), my = 0.5 * (g.ay + g.by);
     const double tx = kG * (g.bx - g.ax), ty = kG * (g.by - g.ay);
-    const T sg = e == L ? -wq : wq;
+    const T sg = low ? -wq : wq;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const double gx = q == 0 ? mx - tx : mx + tx, gy = q == 0 ? my - ty : my + ty;
@@ -1010,15 +1089,19 @@ void k_mv_upd(PM<T> p) {
                          (double)(wLy - wRy) * (gy - 0.5 * g.dy)) / dd;
       const T fwx = (T)(0.5 * (double)(wLx + wRx) + sw * g.dx);
       const T fwy = (T)(0.5 * (double)(wLy + wRy) + sw * g.dy);
-      const T rLx = (T)(gx + oLx), rLy = (T)(gy + oLy);
-      const T rRx = (T)(gx + oRx), rRy = (T)(gy + oRy);
-      T uL[4], uR[4], F[4];
-      boosted_state(pL, rLx, rLy, fwx, fwy, igm1, uL);
-      boosted_state(pR, rRx, rRy, fwx, fwy, igm1, uR);
+      const T rex = (T)(gx + oex), rey = (T)(gy + oey);
+      T ue[4], uj[4], uL[4], uR[4], F[4];
+      boosted_state(pe, rex, rey, fwx, fwy, igm1, ue);
+      boosted_state(pj, (T)(gx + ojx), (T)(gy + ojy), fwx, fwy, igm1, uj);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        uL[v] = low ? ue[v] : uj[v];
+        uR[v] = low ? uj[v] : ue[v];
+      }
       riemann_n<T, RS>(uL, uR, nx, ny, gamma, F, bad);
       unboost(F, fwx, fwy);
-      const T rx = (e == L ? rLx : rRx) - half * wex;
-      const T ry = (e == L ? rLy : rRy) - half * wey;
+      const T rx = rex - half * wex;
+      const T ry = rey - half * wey;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         S0[v] += sg * F[v];
@@ -1031,9 +1114,7 @@ void k_mv_upd(PM<T> p) {
   {
     const double Vh = sh.geo[e], a = sh.geo[3 * n + e], b = sh.geo[4 * n + e],
                  c = sh.geo[5 * n + e];
-    const double2 he = PH[e], ze = P0[e];
-    const double ox = mimg(he.x - ze.x, p.Lx) + sh.geo[1 * n + e] - s0.geo[1 * n + e];
-    const double oy = mimg(he.y - ze.y, p.Ly) + sh.geo[2 * n + e] - s0.geo[2 * n + e];
+    const double ox = oe.x + sh.geo[1 * n + e], oy = oe.y + sh.geo[2 * n + e];
     const double tr = 0.5 * (a + c), disc = sqrt(0.25 * (a - c) * (a - c) + b * b);
     const double lam[2] = {tr + disc, tr - disc};
     double ev[2][2];
@@ -1050,7 +1131,6 @@ void k_mv_upd(PM<T> p) {
         ev[k][1] = vy / nn;
       }
     }
-    const Pred<T> pe = predict(qe, gamma, half);
     const T wv = (T)(0.25 * Vh);
     for (int k = 0; k < 2; ++k) {
       const double r = sqrt(2.0 * fmax(lam[k], 0.0) / Vh);
@@ -1077,6 +1157,8 @@ void k_mv_upd(PM<T> p) {
   const T V0 = (T)s0.geo[e], Mxx = (T)s0.geo[3 * n + e], Mxy = (T)s0.geo[4 * n + e],
           Myy = (T)s0.geo[5 * n + e];
   const T tdt = (T)dt;
+  T qe[12];
+  load12(p.ua, n, e, qe);
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     p.out[(size_t)(3 * v) * n + e] = V0 * qe[3 * v] + tdt * S0[v];
@@ -1131,6 +1213,10 @@ PM<T> make_params(const dg_mesh* m, const void* in, void* out) {
   p.motion = v.motion;
   p.list = v.list;
   p.count = v.list + v.n;
+  p.mid = v.mid;
+  p.pred = static_cast<const T*>(v.pred);
+  p.pred_out = static_cast<T*>(v.pred);
+  p.shift = p.shift_out = v.shift;
   p.s0 = MSet{v.pos[v.cur], v.ring[v.cur], v.deg[v.cur], v.geo[v.cur]};
   p.sh = MSet{v.pos[1], v.ring[1], v.deg[1], v.geo[1]};
   p.xh = v.pos[1];
@@ -1189,6 +1275,7 @@ hipError_t step_t(dg_mesh* m, const void* in, void* out, const double* dt_dev, d
   if (e != hipSuccess) return e;
   // mesh of t^{n+1} (candidates from the half step) and the new state
   if (want_dt) p.dtpart = m->dtpart;
+  p.mid_out = v.mid;
   const MOut next{v.pos[v.nxt], v.ring[v.nxt], v.deg[v.nxt], v.geo[v.nxt]};
   hipLaunchKernelGGL((k_mv_check<T>), g, b, 0, s, p, p.sh, next);
   hipLaunchKernelGGL((k_mv_walk<T>), gw, b, 0, s, p, p.sh, next);
@@ -1269,6 +1356,9 @@ void moving_destroy(dg_mesh* m) {
   }
   (void)hipFree(v.ua);
   (void)hipFree(v.list);
+  (void)hipFree(v.mid);
+  (void)hipFree(v.pred);
+  (void)hipFree(v.shift);
   delete m->mvd;
   m->mvd = nullptr;
 }
@@ -1353,6 +1443,9 @@ dg_status moving_create(dg_mesh* m, const dg_mesh_desc* d) {
     if (e == hipSuccess) e = hipMalloc((void**)&v.geo[k], sizeof(double) * kGeo * n);
   }
   if (e == hipSuccess) e = hipMalloc(&v.ua, m->elem * 12 * n);
+  if (e == hipSuccess) e = hipMalloc((void**)&v.mid, sizeof(double2) * kRing * n);
+  if (e == hipSuccess) e = hipMalloc(&v.pred, m->elem * 14 * n);
+  if (e == hipSuccess) e = hipMalloc((void**)&v.shift, sizeof(double2) * n);
   if (e == hipSuccess) e = hipMalloc((void**)&v.list, sizeof(int) * (n + 1));
   if (e == hipSuccess) e = hipMemset(v.list + n, 0, sizeof(int));
   if (e == hipSuccess)
@@ -1376,6 +1469,7 @@ hipError_t moving_init(dg_mesh* m) {
   p.status = m->status;
   p.list = v.list;
   p.count = v.list + v.n;
+  p.mid_out = v.mid;
   p.n = v.n;
   p.Lx = v.box[0];
   p.Ly = v.box[1];

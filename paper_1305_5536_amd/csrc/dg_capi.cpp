@@ -214,6 +214,16 @@ static int default_step_rows(int64_t ntiles_x, int64_t nrows, bool f64) {
       [&](int64_t w) { return f64 ? (double)ceil_div(w, n) : load_pairs(ceil_div(w, n), 1.45); });
 }
 
+// Whether the fused step hands the rows of a strip to the waves of a workgroup
+// (one workgroup per CU, by registers) instead of marching them: FP64 while there
+// is a CU for each (224 x 256, 256 workgroups, 22.8 against 32 us; 280 x 224, 280
+// of them, 34.6 against 33.4), FP32 for two rounds (280 x 256 24.1 against 25.6 us,
+// 392 x 292, 511 workgroups, 25.6 against 26.9; 448^2, 896, 38.0 against 35.2).
+// The choice depends on the mesh alone, not on the tiling.
+static bool small_step(int64_t ntiles_x, int64_t nrows, bool f64) {
+  return ntiles_x * ceil_div(nrows, kSmallRows) <= simds() / (f64 ? 4 : 2);
+}
+
 // Rows per wave of the 2D MHD stage kernel.  FP64 one wave per SIMD, three rows
 // beyond its own (the prologue loads and limits two rows and solves one extra
 // y-face row) (512^2: 5 rows, one round of 927 waves, 0.111 ms per step against
@@ -460,6 +470,8 @@ dg_status dg_mesh_create(const dg_mesh_desc* d, const dg_config* cfg, dg_mesh_t*
     m->c2.step_rows =
         default_step_rows(m->c2.step_tiles_x, d->n[1], cfg->precision == DG_FP64);
     m->c2.step_tiles_y = (int)((d->n[1] + m->c2.step_rows - 1) / m->c2.step_rows);
+    m->c2.step_small =
+        small_step(m->c2.step_tiles_x, d->n[1], cfg->precision == DG_FP64);
     if (cfg->physics == DG_EULER) {
       // the static scratch of dg_cfl_dt_static on this device (the device
       // that is current here is the mesh's); without its address only that

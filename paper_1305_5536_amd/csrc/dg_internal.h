@@ -22,6 +22,8 @@ enum StageMode : int {
   kStep = 5     // out = one SSP-RK2 step of in (both stages in one pass)
 };
 
+constexpr int kSmallRows = 4;  // rows of a workgroup of the small-mesh step
+
 // Geometry and launch shape of a periodic 2D Cartesian mesh.
 struct Cart2D {
   int nx, ny;
@@ -31,6 +33,7 @@ struct Cart2D {
   int tiles_x, tiles_y;
   // the fused SSP-RK2 step (2D Euler): 56 output columns per wave
   int step_rows, step_tiles_x, step_tiles_y;
+  bool step_small;  // few enough rows for a workgroup of row-waves per strip of rows
 };
 
 struct Cart3D {

@@ -84,3 +84,31 @@ def test_fused_step_of_a_large_mesh_matches_the_stage_pair(torch_cuda, shape, to
     b = s.stage2(U, V1, dt, s.empty()).reshape(12, -1)
     for k in range(12):
         assert (a[k] - b[k]).abs().max() <= tol * b[k].abs().max() * (1 if k % 3 == 0 else shape[0])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("limiter", [True, False])
+@pytest.mark.parametrize("shape", [(5, 1), (55, 2), (57, 3), (3, 11), (56, 4), (130, 33),
+                                   (113, 340), (113, 341), (113, 680), (113, 681)])
+def test_fused_step_of_a_small_mesh_matches_the_stage_pair(torch_cuda, shape, limiter, precision):
+    """A few rows (fewer than a workgroup's four, not a multiple of them), ragged strips, and both
+    sides of the lines between row-waves and marching waves (256 workgroups, FP32 512): the fused step equals
+    the stage kernels to rounding, and the step size it returns is the CFL step of its output.
+    Bounds: 45 units of rounding of the largest value (slopes: per cell width)."""
+    torch = torch_cuda
+    from paper_1305_5536_amd.solver import Solver, cartesian
+    tol = 45 * (2.0 ** -52 if precision == "fp64" else 2.0 ** -23)
+    s = Solver(cartesian(shape, (0.0, 0.0), (1.0, 1.0)), precision=precision, gamma=G53,
+               limiter=limiter)
+    U = s.to_device(W.random_p1_state(shape, (0.0, 0.0), (1.0, 1.0), G53, seed=17, amp=0.1))
+    dt = s.cfl_dt(U, 0.2)
+    nxt = torch.empty_like(dt)
+    out = torch.full_like(U, float("nan"))
+    a = s.step(U, dt, cfl=0.2, dt_next=nxt, out=out).reshape(12, -1)
+    s.check()
+    b = s.stage2(U, s.stage1(U, dt, s.empty()), dt, s.empty()).reshape(12, -1)
+    scale = b[0::3].abs().max()
+    for k in range(12):
+        assert (a[k] - b[k]).abs().max() <= tol * scale * (1 if k % 3 == 0 else max(shape))
+    want = s.cfl_dt(out, 0.2)
+    assert abs(float(nxt) - float(want)) <= tol * float(want)

@@ -32,8 +32,8 @@
 // ranges and entries, geometry, Pi(U^n), the first pass's slots) are issued
 // before the first barrier, so that their latency overlaps phase 0.
 // A stand-alone limiter kernel (k_fl_lim) serves dg_limit.  The discrete
-// adjoint of a step (k_adjfl_L, k_adjfl_lim, k_adjfl_msg) gathers over the
-// global incidence lists, one thread per cell.
+// adjoint of a step sweeps the same blocks (k_adjfl_L) and transposes the limiter
+// over the global incidence lists, one thread per cell (k_adjfl_lim, k_adjfl_msg).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -67,10 +67,8 @@ struct FLDev {
   int* lim_nbr;       // neighbour cell of each incidence
   void* lim_geo;      // [ninc][2] face-centroid offsets, then [ninc][2] A n outward
   void* cell_perim;   // [ncells] sum of face lengths
-  // the discrete adjoint (gathers over the global CSR)
+  // the discrete adjoint (its limiter gathers over the global CSR)
   int* inc_face;      // [ninc] face id << 1 | side (0: the cell is L) of each incidence
-  int* face_lr;       // [nfaces][2] L, R
-  void* face_geo;     // [nfaces][8] nx, ny, A, x_f - c_L (2), c_R' - c_L (2), 0
 };
 
 namespace {
@@ -743,17 +741,18 @@ hipError_t cfl_t(const dg_mesh* m, const void* U, hipStream_t s) {
 // ------------------------------------------------------- discrete adjoint --
 // Adjoint of a stage (as for the Cartesian meshes):
 //   out = Pi_P^T lamW,   lamW = c_id lam + c_L (dL/dW)^T lam + c_extra extra,
-// W = Pi(P), the branch the forward step takes (dt frozen).  k_adjfl_L gathers
-// lamW of a cell over its incidences and its volume points, k_adjfl_lim applies
-// the transpose of each cell's own limiter and leaves a message for the one
-// neighbour whose mean set a bound, k_adjfl_msg adds each cell's messages.  One
-// thread per cell, no atomics; the flux Jacobians come from one reverse sweep per
-// Gauss point (hll_n_vjp), the linear parts (Gauss-point extrapolation, residual
-// weights, M^-1) are transposed by hand.  The gathers' latency bounds all three.
-// Measured (262144 cells, FP64, one adjoint stage): k_adjfl_L 0.129 ms (0.214 ms
-// with a forward-mode solve per state component), k_adjfl_lim 0.044 and
-// k_adjfl_msg 0.017 ms (1.10 ms for differentiating, per coefficient, every
-// limiter that reads a cell).  The adjoint step 2.64 -> 0.42 ms.
+// W = Pi(P), the branch the forward step takes (dt frozen).  k_adjfl_L computes
+// lamW block by block from the faces and the cells' volume points, k_adjfl_lim
+// applies the transpose of each cell's own limiter and leaves a message for the one
+// neighbour whose mean set a bound, k_adjfl_msg adds each cell's messages.  No
+// atomics; the flux Jacobians come from one reverse sweep per Gauss point
+// (hll_n_vjp), the linear parts (Gauss-point extrapolation, residual weights, M^-1)
+// are transposed by hand.  Measured (262144 cells, FP64, one adjoint stage):
+// k_adjfl_L 0.078 ms, bound by the latency of its loads beside 43 us of traffic
+// (0.134 ms with a thread per cell that sweeps its faces from gathered neighbours,
+// 0.107 with those gathers in XCD order and two waves per SIMD, 0.093 as one
+// workgroup per CU with separate tables), k_adjfl_lim 0.044 and k_adjfl_msg 0.017 ms
+// (gathers).  The adjoint step 0.42 -> 0.33 ms.
 template <typename T>
 struct PFA {
   const T* W;      // Pi(P)
@@ -772,10 +771,17 @@ struct PFA {
   const int* inc0;
   const int* nbr;
   const int* inc_face;
-  const int* face_lr;
-  const T* face_geo;
   const T* lim_geo;
   const T* cell_geo;
+  // the blocks (k_adjfl_L)
+  const int* blk_cell0;
+  const int* blk_slot0;
+  const int* blk_halo0;
+  const int* halo_cell;
+  const int* slot_lr;
+  const T* slot_geo;
+  const int* cell_inc0;
+  const int* cell_inc;
 };
 
 // Cotangents of a cell's residual sums from the adjoint of its time
@@ -801,12 +807,12 @@ __device__ __forceinline__ void cotangents(const T* lam, const T* cg, Cot<T>& c)
   }
 }
 
-// Vector-Jacobian product of hll_n on one side: ub is the cotangent of the state
-// of side `side` (0: uL, 1: uR) from the flux cotangent Fb, in one reverse sweep.
-// S_L and S_R take the left state on ties, as hll_n's min and max do.
+// Vector-Jacobian product of hll_n: uLb and uRb are the cotangents of the two
+// states from the flux cotangent Fb, in one reverse sweep.  S_L and S_R take the
+// left state on ties, as hll_n's min and max do.
 template <typename T>
 __device__ __forceinline__ void hll_n_vjp(const T* uL, const T* uR, T nx, T ny, T gamma,
-                                          const T* Fb, int side, T* ub) {
+                                          const T* Fb, T* uLb, T* uRb) {
   const T gm1 = gamma - T(1);
   T ir[2], vx[2], vy[2], p[2], c[2], vn[2];
 #pragma unroll
@@ -838,24 +844,27 @@ __device__ __forceinline__ void hll_n_vjp(const T* uL, const T* uR, T nx, T ny, 
   const T Q = (SR * dot[0] - SL * dot[1] + SL * SR * D) * inv;
   const T SLb = fan ? (Q - dot[1] + SR * D) * inv : T(0);
   const T SRb = fan ? (dot[0] - Q + SL * D) * inv : T(0);
-  // this side's weight of its own flux, of u_R - u_L, and its wave speeds
-  const T a = fan ? (side ? -SL : SR) * inv : ((side ? right : left) ? T(1) : T(0));
-  const T cu = fan ? (side ? SL : -SL) * SR * inv : T(0);
-  const T lb = (loR == (side == 1)) ? SLb : T(0), rb = (hiR == (side == 1)) ? SRb : T(0);
-  const T u0 = side ? uR[0] : uL[0], u1 = side ? uR[1] : uL[1], u2 = side ? uR[2] : uL[2];
-  const T u3 = side ? uR[3] : uL[3];
-  const T sir = side ? ir[1] : ir[0], svx = side ? vx[1] : vx[0], svy = side ? vy[1] : vy[0];
-  const T sp = side ? p[1] : p[0], svn = side ? vn[1] : vn[0], ics = rcp(side ? c[1] : c[0]);
-  const T G0 = a * Fb[0], G1 = a * Fb[1], G2 = a * Fb[2], G3 = a * Fb[3];
-  const T vnb = G0 * u0 + G1 * u1 + G2 * u2 + G3 * (u3 + sp) + lb + rb;
-  const T cb = T(0.5) * gamma * (rb - lb) * ics;  // c = sqrt(gamma p / rho)
-  const T pb = gm1 * (a * g0 + G3 * svn + cb * sir);
-  const T irb = cb * sp;
-  const T vxb = vnb * nx - T(0.5) * pb * u1, vyb = vnb * ny - T(0.5) * pb * u2;
-  ub[0] = G0 * svn - sir * (vxb * svx + vyb * svy + sir * irb) + cu * Fb[0];
-  ub[1] = G1 * svn + vxb * sir - T(0.5) * pb * svx + cu * Fb[1];
-  ub[2] = G2 * svn + vyb * sir - T(0.5) * pb * svy + cu * Fb[2];
-  ub[3] = G3 * svn + pb + cu * Fb[3];
+  const T cu = fan ? SL * SR * inv : T(0);
+#pragma unroll
+  for (int s = 0; s < 2; ++s) {
+    // this side's weight of its own flux, of u_R - u_L, and its wave speeds
+    const T a = fan ? (s ? -SL : SR) * inv : ((s ? right : left) ? T(1) : T(0));
+    const T cs = s ? cu : -cu;
+    const T lb = (loR == (s == 1)) ? SLb : T(0), rb = (hiR == (s == 1)) ? SRb : T(0);
+    const T* u = s == 0 ? uL : uR;
+    T* ub = s == 0 ? uLb : uRb;
+    const T ics = rcp(c[s]);
+    const T G0 = a * Fb[0], G1 = a * Fb[1], G2 = a * Fb[2], G3 = a * Fb[3];
+    const T vnb = G0 * u[0] + G1 * u[1] + G2 * u[2] + G3 * (u[3] + p[s]) + lb + rb;
+    const T cb = T(0.5) * gamma * (rb - lb) * ics;  // c = sqrt(gamma p / rho)
+    const T pb = gm1 * (a * g0 + G3 * vn[s] + cb * ir[s]);
+    const T irb = cb * p[s];
+    const T vxb = vnb * nx - T(0.5) * pb * u[1], vyb = vnb * ny - T(0.5) * pb * u[2];
+    ub[0] = G0 * vn[s] - ir[s] * (vxb * vx[s] + vyb * vy[s] + ir[s] * irb) + cs * Fb[0];
+    ub[1] = G1 * vn[s] + vxb * ir[s] - T(0.5) * pb * vx[s] + cs * Fb[1];
+    ub[2] = G2 * vn[s] + vyb * ir[s] - T(0.5) * pb * vy[s] + cs * Fb[2];
+    ub[3] = G3 * vn[s] + pb + cs * Fb[3];
+  }
 }
 
 // Volume term at one point: cotangent of the state u from those of its fluxes
@@ -876,87 +885,198 @@ __device__ __forceinline__ void euler_xy_vjp(const T* u, T gamma, const T* Fxb, 
   ub[3] = Fxb[3] * vx + Fyb[3] * vy + pb;
 }
 
+// lamW of a block of cells (the blocks of k_fl_step).  The face sweep of a block's
+// faces runs once for both sides and leaves per face and side the sum and the
+// difference of the two Gauss points; each cell then gathers its incidences.  The
+// LDS decides how many workgroups overlap their loads with another's sweep: two per
+// CU in FP64 (80 KB each), because the residual cotangents of the cells and Pi(P)
+// take turns in one table (each thread folds the cotangents of its up to four faces
+// into eight values a face first) and a pass sweeps kBlock faces.
 template <typename T>
-__global__ __launch_bounds__(256) void k_adjfl_L(PFA<T> p) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  if (e >= p.nc) return;
+__global__ __launch_bounds__(kBlock, 2) void k_adjfl_L(PFA<T> p) {
+  __shared__ T cT[12][kLocal];   // rm, rx, ry of each variable, then Pi(P)
+  __shared__ T sB[22][kBlock];   // per slot: each side's ub0 + ub1 and ub1 - ub0, the
+                                 // points' offset, the face centroid from L and from R
+  constexpr int kPasses = kMaxSlots / kBlock;
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int tid = threadIdx.x;
+  const int c0 = p.blk_cell0[b], nown = p.blk_cell0[b + 1] - c0;
+  const int h0 = p.blk_halo0[b], nhalo = p.blk_halo0[b + 1] - h0;
+  const int s0 = p.blk_slot0[b], nslot = p.blk_slot0[b + 1] - s0;
+  const int nc = p.nc;
   const T is3 = T(0.57735026918962576451);  // 1/sqrt(3)
-  T we[12], le[12], g[12];
-  load12(p.W, p.nc, e, we);
-  load12(p.lam, p.nc, e, le);
-  const T* cge = p.cell_geo + 8 * (size_t)e;
-  Cot<T> ce;
-  cotangents(le, cge, ce);
+  const int e = c0 + tid;
+  const bool own = tid < nown;
+  // the last two waves take a halo cell each beside their own
+  const int hi = tid - (kBlock - kMaxHalo);
+  const bool halo = hi >= 0 && hi < nhalo;
+  int ii = 0, i1 = 0;
+  T g[12], we[12], wh[12];
 #pragma unroll
   for (int k = 0; k < 12; ++k) g[k] = T(0);
-  for (int i = p.inc0[e]; i < p.inc0[e + 1]; ++i) {
-    const int fs = p.inc_face[i], f = fs >> 1, side = fs & 1;
-    const int nb = side ? p.face_lr[2 * f] : p.face_lr[2 * f + 1];
-    const T* fg = p.face_geo + 8 * (size_t)f;
-    const T nx = fg[0], ny = fg[1], A = fg[2], fx = fg[3], fy = fg[4], dx = fg[5], dy = fg[6];
-    T wn[12], ln[12];
-    load12(p.W, p.nc, nb, wn);
-    load12(p.lam, p.nc, nb, ln);
-    Cot<T> cn;
-    cotangents(ln, p.cell_geo + 8 * (size_t)nb, cn);
-    // Gauss points x_f -+ A/(2 sqrt 3) t, t = (-n_y, n_x); weights A/2; the L
-    // cell takes -w F, the R cell +w F (mean and the moments about its
-    // centroid).  Values of e and nb are selected element by element (an
-    // array picked through a pointer would leave the registers).
-    const T w = T(0.5) * A, o = T(0.5) * A * is3;
-    const T tx = -ny * o, ty = nx * o;
-    const T se = side ? T(1) : T(-1);
-#pragma unroll 1
-    for (int gp = 0; gp < 2; ++gp) {
-      const T sg = gp ? T(1) : T(-1);
-      const T rLx = fma(sg, tx, fx), rLy = fma(sg, ty, fy);
-      const T rRx = rLx - dx, rRy = rLy - dy;
-      const T rex = side ? rRx : rLx, rey = side ? rRy : rLy;
-      const T rnx = side ? rLx : rRx, rny = side ? rLy : rRy;
-      T uL[4], uR[4], Fb[4];
+  auto put_cot = [&](const Cot<T>& c, int i) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const T ue = we[3 * v] + we[3 * v + 1] * rex + we[3 * v + 2] * rey;
-        const T un = wn[3 * v] + wn[3 * v + 1] * rnx + wn[3 * v + 2] * rny;
-        uL[v] = side ? un : ue;
-        uR[v] = side ? ue : un;
-        Fb[v] = w * se * ((ce.rm[v] + ce.rx[v] * rex + ce.ry[v] * rey) -
-                          (cn.rm[v] + cn.rx[v] * rnx + cn.ry[v] * rny));
-      }
-      T ub[4];
-      hll_n_vjp(uL, uR, nx, ny, p.gamma, Fb, side, ub);
+    for (int v = 0; v < 4; ++v) {
+      cT[3 * v][i] = c.rm[v];
+      cT[3 * v + 1][i] = c.rx[v];
+      cT[3 * v + 2][i] = c.ry[v];
+    }
+  };
+  if (halo) {
+    const int ge = p.halo_cell[h0 + hi];
+    T le[12];
+    load12(p.W, nc, ge, wh);
+    load12(p.lam, nc, ge, le);
+    Cot<T> c;
+    cotangents(le, p.cell_geo + 8 * (size_t)ge, c);
+    put_cot(c, nown + hi);
+  }
+  if (own) {
+    ii = p.cell_inc0[e];
+    i1 = p.cell_inc0[e + 1];
+    T le[12], cg[8];
+    load12(p.W, nc, e, we);
+    load12(p.lam, nc, e, le);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) cg[k] = p.cell_geo[8 * (size_t)e + k];
+    Cot<T> c;
+    cotangents(le, cg, c);
+    put_cot(c, tid);
+    // volume term: the 4 principal-axis points c -+ a_k
+#pragma unroll 1
+    for (int q = 0; q < 4; ++q) {
+      const T sgn = (q & 1) ? T(1) : T(-1);
+      const T ox = sgn * ((q & 2) ? cg[6] : cg[4]);
+      const T oy = sgn * ((q & 2) ? cg[7] : cg[5]);
+      T u[4], ub[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) u[v] = fma(we[3 * v + 1], ox, fma(we[3 * v + 2], oy, we[3 * v]));
+      euler_xy_vjp(u, p.gamma, c.vx, c.vy, ub);
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         g[3 * v] += ub[v];
-        g[3 * v + 1] = fma(rex, ub[v], g[3 * v + 1]);
-        g[3 * v + 2] = fma(rey, ub[v], g[3 * v + 2]);
+        g[3 * v + 1] = fma(ox, ub[v], g[3 * v + 1]);
+        g[3 * v + 2] = fma(oy, ub[v], g[3 * v + 2]);
       }
     }
   }
-  // volume term: the 4 principal-axis points c -+ a_k
-#pragma unroll 1
-  for (int q = 0; q < 4; ++q) {
-    const T sgn = (q & 1) ? T(1) : T(-1);
-    const T ox = sgn * ((q & 2) ? cge[6] : cge[4]);
-    const T oy = sgn * ((q & 2) ? cge[7] : cge[5]);
-    T u[4], ub[4];
+  __syncthreads();
+  // Gauss points x_f -+ A/(2 sqrt 3) t, t = (-n_y, n_x); weights A/2; the L cell
+  // takes -w F, the R cell +w F (mean and the moments about its centroid): the flux
+  // cotangent at the face centroid and its change to a point
+  T aF[kPasses][4], bF[kPasses][4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) u[v] = fma(we[3 * v + 1], ox, fma(we[3 * v + 2], oy, we[3 * v]));
-    euler_xy_vjp(u, p.gamma, ce.vx, ce.vy, ub);
+  for (int j = 0; j < kPasses; ++j) {
+    const int sl = j * kBlock + tid;
+    if (sl < nslot) {
+      const int lr = p.slot_lr[s0 + sl], L = lr & 0xffff, R = lr >> 16;
+      const T* sg = p.slot_geo + 8 * (size_t)(s0 + sl);
+      const T w = T(0.5) * sg[2], o = w * is3;
+      const T tx = -sg[1] * o, ty = sg[0] * o, fx = sg[3], fy = sg[4];
+      const T gx = fx - sg[5], gy = fy - sg[6];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      g[3 * v] += ub[v];
-      g[3 * v + 1] = fma(ox, ub[v], g[3 * v + 1]);
-      g[3 * v + 2] = fma(oy, ub[v], g[3 * v + 2]);
+      for (int v = 0; v < 4; ++v) {
+        T qx = cT[3 * v + 1][R], qy = cT[3 * v + 2][R];
+        const T a = cT[3 * v][R] + qx * gx + qy * gy, d = qx * tx + qy * ty;
+        qx = cT[3 * v + 1][L], qy = cT[3 * v + 2][L];
+        aF[j][v] = w * (a - (cT[3 * v][L] + qx * fx + qy * fy));
+        bF[j][v] = w * (d - (qx * tx + qy * ty));
+      }
     }
   }
+  __syncthreads();
+  if (halo) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) cT[k][nown + hi] = wh[k];
+  }
+  if (own) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) cT[k][tid] = we[k];
+  }
+  // the cell's incidences (sorted by slot), loaded ahead
+  int inc = ii < i1 ? p.cell_inc[ii] : 0, inc1 = ii + 1 < i1 ? p.cell_inc[ii + 1] : 0;
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPasses; ++j) {
+    const int sa = j * kBlock;
+    if (sa >= nslot) break;
+    if (sa + tid < nslot) {
+      const int lr = p.slot_lr[s0 + sa + tid], L = lr & 0xffff, R = lr >> 16;
+      const T* sg = p.slot_geo + 8 * (size_t)(s0 + sa + tid);
+      const T nx = sg[0], ny = sg[1], o = T(0.5) * sg[2] * is3;
+      const T tx = -ny * o, ty = nx * o, fx = sg[3], fy = sg[4];
+      const T gx = fx - sg[5], gy = fy - sg[6];
+      T aL[4], bL[4], aR[4], bR[4];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        T qx = cT[3 * v + 1][L], qy = cT[3 * v + 2][L];
+        aL[v] = cT[3 * v][L] + qx * fx + qy * fy;
+        bL[v] = qx * tx + qy * ty;
+        qx = cT[3 * v + 1][R], qy = cT[3 * v + 2][R];
+        aR[v] = cT[3 * v][R] + qx * gx + qy * gy;
+        bR[v] = qx * tx + qy * ty;
+      }
+      T S[8], D[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) S[k] = D[k] = T(0);
+#pragma unroll
+      for (int gp = 0; gp < 2; ++gp) {
+        const T sgn = gp ? T(1) : T(-1);
+        T uL[4], uR[4], Fb[4], ub[8];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          uL[v] = fma(sgn, bL[v], aL[v]);
+          uR[v] = fma(sgn, bR[v], aR[v]);
+          Fb[v] = fma(sgn, bF[j][v], aF[j][v]);
+        }
+        hll_n_vjp(uL, uR, nx, ny, p.gamma, Fb, ub, ub + 4);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          S[k] += ub[k];
+          D[k] = fma(sgn, ub[k], D[k]);
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          sB[8 * s + v][tid] = S[4 * s + v];
+          sB[8 * s + 4 + v][tid] = D[4 * s + v];
+        }
+      sB[16][tid] = tx;
+      sB[17][tid] = ty;
+      sB[18][tid] = fx;
+      sB[19][tid] = fy;
+      sB[20][tid] = gx;
+      sB[21][tid] = gy;
+    }
+    __syncthreads();
+    // this pass's incidences
+    while (ii < i1 && ((inc & 0xffff) >> 1) < sa + kBlock) {
+      const int ls = ((inc & 0xffff) >> 1) - sa, side = inc & 1;
+      inc = inc1;
+      inc1 = ii + 2 < i1 ? p.cell_inc[ii + 2] : 0;
+      ++ii;
+      const T tx = sB[16][ls], ty = sB[17][ls];
+      const T fx = sB[18 + 2 * side][ls], fy = sB[19 + 2 * side][ls];
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const T S = sB[8 * side + v][ls], D = sB[8 * side + 4 + v][ls];
+        g[3 * v] += S;
+        g[3 * v + 1] += fma(S, fx, D * tx);
+        g[3 * v + 2] += fma(S, fy, D * ty);
+      }
+    }
+    if (sa + kBlock < nslot) __syncthreads();  // the next pass overwrites the table
+  }
+  if (!own) return;
   const double dt = p.dt_dev ? *p.dt_dev : p.dt_host;
   const T cid = (T)p.c_id, cL = (T)(p.c_L_over_dt * dt), cx = (T)p.c_extra;
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
-    T o = fma(cL, g[k], cid * le[k]);
-    if (p.extra) o = fma(cx, p.extra[(size_t)k * p.nc + e], o);
-    p.out[(size_t)k * p.nc + e] = o;
+    T o = fma(cL, g[k], cid * p.lam[(size_t)k * nc + e]);
+    if (p.extra) o = fma(cx, p.extra[(size_t)k * nc + e], o);
+    p.out[(size_t)k * nc + e] = o;
   }
 }
 
@@ -1095,8 +1215,14 @@ hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const doub
   p.inc0 = f.lim_inc0;
   p.nbr = f.lim_nbr;
   p.inc_face = f.inc_face;
-  p.face_lr = f.face_lr;
-  p.face_geo = static_cast<const T*>(f.face_geo);
+  p.blk_cell0 = f.blk_cell0;
+  p.blk_slot0 = f.blk_slot0;
+  p.blk_halo0 = f.blk_halo0;
+  p.halo_cell = f.halo_cell;
+  p.slot_lr = f.slot_lr;
+  p.slot_geo = static_cast<const T*>(f.slot_geo);
+  p.cell_inc0 = f.cell_inc0;
+  p.cell_inc = f.cell_inc;
   p.lim_geo = static_cast<const T*>(f.lim_geo);
   p.cell_geo = static_cast<const T*>(f.cell_geo);
   auto adj_stage = [&](const void* P, const void* lam, const void* extra, double c_id,
@@ -1117,7 +1243,7 @@ hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const doub
     a.c_L_over_dt = c_L_over_dt;
     a.c_extra = c_extra;
     a.out = static_cast<T*>(lim ? ws2 : out);
-    hipLaunchKernelGGL((k_adjfl_L<T>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((k_adjfl_L<T>), dim3(f.nblocks), dim3(kBlock), 0, s, a);
     if (!lim) return hipGetLastError();
     PFA<T> b = p;
     b.P = static_cast<const T*>(P);
@@ -1306,23 +1432,9 @@ dg_status facelist_create(dg_mesh* m, const dg_mesh_desc* d) {
       cside[i] = 1;
     }
   }
-  // the adjoint's incidence codes and global face records
-  std::vector<int> inc_face(inc0[nc]), face_lr(2 * nf);
-  std::vector<double> fgeo(8 * nf, 0.0);
+  // the adjoint's incidence codes
+  std::vector<int> inc_face(inc0[nc]);
   for (int64_t i = 0; i < (int64_t)inc0[nc]; ++i) inc_face[i] = (cface[i] << 1) | cside[i];
-  for (int64_t f = 0; f < nf; ++f) {
-    double rc[2], dLR[2];
-    offsets(f, rc, dLR);
-    face_lr[2 * f] = d->face_cells[2 * f];
-    face_lr[2 * f + 1] = d->face_cells[2 * f + 1];
-    fgeo[8 * f] = d->face_normal[2 * f];
-    fgeo[8 * f + 1] = d->face_normal[2 * f + 1];
-    fgeo[8 * f + 2] = d->face_area[f];
-    fgeo[8 * f + 3] = rc[0];
-    fgeo[8 * f + 4] = rc[1];
-    fgeo[8 * f + 5] = dLR[0];
-    fgeo[8 * f + 6] = dLR[1];
-  }
   // blocks of up to kBlock consecutive cells; a block is halved until its
   // distinct incident faces fit the slot table and its outside neighbours the
   // halo table
@@ -1451,8 +1563,6 @@ dg_status facelist_create(dg_mesh* m, const dg_mesh_desc* d) {
   if (err == hipSuccess) err = up(lgeo, &fd->lim_geo);
   if (err == hipSuccess) err = up(perim, &fd->cell_perim);
   if (err == hipSuccess) err = upload_i(inc_face, &fd->inc_face);
-  if (err == hipSuccess) err = upload_i(face_lr, &fd->face_lr);
-  if (err == hipSuccess) err = up(fgeo, &fd->face_geo);
   if (err != hipSuccess) {
     facelist_destroy(m);
     return hip_fail(err, "dg_mesh_create: face-list upload");
@@ -1478,8 +1588,6 @@ void facelist_destroy(dg_mesh* m) {
   (void)hipFree(f->lim_geo);
   (void)hipFree(f->cell_perim);
   (void)hipFree(f->inc_face);
-  (void)hipFree(f->face_lr);
-  (void)hipFree(f->face_geo);
   delete f;
   m->fld = nullptr;
 }

@@ -116,3 +116,29 @@ def test_mhd_adjoint_in_chunks(oracle, torch_cuda, n):
     s = Solver(cartesian(n, lo, hi), physics="mhd", gamma=G53)
     lam = s.adjoint_step(s.to_device(U), dt, s.to_device(w)).cpu().numpy()
     assert abs(Jv @ w - v @ lam) <= 1e-12 * np.abs(Jv * w).sum()
+
+
+@pytest.mark.parametrize("limiter", [False, True])
+@pytest.mark.parametrize("n,shuffled", [(3, False), (255, False), (256, False), (257, False),
+                                        (700, False), (700, True)])
+def test_voronoi_adjoint_at_block_edges(oracle, torch_cuda, n, shuffled, limiter):
+    """Meshes around the 256 cells of a block, and cells in random order, whose blocks are cut
+    down to few cells by their neighbours outside: <J v, w> = <v, J^T w>."""
+    from paper_1305_5536_amd.solver import Solver
+    mesh = periodic_voronoi(n, seed=8)
+    if shuffled:
+        to = np.random.default_rng(2).permutation(n).astype(np.int32)
+        mesh = dict(mesh, face_cells=to[mesh["face_cells"]])
+        for k in ("generators", "cell_volume", "cell_centroid", "cell_moments"):
+            a = np.empty_like(mesh[k])
+            a[to] = mesh[k]
+            mesh[k] = a
+    om = oracle.Mesh.facelist(mesh)
+    U = _rough(n, 2, False, 23, 0.5)
+    dt = oracle.cfl_dt(om, U, G53, 0.02)
+    rng = np.random.default_rng(12)
+    v, w = rng.standard_normal(U.size), rng.standard_normal(U.size)
+    _, Jv = oracle.step_jvp(om, U, v, dt, G53, limiter)
+    s = Solver(mesh, limiter=limiter, gamma=G53)
+    lam = s.adjoint_step(s.to_device(U), dt, s.to_device(w)).cpu().numpy()
+    assert abs(Jv @ w - v @ lam) <= 1e-12 * np.abs(Jv * w).sum()

@@ -89,3 +89,23 @@ def test_rest_and_motion(mv, torch_cuda, dt_factor):
         changed += int((got["ring"] != first["ring"]).any(axis=1).sum())
     s.check()
     assert (changed > 0) == (dt_factor > 0)
+
+
+@pytest.mark.parametrize("flux", ["exact", "hll"])
+@pytest.mark.parametrize("n,shuffled", [(65, False), (255, False), (256, False), (257, False),
+                                        (900, False), (900, True)])
+def test_update_at_workgroup_edges(mv, torch_cuda, n, shuffled, flux):
+    """Meshes around the 256 cells of a workgroup of the update, and generators in random order,
+    whose faces nearly all lead out of their workgroup."""
+    P = periodic_voronoi(n, seed=14)["generators"]
+    if shuffled:
+        P = P[np.random.default_rng(4).permutation(n)]
+    d = mv.voronoi(P, (1.0, 1.0))
+    U0 = random_voronoi_state(d, G53, seed=6, amp=0.3)
+    s = _solver(d, flux=flux)
+    U, dt = s.to_device(U0), mv.cfl_dt(d, U0, G53, 0.3)
+    for _ in range(2):
+        ref, d = mv.step(d, U.cpu().numpy(), dt, G53, "weno", flux)
+        U = s.step_mh(U, dt)
+        s.check()
+        assert np.abs(U.cpu().numpy() - ref).max() < 1e-11 * np.abs(ref).max()

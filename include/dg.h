@@ -279,7 +279,8 @@ dg_status dg_step_mh(dg_mesh_t mesh, const void* U, void* U_next, double dt, con
  * order, then -z, +z); DG_EUNSUPPORTED otherwise (the exact Riemann solver,
  * the WENO-type limiter, moving meshes).  lam_n must
  * not alias U, V1 or lam_np1.  Allocates two state-sized workspaces on the
- * first call (kept by the handle), on MHD meshes also 7 values per cell and a
+ * first call (kept by the handle), on face lists also four values and four
+ * integers per cell, on MHD meshes 7 values per cell and a
  * face table of 256 MiB at most, or of two rows (planes) of cells where those
  * need more. */
 dg_status dg_adjoint_step(dg_mesh_t mesh, const void* U, const void* V1, double dt,

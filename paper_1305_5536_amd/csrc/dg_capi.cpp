@@ -57,7 +57,8 @@ hipError_t launch_adjoint_mhd3d(const dg_mesh* m, const void* U, const void* V1,
 size_t adjoint_mhd3d_scratch(const dg_mesh* m);
 hipError_t launch_adjoint_facelist(const dg_mesh* m, const void* U, const void* V1,
                                    const double* dt_dev, double dt, const void* lam_np1,
-                                   void* lam_n, void* ws1, void* ws2, hipStream_t s);
+                                   void* lam_n, void* ws1, void* ws2, void* scratch, hipStream_t s);
+size_t adjoint_facelist_scratch(const dg_mesh* m);
 hipError_t launch_cart3d(const dg_mesh* m, int mode, const void* in, const void* u0, void* out,
                          const double* dt_dev, double dt_host, double cfl, double* dt_next,
                          hipStream_t s);
@@ -806,8 +807,10 @@ dg_status dg_adjoint_step(dg_mesh_t m, const void* U, const void* V1, double dt,
   hipError_t e = hipSuccess;
   if (!m->adj_ws1) e = hipMalloc(&m->adj_ws1, bytes);
   if (e == hipSuccess && !m->adj_ws2) e = hipMalloc(&m->adj_ws2, bytes);
-  if (e == hipSuccess && (mhd2 || mhd3) && !m->adj_scratch)
-    e = hipMalloc(&m->adj_scratch, mhd2 ? adjoint_mhd2d_scratch(m) : adjoint_mhd3d_scratch(m));
+  if (e == hipSuccess && (mhd2 || mhd3 || flist) && !m->adj_scratch)
+    e = hipMalloc(&m->adj_scratch, mhd2   ? adjoint_mhd2d_scratch(m)
+                                   : mhd3 ? adjoint_mhd3d_scratch(m)
+                                          : adjoint_facelist_scratch(m));
   if (e != hipSuccess) return hip_fail(e, "dg_adjoint_step: workspace allocation");
   if (!V1) {
     dg_status st = dispatch(m, kStage1, U, nullptr, m->v1, dt_dev, dt, s);
@@ -820,7 +823,7 @@ dg_status dg_adjoint_step(dg_mesh_t m, const void* U, const void* V1, double dt,
         : mhd3 ? launch_adjoint_mhd3d(m, U, V1, dt_dev, dt, lam_np1, lam_n, m->adj_ws1,
                                       m->adj_ws2, m->adj_scratch, s)
                : launch_adjoint_facelist(m, U, V1, dt_dev, dt, lam_np1, lam_n, m->adj_ws1,
-                                         m->adj_ws2, s);
+                                         m->adj_ws2, m->adj_scratch, s);
     if (e != hipSuccess) return hip_fail(e, "dg_adjoint_step launch");
     return DG_OK;
   }

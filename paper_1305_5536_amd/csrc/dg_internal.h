@@ -130,7 +130,7 @@ struct dg_mesh {
   int adj_tiles = 0;
   void* adj_ws1 = nullptr;          // adjoint workspaces (lazy)
   void* adj_ws2 = nullptr;
-  void* adj_scratch = nullptr;      // MHD: face table of a chunk and limiter messages
+  void* adj_scratch = nullptr;      // MHD: face table of a chunk; face lists and MHD: limiter messages
   dg::Batch bt;                     // kind 2
   void* run_ws = nullptr;           // dg_run: second ping-pong buffer (lazy)
   hipStream_t cap_stream = nullptr; // dg_run: capture stream (lazy)

@@ -32,8 +32,8 @@
 // ranges and entries, geometry, Pi(U^n), the first pass's slots) are issued
 // before the first barrier, so that their latency overlaps phase 0.
 // A stand-alone limiter kernel (k_fl_lim) serves dg_limit.  The discrete
-// adjoint of a step sweeps the same blocks (k_adjfl_L) and transposes the limiter
-// over the global incidence lists, one thread per cell (k_adjfl_lim, k_adjfl_msg).
+// adjoint of a step sweeps the same blocks (k_adjfl_L, k_adjfl_msg) and transposes the
+// limiter over the global incidence lists.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -742,24 +742,24 @@ hipError_t cfl_t(const dg_mesh* m, const void* U, hipStream_t s) {
 // Adjoint of a stage (as for the Cartesian meshes):
 //   out = Pi_P^T lamW,   lamW = c_id lam + c_L (dL/dW)^T lam + c_extra extra,
 // W = Pi(P), the branch the forward step takes (dt frozen).  k_adjfl_L computes
-// lamW block by block from the faces and the cells' volume points, k_adjfl_lim
-// applies the transpose of each cell's own limiter and leaves a message for the one
-// neighbour whose mean set a bound, k_adjfl_msg adds each cell's messages.  No
-// atomics; the flux Jacobians come from one reverse sweep per Gauss point
-// (hll_n_vjp), the linear parts (Gauss-point extrapolation, residual weights, M^-1)
-// are transposed by hand.  Measured (262144 cells, FP64, one adjoint stage):
-// k_adjfl_L 0.078 ms, bound by the latency of its loads beside 43 us of traffic
-// (0.134 ms with a thread per cell that sweeps its faces from gathered neighbours,
-// 0.107 with those gathers in XCD order and two waves per SIMD, 0.093 as one
-// workgroup per CU with separate tables), k_adjfl_lim 0.044 and k_adjfl_msg 0.017 ms
-// (gathers).  The adjoint step 0.42 -> 0.33 ms.
+// lamW block by block from the faces and the cells' volume points, applies the
+// transpose of each cell's own limiter and leaves a message for the one neighbour
+// whose mean set a bound; k_adjfl_msg adds each cell's messages.  No atomics; the
+// flux Jacobians come from one reverse sweep per Gauss point (hll_n_vjp), the linear
+// parts (Gauss-point extrapolation, residual weights, M^-1) are transposed by hand.
+// Measured (262144 cells, FP64, one adjoint stage): k_adjfl_L 0.100 ms, bound by the
+// latency of its loads, and k_adjfl_msg 0.017 ms (gathers).  With the limiter's part
+// as a kernel of its own 0.076 + 0.046 ms (0.034 with four incidences in flight,
+// which fit two waves per SIMD, instead of eight); the sweep as one workgroup per CU
+// with separate tables 0.093 in place of 0.076, as a thread per cell that sweeps its
+// faces from gathered neighbours 0.134 (0.107 in XCD order with two waves per SIMD).
+// The adjoint step 0.42 -> 0.28 ms.
 template <typename T>
 struct PFA {
   const T* W;      // Pi(P)
-  const T* P;      // the stage input (k_adjfl_lim)
-  const T* lam;    // adjoint of the stage output (k_adjfl_L)
+  const T* P;      // the stage input (limit_transpose)
+  const T* lam;    // adjoint of the stage output
   const T* extra;  // added to lamW with weight c_extra (may be NULL)
-  const T* lamW;   // k_adjfl_lim input
   T* out;
   T* msg;          // limiter messages: 4 values a cell
   int* to;         // and the incidences they go through
@@ -885,6 +885,92 @@ __device__ __forceinline__ void euler_xy_vjp(const T* u, T gamma, const T* Fxb, 
   ub[3] = Fxb[3] * vx + Fyb[3] * vy + pb;
 }
 
+// The limiter transpose Pi_P^T lamW of one cell's own limiter (that of k_fl_lim:
+// bounds over the cell and its neighbours in the incidence order, alpha = min
+// over the incidences of psi at the face centroid, the first on ties): writes
+// the adjoint of its gradients and the part its own mean takes, and per variable
+// a message for the neighbour whose mean set the bound.  msg[v * nc + e] holds
+// the value, to[v * nc + e] the incidence code (face << 1 | side) through which
+// the cell sees that neighbour, -1 for no message.
+template <typename T>
+__device__ __forceinline__ void limit_transpose(const PFA<T>& p, int e, const T* lw) {
+  T q[12];
+  load12(p.P, p.nc, e, q);
+  T hi[4], lo[4];
+  int ihi[4], ilo[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    hi[v] = lo[v] = q[3 * v];
+    ihi[v] = ilo[v] = -1;
+  }
+  // incidences kBatch at a time with their loads in flight (eight spill 100 B a lane:
+  // 0.112 against 0.100 ms)
+  constexpr int kBatch = 4;
+  const int i0 = p.inc0[e], i1 = p.inc0[e + 1];
+  for (int b0 = i0; b0 < i1; b0 += kBatch) {
+    int nb[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) nb[u] = b0 + u < i1 ? p.nbr[b0 + u] : e;
+    T m[kBatch][4];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) m[u][v] = p.P[(3 * v) * p.nc + nb[u]];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        ihi[v] = m[u][v] > hi[v] ? b0 + u : ihi[v];
+        ilo[v] = m[u][v] < lo[v] ? b0 + u : ilo[v];
+        hi[v] = fmax(hi[v], m[u][v]);
+        lo[v] = fmin(lo[v], m[u][v]);
+      }
+  }
+  // alpha and the increment d = g . r of the face that sets it (d = 0: none)
+  T al[4], da[4], rx[4], ry[4];
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    al[v] = T(1);
+    da[v] = rx[v] = ry[v] = T(0);
+  }
+  for (int b0 = i0; b0 < i1; b0 += kBatch) {
+    T ox[kBatch], oy[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = b0 + u < i1 ? b0 + u : b0;
+      ox[u] = p.lim_geo[2 * (size_t)i];
+      oy[u] = p.lim_geo[2 * (size_t)i + 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const T d = q[3 * v + 1] * ox[u] + q[3 * v + 2] * oy[u];
+        const T psi = psi_of(d, q[3 * v], hi[v], lo[v]);
+        const bool set = psi < al[v];
+        al[v] = set ? psi : al[v];
+        da[v] = set ? d : da[v];
+        rx[v] = set ? ox[u] : rx[v];
+        ry[v] = set ? oy[u] : ry[v];
+      }
+  }
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    // psi = (bound - phi) / d: bound with cotangent ab / d, d with -psi ab / d
+    const bool act = da[v] != T(0), up = da[v] > T(0);
+    const T ab = lw[3 * v + 1] * q[3 * v + 1] + lw[3 * v + 2] * q[3 * v + 2];
+    const T ad = fabs(da[v]);
+    const T w = act ? div_small(up ? ab : -ab, ad) : T(0);
+    const int to = up ? ihi[v] : ilo[v];
+    const bool send = act && to >= 0;
+    p.out[(size_t)(3 * v) * p.nc + e] = lw[3 * v] - (send ? w : T(0));
+    p.out[(size_t)(3 * v + 1) * p.nc + e] = al[v] * (lw[3 * v + 1] - w * rx[v]);
+    p.out[(size_t)(3 * v + 2) * p.nc + e] = al[v] * (lw[3 * v + 2] - w * ry[v]);
+    p.msg[(size_t)v * p.nc + e] = w;
+    p.to[(size_t)v * p.nc + e] = send ? p.inc_face[to] : -1;
+  }
+}
+
 // lamW of a block of cells (the blocks of k_fl_step).  The face sweep of a block's
 // faces runs once for both sides and leaves per face and side the sum and the
 // difference of the two Gauss points; each cell then gathers its incidences.  The
@@ -892,7 +978,7 @@ __device__ __forceinline__ void euler_xy_vjp(const T* u, T gamma, const T* Fxb, 
 // CU in FP64 (80 KB each), because the residual cotangents of the cells and Pi(P)
 // take turns in one table (each thread folds the cotangents of its up to four faces
 // into eight values a face first) and a pass sweeps kBlock faces.
-template <typename T>
+template <typename T, bool LIM>
 __global__ __launch_bounds__(kBlock, 2) void k_adjfl_L(PFA<T> p) {
   __shared__ T cT[12][kLocal];   // rm, rx, ry of each variable, then Pi(P)
   __shared__ T sB[22][kBlock];   // per slot: each side's ub0 + ub1 and ub1 - ub0, the
@@ -1074,97 +1160,14 @@ __global__ __launch_bounds__(kBlock, 2) void k_adjfl_L(PFA<T> p) {
   const T cid = (T)p.c_id, cL = (T)(p.c_L_over_dt * dt), cx = (T)p.c_extra;
 #pragma unroll
   for (int k = 0; k < 12; ++k) {
-    T o = fma(cL, g[k], cid * p.lam[(size_t)k * nc + e]);
-    if (p.extra) o = fma(cx, p.extra[(size_t)k * nc + e], o);
-    p.out[(size_t)k * nc + e] = o;
+    g[k] = fma(cL, g[k], cid * p.lam[(size_t)k * nc + e]);
+    if (p.extra) g[k] = fma(cx, p.extra[(size_t)k * nc + e], g[k]);
   }
-}
-
-// The limiter transpose Pi_P^T lamW of one cell's own limiter (that of k_fl_lim:
-// bounds over the cell and its neighbours in the incidence order, alpha = min
-// over the incidences of psi at the face centroid, the first on ties): writes
-// the adjoint of its gradients and the part its own mean takes, and per variable
-// a message for the neighbour whose mean set the bound.  msg[v * nc + e] holds
-// the value, to[v * nc + e] the incidence code (face << 1 | side) through which
-// the cell sees that neighbour, -1 for no message.
-template <typename T>
-__global__ __launch_bounds__(256) void k_adjfl_lim(PFA<T> p) {
-  const int e = xcd_remap(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
-  if (e >= p.nc) return;
-  T q[12], lw[12];
-  load12(p.P, p.nc, e, q);
-  load12(p.lamW, p.nc, e, lw);
-  T hi[4], lo[4];
-  int ihi[4], ilo[4];
+  if (LIM) {
+    limit_transpose(p, e, g);
+  } else {
 #pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    hi[v] = lo[v] = q[3 * v];
-    ihi[v] = ilo[v] = -1;
-  }
-  // incidences kBatch at a time with their loads in flight, as k_fl_lim does
-  constexpr int kBatch = 8;
-  const int i0 = p.inc0[e], i1 = p.inc0[e + 1];
-  for (int b0 = i0; b0 < i1; b0 += kBatch) {
-    int nb[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) nb[u] = b0 + u < i1 ? p.nbr[b0 + u] : e;
-    T m[kBatch][4];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) m[u][v] = p.P[(3 * v) * p.nc + nb[u]];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        ihi[v] = m[u][v] > hi[v] ? b0 + u : ihi[v];
-        ilo[v] = m[u][v] < lo[v] ? b0 + u : ilo[v];
-        hi[v] = fmax(hi[v], m[u][v]);
-        lo[v] = fmin(lo[v], m[u][v]);
-      }
-  }
-  // alpha and the increment d = g . r of the face that sets it (d = 0: none)
-  T al[4], da[4], rx[4], ry[4];
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    al[v] = T(1);
-    da[v] = rx[v] = ry[v] = T(0);
-  }
-  for (int b0 = i0; b0 < i1; b0 += kBatch) {
-    T ox[kBatch], oy[kBatch];
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int i = b0 + u < i1 ? b0 + u : b0;
-      ox[u] = p.lim_geo[2 * (size_t)i];
-      oy[u] = p.lim_geo[2 * (size_t)i + 1];
-    }
-#pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const T d = q[3 * v + 1] * ox[u] + q[3 * v + 2] * oy[u];
-        const T psi = psi_of(d, q[3 * v], hi[v], lo[v]);
-        const bool set = psi < al[v];
-        al[v] = set ? psi : al[v];
-        da[v] = set ? d : da[v];
-        rx[v] = set ? ox[u] : rx[v];
-        ry[v] = set ? oy[u] : ry[v];
-      }
-  }
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    // psi = (bound - phi) / d: bound with cotangent ab / d, d with -psi ab / d
-    const bool act = da[v] != T(0), up = da[v] > T(0);
-    const T ab = lw[3 * v + 1] * q[3 * v + 1] + lw[3 * v + 2] * q[3 * v + 2];
-    const T ad = fabs(da[v]);
-    const T w = act ? div_small(up ? ab : -ab, ad) : T(0);
-    const int to = up ? ihi[v] : ilo[v];
-    const bool send = act && to >= 0;
-    p.out[(size_t)(3 * v) * p.nc + e] = lw[3 * v] - (send ? w : T(0));
-    p.out[(size_t)(3 * v + 1) * p.nc + e] = al[v] * (lw[3 * v + 1] - w * rx[v]);
-    p.out[(size_t)(3 * v + 2) * p.nc + e] = al[v] * (lw[3 * v + 2] - w * ry[v]);
-    p.msg[(size_t)v * p.nc + e] = w;
-    p.to[(size_t)v * p.nc + e] = send ? p.inc_face[to] : -1;
+    for (int k = 0; k < 12; ++k) p.out[(size_t)k * nc + e] = g[k];
   }
 }
 
@@ -1203,7 +1206,7 @@ __global__ __launch_bounds__(256) void k_adjfl_msg(PFA<T> p) {
 template <typename T>
 hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const double* dt_dev,
                      double dt, const void* lam_np1, void* lam_n, void* ws1, void* ws2,
-                     hipStream_t s) {
+                     void* scratch, hipStream_t s) {
   const FLDev& f = *m->fld;
   const bool lim = m->cfg.limiter == DG_LIMITER_MINMOD;
   const dim3 grid((unsigned)((f.ncells + 255) / 256)), block(256);
@@ -1227,8 +1230,7 @@ hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const doub
   p.cell_geo = static_cast<const T*>(f.cell_geo);
   auto adj_stage = [&](const void* P, const void* lam, const void* extra, double c_id,
                        double c_L_over_dt, double c_extra, void* out) -> hipError_t {
-    // W = Pi(P) into ws1; lamW into ws2 (or straight into out without a
-    // limiter); out = Pi_P^T lamW
+    // W = Pi(P) into ws1; out = Pi_P^T lamW (lamW itself without a limiter)
     const void* W = P;
     if (lim) {
       hipError_t r = lim_t<T>(m, P, ws1, s);
@@ -1237,31 +1239,30 @@ hipError_t adjoint_t(const dg_mesh* m, const void* U, const void* V1, const doub
     }
     PFA<T> a = p;
     a.W = static_cast<const T*>(W);
+    a.P = static_cast<const T*>(P);
     a.lam = static_cast<const T*>(lam);
     a.extra = static_cast<const T*>(extra);
     a.c_id = c_id;
     a.c_L_over_dt = c_L_over_dt;
     a.c_extra = c_extra;
-    a.out = static_cast<T*>(lim ? ws2 : out);
-    hipLaunchKernelGGL((k_adjfl_L<T>), dim3(f.nblocks), dim3(kBlock), 0, s, a);
-    if (!lim) return hipGetLastError();
-    PFA<T> b = p;
-    b.P = static_cast<const T*>(P);
-    b.lamW = static_cast<const T*>(ws2);
-    b.out = static_cast<T*>(out);
-    // W is no longer needed: its workspace takes the messages
-    b.msg = static_cast<T*>(ws1);
-    b.to = reinterpret_cast<int*>(b.msg + (size_t)4 * f.ncells);
-    hipLaunchKernelGGL((k_adjfl_lim<T>), grid, block, 0, s, b);
-    hipLaunchKernelGGL((k_adjfl_msg<T>), grid, block, 0, s, b);
+    a.out = static_cast<T*>(out);
+    a.msg = static_cast<T*>(scratch);
+    a.to = reinterpret_cast<int*>(a.msg + (size_t)4 * f.ncells);
+    const dim3 blocks((unsigned)f.nblocks);
+    if (!lim) {
+      hipLaunchKernelGGL((k_adjfl_L<T, false>), blocks, dim3(kBlock), 0, s, a);
+    } else {
+      hipLaunchKernelGGL((k_adjfl_L<T, true>), blocks, dim3(kBlock), 0, s, a);
+      hipLaunchKernelGGL((k_adjfl_msg<T>), grid, block, 0, s, a);
+    }
     return hipGetLastError();
   };
-  // stage 2: lam_V1 = Pi_V1^T [lam'/2 + (dt/2) L^T lam'] (in lam_n with the
-  // limiter, else in ws2); stage 1: lam_n = Pi_U^T [lam_V1 + dt L^T lam_V1 + lam'/2]
-  void* lam_v1 = lim ? lam_n : ws2;
-  hipError_t e = adj_stage(V1, lam_np1, nullptr, 0.5, 0.5, 0.0, lam_v1);
+  // stage 2: lam_V1 = Pi_V1^T [lam'/2 + (dt/2) L^T lam'] (in ws2: blocks write their
+  // cells of lam_n while others still read their halo of lam_V1); stage 1:
+  // lam_n = Pi_U^T [lam_V1 + dt L^T lam_V1 + lam'/2]
+  hipError_t e = adj_stage(V1, lam_np1, nullptr, 0.5, 0.5, 0.0, ws2);
   if (e != hipSuccess) return e;
-  return adj_stage(U, lam_v1, lam_np1, 1.0, 1.0, 0.5, lam_n);
+  return adj_stage(U, ws2, lam_np1, 1.0, 1.0, 0.5, lam_n);
 }
 
 // ------------------------------------------------------------ host setup --
@@ -1633,10 +1634,16 @@ hipError_t launch_facelist(const dg_mesh* m, int mode, const void* in, const voi
 
 hipError_t launch_adjoint_facelist(const dg_mesh* m, const void* U, const void* V1,
                                    const double* dt_dev, double dt, const void* lam_np1,
-                                   void* lam_n, void* ws1, void* ws2, hipStream_t s) {
+                                   void* lam_n, void* ws1, void* ws2, void* scratch,
+                                   hipStream_t s) {
   if (m->cfg.precision == DG_FP64)
-    return adjoint_t<double>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, s);
-  return adjoint_t<float>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, s);
+    return adjoint_t<double>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, scratch, s);
+  return adjoint_t<float>(m, U, V1, dt_dev, dt, lam_np1, lam_n, ws1, ws2, scratch, s);
+}
+
+// Bytes of the limiter messages: four values and four incidence codes a cell.
+size_t adjoint_facelist_scratch(const dg_mesh* m) {
+  return (size_t)m->ncells * 4 * ((size_t)m->elem + sizeof(int));
 }
 
 hipError_t launch_facelist_cfl(const dg_mesh* m, const void* U, double cfl, double* dt_dev,

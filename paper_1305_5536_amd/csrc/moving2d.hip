@@ -64,7 +64,6 @@
 namespace dg {
 
 constexpr int kRing = 16;  // neighbours a cell may have
-constexpr int kTwice = 64;  // k_mv_walk to k_mv_geom: a neighbour appears twice in the ring
 constexpr int kFast = 8;   // neighbours of a cell whose ring k_mv_check can keep
 constexpr int kGeo = 6;    // V, centroid - generator (2), Mxx, Mxy, Myy
 constexpr int kWalkBlocks = 2048;  // most workgroups of the walk (four cells at a time each)
@@ -695,7 +694,11 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
 // t_k = (|d_k|^2 - d_j . d_k) / (2 perp(d_j) . d_k) when perp(d_j) . d_k > 0, and
 // the next neighbour is the candidate with the smallest t_k (compared by
 // cross-multiplication; ties to the smaller index).  The walk ends back at the
-// first neighbour; nothing but the ring is stored.
+// first neighbour; nothing but the ring is stored.  The next face depends on the
+// current one alone, so a walk that meets a neighbour again before the first one has
+// run into a circle and the cell is not bounded: no ring holds a neighbour twice (the
+// rings given at creation, those k_mv_check keeps and those that lose short faces
+// are distinct too).
 template <typename T>
 __global__ __launch_bounds__(256) void k_mv_walk(PM<T> p, MSet src, MOut dst) {
   const int lane = threadIdx.x & 63;
@@ -757,7 +760,7 @@ __global__ __launch_bounds__(256) void k_mv_walk(PM<T> p, MSet src, MOut dst) {
     int d = 0, cur = j0;
     double cx = __shfl(bx, 0), cy = __shfl(by, 0);
     while (!bad) {
-      if (d > kRing) {
+      if (d > kRing || __any(mine == cur)) {
         bad = true;
         break;
       }
@@ -798,12 +801,9 @@ __global__ __launch_bounds__(256) void k_mv_walk(PM<T> p, MSet src, MOut dst) {
       cy = __shfl(ny, 0);
     }
     bad |= d > kRing;
-    bool twice = false;
-    for (int t = 1; t < kRing; ++t) twice |= lane + t < d && __shfl_down(mine, t) == mine;
-    const bool flag = __any(twice);
     if (lane < kRing) dst.ring[(size_t)e * kRing + lane] = !bad && lane < d ? mine : -1;
     if (lane == 0) {
-      dst.deg[e] = bad ? 0 : d + (flag ? kTwice : 0);
+      dst.deg[e] = bad ? 0 : d;
       if (bad) atomicOr(p.status, 2);
     }
   }
@@ -820,10 +820,8 @@ __global__ __launch_bounds__(256) void k_mv_geom(PM<T> p, MOut dst) {
     const double2 pe = P[e];
     const double xe = pe.x, ye = pe.y;
     int* ring = dst.ring + (size_t)e * kRing;
-    // (k_mv_walk adds kTwice to the degree where a neighbour appears twice)
     int d = dst.deg[e];
-    bool look = d >= kTwice;
-    d &= kTwice - 1;
+    bool look = false;
     bool bad = d < 3 || d > kRing;
     Moments mom;
     // f(k, a, b) for every edge of the polygon: face k runs from vertex k, the one
@@ -878,8 +876,6 @@ __global__ __launch_bounds__(256) void k_mv_geom(PM<T> p, MOut dst) {
         if (g.A >= 1e-10 * sqrt(g.dx * g.dx + g.dy * g.dy)) ring[dk++] = j;
         prev = j;
       }
-      for (int k = 0; k < dk; ++k)
-        for (int k2 = k + 1; k2 < dk; ++k2) bad |= ring[k] == ring[k2];
       bad |= dk < 3;
       for (int k = dk; k < kRing; ++k) ring[k] = -1;
       dst.deg[e] = bad ? 0 : dk;

@@ -109,3 +109,21 @@ def test_update_at_workgroup_edges(mv, torch_cuda, n, shuffled, flux):
         U = s.step_mh(U, dt)
         s.check()
         assert np.abs(U.cpu().numpy() - ref).max() < 1e-11 * np.abs(ref).max()
+
+
+def test_generators_that_jump_are_reported(mv, torch_cuda):
+    """Generators that jump across the box leave cells whose previous neighbours do not bound
+    them: the walk ends (it may circle without meeting its first face) and dg_check says so."""
+    from paper_1305_5536_amd.capi import DGError
+    d = mv.voronoi(periodic_voronoi(900, seed=8)["generators"], (1.0, 1.0))
+    s = _solver(d)
+    U = random_voronoi_state(d, G53, seed=5, amp=0.1).reshape(12, -1)
+    v = np.random.default_rng(3).uniform(-1.0, 1.0, (2, U.shape[1]))
+    U[9] += 0.5 * U[0] * (v ** 2).sum(0)
+    U[3], U[6], U[[4, 5, 7, 8]] = U[0] * v[0], U[0] * v[1], 0.0
+    s.step_mh(s.to_device(U.reshape(-1)), 0.6)
+    with pytest.raises(DGError, match="DG_EMESH"):
+        s.check()
+    deg, ring = (s.geometry()[k] for k in ("degree", "ring"))
+    for k, r in zip(deg, ring):
+        assert len(set(r[:k].tolist())) == k <= 16 and (r[k:] == -1).all()

@@ -564,10 +564,14 @@ __device__ __forceinline__ void nearest_image(const PM_box& b, double& dx, doubl
 // then each is a vertex of the cell, and the walk from the nearest neighbour
 // would visit the same faces in the same order.  The test keeps a distance from
 // rounding (sine of the angle between neighbours above 1e-2, vertices inside by
-// 1e-9 of the candidate's distance); cells that miss it, that have more than
-// kFast neighbours, or whose ring changed, go to the list.  The vertices and
-// neighbours stay in registers; a candidate costs kFast comparisons of its index
-// and kFast half-plane tests, no list and no dependent scan.  The latency of its
+// 1e-9 of the candidate's distance).  A candidate within that distance of one
+// vertex (four cells that meet in a point, as on a lattice) leaves the ring as it is
+// where its face, if it has one, is one that k_mv_geom drops (the walk of such a cell
+// gives the same ring once that face is dropped; a step on a square lattice of 512^2
+// cells takes 0.29 ms, 2.76 ms with every such cell on the list).  Cells that miss the
+// test, that have more than kFast neighbours, or whose ring changed, go to the list.
+// The vertices and neighbours stay in registers; a candidate costs kFast comparisons
+// of its index and kFast products, no list and no dependent scan.  The latency of its
 // three gathers (ring, neighbours' rings, positions) bounds it.  Measured (262144
 // cells, FP64): 0.066 ms, and 0.015 ms for the walk of the listed cells; walking
 // every cell, one thread each over a list of its candidates in LDS, took 0.177
@@ -611,8 +615,8 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
       if (k < d) ok &= den > 0.0 && den * den > 1e-4 * n2[k] * m1;
       // 2 x the vertex: d_k + t perp(d_k), t = (|d_k1|^2 - d_k . d_k1) / den
       const double t = (m1 - (dx[k] * x1 + dy[k] * y1)) * rcp(den);
-      vx[k] = dx[k] - t * dy[k];
-      vy[k] = dy[k] + t * dx[k];
+      vx[k] = k < d ? dx[k] - t * dy[k] : 0.0;
+      vy[k] = k < d ? dy[k] + t * dx[k] : 0.0;
     }
     // the cell's other neighbours, then every candidate further out
 #pragma unroll
@@ -622,8 +626,44 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
         const bool own = c == k || c == (k + 1 < d ? k + 1 : 0);
         if (c < d && k < d && !own) ok &= vx[k] * dx[c] + vy[k] * dy[c] < kIn * n2[c];
       }
+    // Whether candidate c, which the test above leaves open, has at most a face that
+    // k_mv_geom drops: it touches one vertex only, between its two neighbours, and the
+    // cut it makes there, its depth times (cot + cot) of its angles to them, is shorter
+    // than half of 1e-10 of its distance.  (Positions are read again: this is rare, and
+    // the offsets would cost registers in the loop below.)
+    auto grazes = [&](int c) {
+      auto offset = [&](int i, double& x, double& y) {
+        const double2 q = XY[i];
+        x = q.x - pe.x;
+        y = q.y - pe.y;
+        nearest_image(box, x, y);
+      };
+      double cx, cy;
+      offset(c, cx, cy);
+      const double m = cx * cx + cy * cy;
+      int touched = 0;
+      bool drop = true;
+#pragma unroll
+      for (int k = 0; k < kFast; ++k) {
+        const double cut = vx[k] * cx + vy[k] * cy - m;
+        if (k < d && !(cut < (kIn - 1.0) * m)) {
+          double ax, ay, bx, by;
+          offset(r[k], ax, ay);
+          offset(k + 1 == kFast || k + 1 >= d ? r[0] : r[(k + 1) % kFast], bx, by);
+          const double sa = ax * cy - ay * cx, sb = cx * by - cy * bx, ma = ax * ax + ay * ay,
+                       mb = bx * bx + by * by, sab = ax * by - ay * bx;
+          // (well conditioned: sines above 0.1, distances within a factor of 4)
+          drop &= sa > 0.0 && sb > 0.0 && sa * sa > 0.01 * ma * m && sb * sb > 0.01 * mb * m &&
+                  sab * sab > 0.01 * ma * mb && fmax(ma, mb) < 16.0 * m;
+          drop &= (fmax(cut, 0.0) + 1e-12 * m) * ((ax * cx + ay * cy) * sb + (bx * cx + by * cy) * sa) <
+                  1e-10 * m * (sa * sb);
+          ++touched;
+        }
+      }
+      return drop && touched == 1;
+    };
     if (ok) {
-      for (int a = 0; a < d; ++a) {
+      for (int a = 0; a < d && ok; ++a) {
         const int j = src.ring[(size_t)e * kRing + a];
         const int dj = min(src.deg[j], kRing);
         for (int b = 0; b < dj; b += 8) {
@@ -638,17 +678,20 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
             for (int k = 0; k < kFast; ++k) out[u] &= c[u] != r[k];
             q[u] = XY[out[u] ? c[u] : e];
           }
+          unsigned open = 0;
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
             double cx = q[u].x - pe.x, cy = q[u].y - pe.y;
             nearest_image(box, cx, cy);
-            const double m = kIn * (cx * cx + cy * cy);
-            bool in = true;
+            const double m = cx * cx + cy * cy;
+            double most = vx[0] * cx + vy[0] * cy;
 #pragma unroll
-            for (int k = 0; k < kFast; ++k)
-              in &= k >= d || vx[k] * cx + vy[k] * cy < m;
-            ok &= in || !out[u];
+            for (int k = 1; k < kFast; ++k) most = fmax(most, vx[k] * cx + vy[k] * cy);
+            ok &= !out[u] || most < (2.0 - kIn) * m;
+            open |= out[u] && !(most < kIn * m) ? 1u << u : 0u;
           }
+          for (; open && ok; open &= open - 1)
+            ok = grazes(src.ring[(size_t)j * kRing + b + __ffs(open) - 1]);
         }
       }
     }

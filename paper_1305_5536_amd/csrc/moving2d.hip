@@ -66,7 +66,8 @@ namespace dg {
 constexpr int kRing = 16;  // neighbours a cell may have
 constexpr int kFast = 8;   // neighbours of a cell whose ring k_mv_check can keep
 constexpr int kGeo = 6;    // V, centroid - generator (2), Mxx, Mxy, Myy
-constexpr int kWalkBlocks = 2048;  // most workgroups of the walk (four cells at a time each)
+constexpr int kWalkBlocks = 2048;  // most workgroups of the walk
+constexpr int kCand = 40;  // distinct candidates of a cell that a thread can walk
 
 struct MVDev {
   int n = 0;
@@ -564,12 +565,13 @@ __device__ __forceinline__ void nearest_image(const PM_box& b, double& dx, doubl
 // then each is a vertex of the cell, and the walk from the nearest neighbour
 // would visit the same faces in the same order.  The test keeps a distance from
 // rounding (sine of the angle between neighbours above 1e-2, vertices inside by
-// 1e-9 of the candidate's distance).  A candidate within that distance of one
-// vertex (four cells that meet in a point, as on a lattice) leaves the ring as it is
-// where its face, if it has one, is one that k_mv_geom drops (the walk of such a cell
-// gives the same ring once that face is dropped; a step on a square lattice of 512^2
-// cells takes 0.29 ms, 2.76 ms with every such cell on the list).  Cells that miss the
-// test, that have more than kFast neighbours, or whose ring changed, go to the list.
+// 1e-9 of the candidate's distance).  Nearer candidates (four cells that meet in a
+// point, as on a lattice) are looked at one by one (`settled`): one that is inside
+// beyond rounding, or whose face k_mv_geom would drop, leaves the ring as it is (the
+// walk of such a cell gives the same ring once that face is dropped; a step on a
+// square lattice of 512^2 cells takes 0.29 ms, 2.76 ms with every such cell on the
+// list).  Cells that miss the test, that have more than kFast neighbours, or whose ring
+// changed, go to the list.
 // The vertices and neighbours stay in registers; a candidate costs kFast comparisons
 // of its index and kFast products, no list and no dependent scan.  The latency of its
 // three gathers (ring, neighbours' rings, positions) bounds it.  Measured (262144
@@ -618,20 +620,15 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
       vx[k] = k < d ? dx[k] - t * dy[k] : 0.0;
       vy[k] = k < d ? dy[k] + t * dx[k] : 0.0;
     }
-    // the cell's other neighbours, then every candidate further out
-#pragma unroll
-    for (int c = 0; c < kFast; ++c)
-#pragma unroll
-      for (int k = 0; k < kFast; ++k) {
-        const bool own = c == k || c == (k + 1 < d ? k + 1 : 0);
-        if (c < d && k < d && !own) ok &= vx[k] * dx[c] + vy[k] * dy[c] < kIn * n2[c];
-      }
-    // Whether candidate c, which the test above leaves open, has at most a face that
-    // k_mv_geom drops: it touches one vertex only, between its two neighbours, and the
-    // cut it makes there, its depth times (cot + cot) of its angles to them, is shorter
-    // than half of 1e-10 of its distance.  (Positions are read again: this is rare, and
-    // the offsets would cost registers in the loop below.)
-    auto grazes = [&](int c) {
+    // Candidates that come within 1e-9 of a vertex: c, the neighbour `own` of the cell
+    // or (own < 0) one further out.  Where the vertex is well conditioned (sines above
+    // 0.1, distances within a factor of 4) 1e-12 of the distance is far from rounding.
+    // A candidate further out may also touch or cut one vertex, between its two
+    // neighbours, if the cut, its depth times (cot + cot) of its angles to them, is
+    // shorter than half of the length (1e-10 of its distance) below which k_mv_geom
+    // drops a face.  (Rare; the positions are read again, since the offsets would cost
+    // registers in the loop over the candidates.)
+    auto settled = [&](int c, int own) {
       auto offset = [&](int i, double& x, double& y) {
         const double2 q = XY[i];
         x = q.x - pe.x;
@@ -641,27 +638,44 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
       double cx, cy;
       offset(c, cx, cy);
       const double m = cx * cx + cy * cy;
-      int touched = 0;
-      bool drop = true;
+      int cuts = 0;
+      bool good = true;
 #pragma unroll
       for (int k = 0; k < kFast; ++k) {
+        const int next = k + 1 < d ? k + 1 : 0;
         const double cut = vx[k] * cx + vy[k] * cy - m;
-        if (k < d && !(cut < (kIn - 1.0) * m)) {
+        if (k < d && own != k && own != next && !(cut < (kIn - 1.0) * m)) {
           double ax, ay, bx, by;
           offset(r[k], ax, ay);
-          offset(k + 1 == kFast || k + 1 >= d ? r[0] : r[(k + 1) % kFast], bx, by);
-          const double sa = ax * cy - ay * cx, sb = cx * by - cy * bx, ma = ax * ax + ay * ay,
-                       mb = bx * bx + by * by, sab = ax * by - ay * bx;
-          // (well conditioned: sines above 0.1, distances within a factor of 4)
-          drop &= sa > 0.0 && sb > 0.0 && sa * sa > 0.01 * ma * m && sb * sb > 0.01 * mb * m &&
-                  sab * sab > 0.01 * ma * mb && fmax(ma, mb) < 16.0 * m;
-          drop &= (fmax(cut, 0.0) + 1e-12 * m) * ((ax * cx + ay * cy) * sb + (bx * cx + by * cy) * sa) <
-                  1e-10 * m * (sa * sb);
-          ++touched;
+          offset(k + 1 < kFast && k + 1 < d ? r[(k + 1) % kFast] : r[0], bx, by);
+          const double sa = ax * cy - ay * cx, sb = cx * by - cy * bx, sab = ax * by - ay * bx;
+          const double ma = ax * ax + ay * ay, mb = bx * bx + by * by;
+          good &= sa * sa > 0.01 * ma * m && sb * sb > 0.01 * mb * m && sab * sab > 0.01 * ma * mb &&
+                  fmax(ma, mb) < 16.0 * m;
+          if (!(cut < -1e-12 * m)) {
+            good &= sa > 0.0 && sb > 0.0 &&
+                    (fmax(cut, 0.0) + 1e-12 * m) *
+                            ((ax * cx + ay * cy) * sb + (bx * cx + by * cy) * sa) <
+                        1e-10 * m * (sa * sb);
+            ++cuts;
+          }
         }
       }
-      return drop && touched == 1;
+      return good && cuts <= (own < 0 ? 1 : 0);
     };
+    // the cell's other neighbours, then every candidate further out
+    unsigned open = 0;
+#pragma unroll
+    for (int c = 0; c < kFast; ++c)
+#pragma unroll
+      for (int k = 0; k < kFast; ++k) {
+        const bool own = c == k || c == (k + 1 < d ? k + 1 : 0);
+        if (c < d && k < d && !own && !(vx[k] * dx[c] + vy[k] * dy[c] < kIn * n2[c])) open |= 1u << c;
+      }
+    for (; open && ok; open &= open - 1) {
+      const int c = __ffs(open) - 1;
+      ok = settled(src.ring[(size_t)e * kRing + c], c);
+    }
     if (ok) {
       for (int a = 0; a < d && ok; ++a) {
         const int j = src.ring[(size_t)e * kRing + a];
@@ -678,7 +692,7 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
             for (int k = 0; k < kFast; ++k) out[u] &= c[u] != r[k];
             q[u] = XY[out[u] ? c[u] : e];
           }
-          unsigned open = 0;
+          open = 0;
 #pragma unroll
           for (int u = 0; u < 8; ++u) {
             double cx = q[u].x - pe.x, cy = q[u].y - pe.y;
@@ -691,7 +705,7 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
             open |= out[u] && !(most < kIn * m) ? 1u << u : 0u;
           }
           for (; open && ok; open &= open - 1)
-            ok = grazes(src.ring[(size_t)j * kRing + b + __ffs(open) - 1]);
+            ok = settled(src.ring[(size_t)j * kRing + b + __ffs(open) - 1], -1);
         }
       }
     }
@@ -728,127 +742,226 @@ __global__ __launch_bounds__(256) void k_mv_check(PM<T> p, MSet src, MOut dst) {
   }
 }
 
-// One wave per listed cell, the candidates spread over its lanes (an entry that
-// several neighbours list appears several times: equal values, harmless).  The
-// cell is walked counter-clockwise, one face at a time.  The nearest candidate is
-// a neighbour (the midpoint of the two generators lies on their common face).
-// The face of neighbour j lies on the bisector x(t) = d_j/2 + t perp(d_j),
-// perp(d) = (-d_y, d_x); candidate k bounds it from the counter-clockwise side at
-// t_k = (|d_k|^2 - d_j . d_k) / (2 perp(d_j) . d_k) when perp(d_j) . d_k > 0, and
-// the next neighbour is the candidate with the smallest t_k (compared by
-// cross-multiplication; ties to the smaller index).  The walk ends back at the
-// first neighbour; nothing but the ring is stored.  The next face depends on the
+// The walk of a listed cell.  The cell is walked counter-clockwise, one face at a
+// time.  The nearest candidate is a neighbour (the midpoint of the two generators lies
+// on their common face).  The face of neighbour j lies on the bisector
+// x(t) = d_j/2 + t perp(d_j), perp(d) = (-d_y, d_x); candidate k bounds it from the
+// counter-clockwise side at t_k = (|d_k|^2 - d_j . d_k) / (2 perp(d_j) . d_k) when
+// perp(d_j) . d_k > 0, and the next neighbour is the candidate with the smallest t_k
+// (compared by cross-multiplication; ties to the smaller index).  The walk ends back at
+// the first neighbour; nothing but the ring is stored.  The next face depends on the
 // current one alone, so a walk that meets a neighbour again before the first one has
 // run into a circle and the cell is not bounded: no ring holds a neighbour twice (the
 // rings given at creation, those k_mv_check keeps and those that lose short faces
 // are distinct too).
+struct WalkMin {  // the smallest t_k so far, as num / den
+  double num = 1.0, den = 0.0, x = 0.0, y = 0.0;
+  int k = -1;
+  __device__ __forceinline__ void take(int id, double nu, double de, double dx, double dy) {
+    const double l = nu * den, r = num * de;
+    if (k < 0 || l < r || (l == r && id < k)) {
+      num = nu;
+      den = de;
+      k = id;
+      x = dx;
+      y = dy;
+    }
+  }
+};
+
+// By a wave, the candidates spread over its lanes (an entry that several neighbours
+// list appears several times: equal values, harmless).
 template <typename T>
-__global__ __launch_bounds__(256) void k_mv_walk(PM<T> p, MSet src, MOut dst) {
+__device__ __forceinline__ void walk_by_wave(const PM<T>& p, const MSet& src, const MOut& dst,
+                                             const PM_box& box, int e) {
   const int lane = threadIdx.x & 63;
-  const int count = *p.count, nw = gridDim.x * 4;
-  const int n = p.n;
-  const double2* XY = reinterpret_cast<const double2*>(dst.x + 2 * (size_t)n);
-  const PM_box box{p.Lx, p.Ly, 1.0 / p.Lx, 1.0 / p.Ly};
+  const double2* XY = reinterpret_cast<const double2*>(dst.x + 2 * (size_t)p.n);
   constexpr int kSlots = (kRing * (kRing + 1) + 63) / 64;
-  for (int i = blockIdx.x * 4 + (threadIdx.x >> 6); i < count; i += nw) {
-    const int e = __builtin_amdgcn_readfirstlane(p.list[i]);
-    const double2 pe = XY[e];
-    const int d0 = min(src.deg[e], kRing);
-    int id[kSlots];
-    double kx[kSlots], ky[kSlots];
+  const double2 pe = XY[e];
+  const int d0 = min(src.deg[e], kRing);
+  int id[kSlots];
+  double kx[kSlots], ky[kSlots];
 #pragma unroll
-    for (int q = 0; q < kSlots; ++q) {
-      const int t = lane + 64 * q, a = t / (kRing + 1), b = t - a * (kRing + 1) - 1;
-      id[q] = -1;
-      kx[q] = ky[q] = 0.0;
-      if (a < d0) {
-        const int j = src.ring[(size_t)e * kRing + a];
-        const int k = b < 0 ? j : (b < min(src.deg[j], kRing) ? src.ring[(size_t)j * kRing + b] : e);
-        if (k != e) {
-          const double2 pk = XY[k];
-          id[q] = k;
-          kx[q] = pk.x - pe.x;
-          ky[q] = pk.y - pe.y;
-          nearest_image(box, kx[q], ky[q]);
-        }
+  for (int q = 0; q < kSlots; ++q) {
+    const int t = lane + 64 * q, a = t / (kRing + 1), b = t - a * (kRing + 1) - 1;
+    id[q] = -1;
+    kx[q] = ky[q] = 0.0;
+    if (a < d0) {
+      const int j = src.ring[(size_t)e * kRing + a];
+      const int k = b < 0 ? j : (b < min(src.deg[j], kRing) ? src.ring[(size_t)j * kRing + b] : e);
+      if (k != e) {
+        const double2 pk = XY[k];
+        id[q] = k;
+        kx[q] = pk.x - pe.x;
+        ky[q] = pk.y - pe.y;
+        nearest_image(box, kx[q], ky[q]);
       }
     }
-    // the nearest candidate
-    double best = 1e300, bx = 0.0, by = 0.0;
-    int j0 = -1;
+  }
+  // the nearest candidate
+  double best = 1e300, bx = 0.0, by = 0.0;
+  int j0 = -1;
+#pragma unroll
+  for (int q = 0; q < kSlots; ++q) {
+    const double dd = kx[q] * kx[q] + ky[q] * ky[q];
+    if (id[q] >= 0 && (j0 < 0 || dd < best || (dd == best && id[q] < j0))) {
+      best = dd;
+      j0 = id[q];
+      bx = kx[q];
+      by = ky[q];
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double ob = __shfl_xor(best, o), ox = __shfl_xor(bx, o), oy = __shfl_xor(by, o);
+    const int oj = __shfl_xor(j0, o);
+    if (oj >= 0 && (j0 < 0 || ob < best || (ob == best && oj < j0))) {
+      best = ob;
+      j0 = oj;
+      bx = ox;
+      by = oy;
+    }
+  }
+  // (one lane's winner for all: near ties may round differently across lanes)
+  j0 = __builtin_amdgcn_readfirstlane(j0);
+  bool bad = j0 < 0;
+  int mine = -1;  // ring entry `lane`
+  int d = 0, cur = j0;
+  double cx = __shfl(bx, 0), cy = __shfl(by, 0);
+  while (!bad) {
+    if (d > kRing || __any(mine == cur)) {
+      bad = true;
+      break;
+    }
+    mine = lane == d ? cur : mine;
+    ++d;
+    WalkMin w;
 #pragma unroll
     for (int q = 0; q < kSlots; ++q) {
-      const double dd = kx[q] * kx[q] + ky[q] * ky[q];
-      if (id[q] >= 0 && (j0 < 0 || dd < best || (dd == best && id[q] < j0))) {
-        best = dd;
-        j0 = id[q];
-        bx = kx[q];
-        by = ky[q];
-      }
+      const double den = cx * ky[q] - cy * kx[q];  // perp(d_cur) . d_k
+      if (id[q] >= 0 && id[q] != cur && den > 0.0)
+        w.take(id[q], kx[q] * kx[q] + ky[q] * ky[q] - (cx * kx[q] + cy * ky[q]), den, kx[q], ky[q]);
     }
     for (int o = 32; o > 0; o >>= 1) {
-      const double ob = __shfl_xor(best, o), ox = __shfl_xor(bx, o), oy = __shfl_xor(by, o);
-      const int oj = __shfl_xor(j0, o);
-      if (oj >= 0 && (j0 < 0 || ob < best || (ob == best && oj < j0))) {
-        best = ob;
-        j0 = oj;
-        bx = ox;
-        by = oy;
-      }
+      const int ok = __shfl_xor(w.k, o);
+      const double on = __shfl_xor(w.num, o), od = __shfl_xor(w.den, o);
+      const double ox = __shfl_xor(w.x, o), oy = __shfl_xor(w.y, o);
+      if (ok >= 0) w.take(ok, on, od, ox, oy);
     }
-    // (one lane's winner for all: near ties may round differently across lanes)
-    j0 = __builtin_amdgcn_readfirstlane(j0);
-    bool bad = j0 < 0;
-    int mine = -1;  // ring entry `lane`
-    int d = 0, cur = j0;
-    double cx = __shfl(bx, 0), cy = __shfl(by, 0);
-    while (!bad) {
-      if (d > kRing || __any(mine == cur)) {
-        bad = true;
-        break;
-      }
-      mine = lane == d ? cur : mine;
-      ++d;
-      int nxt = -1;
-      double nb_ = 1.0, db_ = 0.0, nx = 0.0, ny = 0.0;
-      auto take = [&](int k, double num, double den, double x, double y) {
-        const double l = num * db_, r = nb_ * den;
-        if (nxt < 0 || l < r || (l == r && k < nxt)) {
-          nb_ = num;
-          db_ = den;
-          nxt = k;
-          nx = x;
-          ny = y;
-        }
-      };
+    const int nxt = __builtin_amdgcn_readfirstlane(w.k);
+    if (nxt < 0) {
+      bad = true;
+      break;
+    }
+    if (nxt == j0) break;
+    cur = nxt;
+    cx = __shfl(w.x, 0);
+    cy = __shfl(w.y, 0);
+  }
+  bad |= d > kRing;
+  if (lane < kRing) dst.ring[(size_t)e * kRing + lane] = !bad && lane < d ? mine : -1;
+  if (lane == 0) {
+    dst.deg[e] = bad ? 0 : d;
+    if (bad) atomicOr(p.status, 2);
+  }
+}
+
+// By a thread, over the list of its distinct candidates in a column of LDS (no
+// barrier), kChunk of their positions loaded together.  False, and nothing written,
+// where they are more than kCand.
+template <typename T>
+__device__ __forceinline__ bool walk_by_thread(const PM<T>& p, const MSet& src, const MOut& dst,
+                                               const PM_box& box, int e, int* cl) {
+  constexpr int kChunk = 4;
+  const double2* XY = reinterpret_cast<const double2*>(dst.x + 2 * (size_t)p.n);
+  const double2 pe = XY[e];
+  const int d0 = min(src.deg[e], kRing);
+  int nc = 0;
+  for (int a = 0; a < d0; ++a) {
+    const int j = src.ring[(size_t)e * kRing + a];
+    const int dj = min(src.deg[j], kRing);
+    for (int b = -1; b < dj; ++b) {
+      const int k = b < 0 ? j : src.ring[(size_t)j * kRing + b];
+      bool seen = k == e;
+      for (int c = 0; c < nc && !seen; ++c) seen = cl[c * 256] == k;
+      if (seen) continue;
+      if (nc == kCand) return false;
+      cl[nc++ * 256] = k;
+    }
+  }
+  auto visit = [&](auto&& f) {
+    for (int c0 = 0; c0 < nc; c0 += kChunk) {
+      int k[kChunk];
+      double2 q[kChunk];
 #pragma unroll
-      for (int q = 0; q < kSlots; ++q) {
-        const double den = cx * ky[q] - cy * kx[q];  // perp(d_cur) . d_k
-        if (id[q] >= 0 && id[q] != cur && den > 0.0)
-          take(id[q], kx[q] * kx[q] + ky[q] * ky[q] - (cx * kx[q] + cy * ky[q]), den, kx[q], ky[q]);
+      for (int u = 0; u < kChunk; ++u) k[u] = c0 + u < nc ? cl[(c0 + u) * 256] : e;
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u) q[u] = XY[k[u]];
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u) {
+        if (k[u] == e) continue;
+        double dx = q[u].x - pe.x, dy = q[u].y - pe.y;
+        nearest_image(box, dx, dy);
+        f(k[u], dx, dy);
       }
-      for (int o = 32; o > 0; o >>= 1) {
-        const int ok = __shfl_xor(nxt, o);
-        const double on = __shfl_xor(nb_, o), od = __shfl_xor(db_, o);
-        const double ox = __shfl_xor(nx, o), oy = __shfl_xor(ny, o);
-        if (ok >= 0) take(ok, on, od, ox, oy);
-      }
-      nxt = __builtin_amdgcn_readfirstlane(nxt);
-      if (nxt < 0) {
-        bad = true;
-        break;
-      }
-      if (nxt == j0) break;
-      cur = nxt;
-      cx = __shfl(nx, 0);
-      cy = __shfl(ny, 0);
     }
-    bad |= d > kRing;
-    if (lane < kRing) dst.ring[(size_t)e * kRing + lane] = !bad && lane < d ? mine : -1;
-    if (lane == 0) {
-      dst.deg[e] = bad ? 0 : d;
-      if (bad) atomicOr(p.status, 2);
+  };
+  int j0 = -1, cur, d = 0;
+  double best = 1e300, cx = 0.0, cy = 0.0;
+  visit([&](int k, double dx, double dy) {
+    const double dd = dx * dx + dy * dy;
+    if (j0 < 0 || dd < best || (dd == best && k < j0)) {
+      best = dd;
+      j0 = k;
+      cx = dx;
+      cy = dy;
     }
+  });
+  int* ring = dst.ring + (size_t)e * kRing;
+  bool bad = j0 < 0;
+  cur = j0;
+  while (!bad) {
+    if (d == kRing) {  // (a circle that misses the first neighbour ends here too)
+      bad = true;
+      break;
+    }
+    ring[d++] = cur;
+    WalkMin w;
+    visit([&](int k, double dx, double dy) {
+      const double den = cx * dy - cy * dx;  // perp(d_cur) . d_k
+      if (k != cur && den > 0.0) w.take(k, dx * dx + dy * dy - (cx * dx + cy * dy), den, dx, dy);
+    });
+    bad = w.k < 0;
+    if (w.k == j0) break;
+    cur = w.k;
+    cx = w.x;
+    cy = w.y;
+  }
+  for (int k = bad ? 0 : d; k < kRing; ++k) ring[k] = -1;
+  dst.deg[e] = bad ? 0 : d;
+  if (bad) atomicOr(p.status, 2);
+  return true;
+}
+
+// A short list is walked by a wave a cell, for the shortest chain; a list of more than a
+// tenth of the cells by a thread a cell, for the least work.  Measured (262144 cells,
+// FP64; check, walk and geometry): 5% and 8% of the cells on the list 0.21 ms by waves
+// and 0.40 and 0.23 by threads, 12% 0.34 against 0.29, all 1.3 against 0.4.
+template <typename T>
+__global__ __launch_bounds__(256) void k_mv_walk(PM<T> p, MSet src, MOut dst) {
+  __shared__ int cl[kCand * 256];
+  const int count = *p.count, tid = threadIdx.x;
+  const PM_box box{p.Lx, p.Ly, 1.0 / p.Lx, 1.0 / p.Ly};
+  if (count > p.n / 10) {
+    for (int i0 = blockIdx.x * 256 + (tid & ~63); i0 < count; i0 += gridDim.x * 256) {
+      const int i = i0 + (tid & 63);
+      const int e = i < count ? p.list[i] : -1;
+      const bool more = e >= 0 && !walk_by_thread(p, src, dst, box, e, cl + tid);
+      for (unsigned long long m = __ballot(more); m; m &= m - 1)
+        walk_by_wave(p, src, dst, box, __builtin_amdgcn_readlane(e, __ffsll((long long)m) - 1));
+    }
+  } else {
+    for (int i = blockIdx.x * 4 + (tid >> 6); i < count; i += gridDim.x * 4)
+      walk_by_wave(p, src, dst, box, __builtin_amdgcn_readfirstlane(p.list[i]));
   }
 }
 

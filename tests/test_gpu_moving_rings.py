@@ -202,3 +202,33 @@ def test_lattice_step_time(mv, torch_cuda):
         s.check()
         ms.append(a.elapsed_time(b) / n)
     assert ms[0] < 1.5 * ms[1], ms
+
+
+def test_long_list_with_a_high_degree_cell(mv, torch_cuda, monkeypatch):
+    """A lattice jittered so that every ring is walked, a thread a cell, around a cell with 16
+    neighbours, whose candidates are more than a thread lists."""
+    m, h = 24, 1.0 / 24
+    P = _lattice(m, 3e-10, seed=3)["generators"]
+    c = np.array([0.5, 0.5]) + 0.1 * h
+    ang = 2 * math.pi * (np.arange(16) + np.random.default_rng(4).uniform(-0.05, 0.05, 16)) / 16
+    P = np.concatenate([P[np.linalg.norm(P - c, axis=1) > 4.2 * h], c[None],
+                        c + 2.8 * h * np.stack([np.cos(ang), np.sin(ang)], 1)])
+    n = len(P)
+    d = mv.voronoi(P, (1.0, 1.0))
+    nb = mv.neighbours(d)
+    assert len(nb[n - 17]) == 16
+    assert len(set(nb[n - 17]).union(*(nb[j] for j in nb[n - 17])) - {n - 17}) > 40
+    s = _solver(d)
+    U = s.to_device(_uniform(n))
+    for it in range(3):
+        got = s.geometry()
+        sets = []
+        for tiny in (0.9e-10, 1.1e-10):
+            monkeypatch.setattr(mv, "_TINY_FACE", tiny)
+            sets.append(mv.neighbours(mv.voronoi(got["generators"], (1.0, 1.0))))
+        same = [i for i in range(n) if set(sets[0][i]) == set(sets[1][i])]
+        assert len(same) > 0.7 * n and n - 17 in same
+        for i in same:
+            assert set(got["ring"][i, :got["degree"][i]].tolist()) == set(sets[0][i]), (it, i)
+        U = s.step_mh(U, 2e-3)
+        s.check()

@@ -142,3 +142,31 @@ def test_voronoi_adjoint_at_block_edges(oracle, torch_cuda, n, shuffled, limiter
     s = Solver(mesh, limiter=limiter, gamma=G53)
     lam = s.adjoint_step(s.to_device(U), dt, s.to_device(w)).cpu().numpy()
     assert abs(Jv @ w - v @ lam) <= 1e-12 * np.abs(Jv * w).sum()
+
+
+@pytest.mark.parametrize("mach,aligned,limiter", [(0.2, False, False), (0.2, False, True),
+                                                  (4.0, False, False), (4.0, False, True),
+                                                  (0.1, True, False)])
+@pytest.mark.parametrize("n", [(5, 4), (3, 3, 2)])
+def test_hlld_regions_fp32(oracle, torch_cuda, n, mach, aligned, limiter):
+    """FP32, where every face takes the reverse sweep.  Bar: 32 times what one rounding of the
+    state (three random perturbations of 2^-24 of each value) changes the exact product by, and 32
+    units of rounding; the product of nearly degenerate star states is that sensitive.  (Aligned
+    fields without the limiter, whose decision on the uniform field is one of rounding alone.)"""
+    from paper_1305_5536_amd.solver import Solver, cartesian
+    dim = len(n)
+    lo, hi = (0.0,) * dim, (1.0,) * dim
+    om = oracle.Mesh.cartesian(n, lo, hi)
+    U = _rough(int(np.prod(n)), dim, True, 7 + dim, mach, aligned).astype(np.float32).astype(float)
+    dt = float(np.float32(oracle.cfl_dt(om, U, G53, 0.02, mhd=True)))
+    rng = np.random.default_rng(5)
+    w = rng.standard_normal(U.size).astype(np.float32).astype(float)
+    s = Solver(cartesian(n, lo, hi), physics="mhd", precision="fp32", limiter=limiter, gamma=G53)
+    got = s.adjoint_step(s.to_device(U), dt, s.to_device(w)).cpu().numpy().astype(float)
+    want = _entries(oracle, om, U, dt, w, range(U.size), True, limiter)
+    near = [_entries(oracle, om, U * (1 + 2.0 ** -24 * rng.uniform(-1, 1, U.size)), dt, w,
+                     range(U.size), True, limiter) for _ in range(3)]
+    bar = 32 * max(_error(x, want, dim, True) for x in near) + 32 * 2.0 ** -23
+    err = _error(got, want, dim, True)
+    print(f"HLLD FP32 {n} mach {mach} aligned {aligned} limiter {limiter}: {err:.2e} of {bar:.2e}")
+    assert err < bar

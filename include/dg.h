@@ -280,9 +280,9 @@ dg_status dg_step_mh(dg_mesh_t mesh, const void* U, void* U_next, double dt, con
  * the WENO-type limiter, moving meshes).  lam_n must
  * not alias U, V1 or lam_np1.  Allocates two state-sized workspaces on the
  * first call (kept by the handle), on face lists also four values and four
- * integers per cell, on MHD meshes 7 values per cell and a
- * face table of 256 MiB at most, or of two rows (planes) of cells where those
- * need more. */
+ * integers per cell, on MHD meshes 7 values per cell and a face table of
+ * 256 MiB at most, or of two rows of cells (four in 3D) where those need
+ * more. */
 dg_status dg_adjoint_step(dg_mesh_t mesh, const void* U, const void* V1, double dt,
                           const double* dt_dev, const void* lam_np1, void* lam_n, void* stream);
 

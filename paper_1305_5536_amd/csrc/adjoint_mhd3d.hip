@@ -8,7 +8,8 @@
 // The same two adjoint stages as in two dimensions (stage 2: P = V1,
 // lam = lam', c_id = 1/2, c_L = dt/2; stage 1: P = U, lam = lam_V1, c_id = 1,
 // c_L = dt, extra = lam' with weight 1/2), each the forward limiter (k_lim3d)
-// into a workspace, then, chunk of planes by chunk of planes, without atomics:
+// into a workspace, then chunk by chunk of planes (of rows where two planes are too
+// many for the face table), without atomics:
 //   k_adj3m_face one thread per half face (two of the four Gauss points), each
 //                face once: flux cotangents from the transposed residual weights
 //                of both adjacent cells, one reverse sweep through the HLLD flux
@@ -92,14 +93,15 @@ struct PJ3 {
   const T* lam;
   const T* extra;
   T* out;
-  T* F;            // face table of the planes at hand: [192][nF]
+  T* F;            // face table of the chunk at hand: [192][nF]
   T* msg;          // limiter messages: 6 values a cell
   unsigned* code;  // and their directions
   const double* dt_dev;
   double dt_host;
   double c_id, c_L_over_dt, c_extra;
   int nx, ny, nz, nc;
-  int plane0, planes, nF;  // planes at hand, nF = nx ny (planes + 1)
+  int plane0, planes, cell0, nr;  // chunk at hand: nr cells (whole rows) from cell0 of these planes
+  int nt, nF;  // cells of a plane in the table: one row more where nr < nx ny; nF = nt (planes + 1)
   T gamma, eps;
   T c4h[3], c15[3], cs[3][3], pt[3][3], half[3], q[3], imu[3], ib[4];
 };
@@ -249,26 +251,27 @@ __device__ __forceinline__ void face_adjoint3(const PJ3<T>& p, int eL, int eR, i
   }
 }
 
-// The lower faces of the cells of planes [plane0, plane0 + planes), and the -z
-// faces of the plane above them.  One thread per half face; six half faces of 64
-// consecutive cells are neighbouring workgroups (they share the cells' rows).
+// The lower faces of the chunk's cells, the -z faces of the plane above them and,
+// where the chunk has not all rows, the -y faces of the row above them.  One thread per
+// half face; six half faces of 64 consecutive cells are neighbouring workgroups (they
+// share the cells' rows).
 template <typename T>
 __global__ __launch_bounds__(64) void k_adj3m_face(PJ3<T> p) {
   const int b = blockIdx.x, part = b % 6;
   const int le = (b / 6) * 64 + threadIdx.x;
   if (le >= p.nF) return;
   const int nxy = p.nx * p.ny;
-  const int lp = le / nxy, r = le - lp * nxy;
-  const int j = r / p.nx, i = r - j * p.nx;
-  int k = p.plane0 + lp;
+  const int lp = le / p.nt, r = le - lp * p.nt, i = r % p.nx;
+  int k = p.plane0 + lp, c = p.cell0 + r;  // plane, cell within it
   if (k >= p.nz) k -= p.nz;
-  const int e = k * nxy + r;
+  if (c >= nxy) c -= nxy;
+  const int e = k * nxy + c;
   const int axis = part >> 1, half1 = part & 1;
-  if (axis < 2 && lp == p.planes) return;
+  if ((axis < 2 && lp == p.planes) || (axis != 1 && r >= p.nr)) return;
   if (axis == 0)
     face_adjoint3<T, 0>(p, i == 0 ? e + p.nx - 1 : e - 1, e, half1, le);
   else if (axis == 1)
-    face_adjoint3<T, 1>(p, j == 0 ? e + nxy - p.nx : e - p.nx, e, half1, le);
+    face_adjoint3<T, 1>(p, c < p.nx ? e + nxy - p.nx : e - p.nx, e, half1, le);
   else
     face_adjoint3<T, 2>(p, k == 0 ? e + (p.nz - 1) * nxy : e - nxy, e, half1, le);
 }
@@ -340,22 +343,23 @@ __device__ void volume_adjoint3(const T* ce, const AccBar3<T>& ae, const PJ3<T>&
 template <typename T, bool LIM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 8)))
 void k_adj3m_cell(PJ3<T> p) {
-  const int le = blockIdx.x * 256 + threadIdx.x;
-  const int nxy = p.nx * p.ny;
-  if (le >= nxy * p.planes) return;
-  const int e = p.plane0 * nxy + le;
+  const int lc = blockIdx.x * 256 + threadIdx.x;
+  if (lc >= p.nr * p.planes) return;
+  const int lp = lc / p.nr, r = lc - lp * p.nr;
+  const int e = (p.plane0 + lp) * (p.nx * p.ny) + p.cell0 + r;
   T lw[kNC3];
   {
-    const int i = le % p.nx, j = (le / p.nx) % p.ny;
+    const int lr = r / p.nx, i = r - lr * p.nx;
+    const int le = lp * p.nt + r;
     T g[kNC3];
 #pragma unroll
     for (int k = 0; k < kNC3; ++k) g[k] = T(0);
     add_face3<T, 0, 1>(p, le, g);
     add_face3<T, 0, 0>(p, i == p.nx - 1 ? le - i : le + 1, g);
     add_face3<T, 1, 1>(p, le, g);
-    add_face3<T, 1, 0>(p, j == p.ny - 1 ? le - j * p.nx : le + p.nx, g);
+    add_face3<T, 1, 0>(p, lr == p.ny - 1 ? le - lr * p.nx : le + p.nx, g);
     add_face3<T, 2, 1>(p, le, g);
-    add_face3<T, 2, 0>(p, le + nxy, g);
+    add_face3<T, 2, 0>(p, le + p.nt, g);
     T ce[kNC3], la[kNC3];
     load31(p.W, p.nc, e, ce);
     load31(p.lam, p.nc, e, la);
@@ -515,14 +519,23 @@ PJ3<T> make_adj3_params(const dg_mesh* m, const double* dt_dev, double dt) {
   return p;
 }
 
-// Planes whose face table fits the budget (at least one), shared evenly.
-int chunk_planes(const dg_mesh* m) {
-  const int nz = m->c3.nz;
-  const size_t plane = kFaceVals3 * m->elem * (size_t)m->c3.nx * (size_t)m->c3.ny;
-  const int most =
-      (int)std::min<size_t>((size_t)nz, std::max<size_t>(kAdjFaceBudget / plane, 2) - 1);
-  const int chunks = (nz + most - 1) / most;
-  return (nz + chunks - 1) / chunks;
+// Planes, and rows of them, whose face table fits the budget, shared evenly: whole
+// planes, at least one, or where two planes are over it at least one row of one.
+struct Chunk3 {
+  int planes, rows, rt;
+};
+
+Chunk3 chunk3(const dg_mesh* m) {
+  const int ny = m->c3.ny, nz = m->c3.nz;
+  const size_t row = kFaceVals3 * m->elem * (size_t)m->c3.nx;
+  auto share = [](int n, size_t most) {
+    const int chunks = (int)((n + most - 1) / most);
+    return (n + chunks - 1) / chunks;
+  };
+  const size_t planes = kAdjFaceBudget / (row * ny);
+  if (planes >= 2) return {share(nz, planes - 1), ny, ny};
+  const int rows = share(ny, std::max<size_t>(kAdjFaceBudget / (2 * row), 2) - 1);
+  return {1, rows, rows < ny ? rows + 1 : ny};
 }
 
 template <typename T>
@@ -531,7 +544,7 @@ hipError_t adjoint3_t(const dg_mesh* m, const void* U, const void* V1, const dou
                       void* scratch, hipStream_t s) {
   const bool lim = m->cfg.limiter == DG_LIMITER_MINMOD;
   const PJ3<T> p = make_adj3_params<T>(m, dt_dev, dt);
-  const int chunk = chunk_planes(m), nxy = p.nx * p.ny;
+  const Chunk3 chunk = chunk3(m);
   auto adj_stage = [&](const void* P, const void* lam, const void* extra, double c_id,
                        double c_L_over_dt, double c_extra, void* out) -> hipError_t {
     // W = Pi(P) into ws1; out = Pi_P^T lamW
@@ -553,11 +566,16 @@ hipError_t adjoint3_t(const dg_mesh* m, const void* U, const void* V1, const dou
     a.msg = static_cast<T*>(scratch);
     a.code = reinterpret_cast<unsigned*>(a.msg + (size_t)6 * m->ncells);
     a.F = a.msg + (size_t)7 * m->ncells;
-    for (a.plane0 = 0; a.plane0 < p.nz; a.plane0 += chunk) {
-      a.planes = std::min(chunk, p.nz - a.plane0);
-      a.nF = nxy * (a.planes + 1);
+    for (int c = 0, nr = (p.ny + chunk.rows - 1) / chunk.rows; (c / nr) * chunk.planes < p.nz; ++c) {
+      a.plane0 = (c / nr) * chunk.planes;
+      a.planes = std::min(chunk.planes, p.nz - a.plane0);
+      const int row0 = (c % nr) * chunk.rows, rows = std::min(chunk.rows, p.ny - row0);
+      a.cell0 = p.nx * row0;
+      a.nr = p.nx * rows;
+      a.nt = rows < p.ny ? a.nr + p.nx : a.nr;
+      a.nF = a.nt * (a.planes + 1);
       hipLaunchKernelGGL((k_adj3m_face<T>), dim3(6 * ((a.nF + 63) / 64)), dim3(64), 0, s, a);
-      const dim3 cells((nxy * a.planes + 255) / 256);
+      const dim3 cells((a.nr * a.planes + 255) / 256);
       if (lim)
         hipLaunchKernelGGL((k_adj3m_cell<T, true>), cells, dim3(256), 0, s, a);
       else
@@ -576,8 +594,8 @@ hipError_t adjoint3_t(const dg_mesh* m, const void* U, const void* V1, const dou
 }  // namespace
 
 size_t adjoint_mhd3d_scratch(const dg_mesh* m) {
-  return (7 * (size_t)m->ncells +
-          kFaceVals3 * (size_t)m->c3.nx * (size_t)m->c3.ny * (chunk_planes(m) + 1)) * m->elem;
+  const Chunk3 c = chunk3(m);
+  return (7 * (size_t)m->ncells + kFaceVals3 * (size_t)m->c3.nx * c.rt * (c.planes + 1)) * m->elem;
 }
 
 hipError_t launch_adjoint_mhd3d(const dg_mesh* m, const void* U, const void* V1,

@@ -170,3 +170,29 @@ def test_hlld_regions_fp32(oracle, torch_cuda, n, mach, aligned, limiter):
     err = _error(got, want, dim, True)
     print(f"HLLD FP32 {n} mach {mach} aligned {aligned} limiter {limiter}: {err:.2e} of {bar:.2e}")
     assert err < bar
+
+
+@pytest.mark.parametrize("n", [(310, 303, 1), (331, 290, 2), (45000, 2, 1)])
+def test_flat_mhd_adjoint_in_chunks_of_rows(oracle, torch_cuda, n):
+    """3D meshes of which two planes are over the face table's 256 MiB go chunk by chunk of rows (the
+    last one of single rows): <J v, w> = <v, J^T w>, and the first call takes two states, seven
+    values a cell, the table and no more."""
+    torch = torch_cuda
+    from paper_1305_5536_amd.solver import Solver, cartesian
+    lo, hi = (0.0,) * 3, (1.0,) * 3
+    om = oracle.Mesh.cartesian(n, lo, hi)
+    U = W.random_p1_state(n, lo, hi, G53, seed=3, amp=0.1, mhd=True)
+    dt = oracle.cfl_dt(om, U, G53, 0.3, mhd=True)
+    rng = np.random.default_rng(11)
+    v, w = rng.standard_normal(U.size), rng.standard_normal(U.size)
+    _, Jv = oracle.step_jvp(om, U, v, dt, G53, True, mhd=True)
+    s = Solver(cartesian(n, lo, hi), physics="mhd", gamma=G53)
+    u, lam, out = s.to_device(U), s.to_device(w), s.empty()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    s.adjoint_step(u, dt, lam, out=out)
+    torch.cuda.synchronize()
+    used = free - torch.cuda.mem_get_info()[0]
+    table = max(256 << 20, 4 * n[0] * 192 * 8)
+    assert used <= 8 * (2 * U.size + 7 * int(np.prod(n))) + table + (32 << 20), used
+    assert abs(Jv @ w - v @ out.cpu().numpy()) <= 1e-12 * np.abs(Jv * w).sum()

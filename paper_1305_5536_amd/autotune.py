@@ -7,7 +7,8 @@ add the workgroup size (waves per workgroup) and the grid: one wave per tile,
 or a persistent grid of fewer waves that walk the tile list (tuned by
 coordinate descent: rows, then workgroup size, then grid).  The tuner times one
 SSP-RK2 step (stage 1 + stage 2, HIP events on the current stream) for each
-candidate on the caller's own state and keeps the fastest.  Results are cached
+candidate, the library's own default among them, on the caller's own state and
+keeps the fastest.  Results are cached
 in a JSON file keyed by GPU architecture, mesh shape, physics and precision
 (default ``~/.cache/dgmi/autotune.json``; override with ``DG_AUTOTUNE_CACHE``).
 Results of the solver do not depend on the choice, only its speed.
@@ -20,7 +21,7 @@ import os
 
 import torch
 
-DEFAULT_CANDIDATES = (2, 4, 6, 8, 12, 16, 24, 32, 48, 64)
+DEFAULT_CANDIDATES = (1, 2, 4, 6, 8, 12, 16, 24, 32, 48, 64)
 
 
 def cache_path() -> str:
@@ -71,10 +72,17 @@ def time_step(solver, U, V1, Un, dt, reps: int = 10) -> float:
     return a.elapsed_time(b) * 1e-3 / reps
 
 
+def _own_tiling(solver) -> int:
+    """The library's default for this mesh (the solver is left at it)."""
+    solver.tiling = 0
+    return solver.tiling
+
+
 def autotune(solver, U, shape, candidates=DEFAULT_CANDIDATES, reps: int = 10,
              use_cache: bool = True) -> dict:
     """Pick the fastest rows-per-wave for ``solver`` on state ``U``; returns
-    ``{"rows": r, "times": {r: seconds}}`` and leaves the solver set to r."""
+    ``{"rows": r, "times": {r: seconds}}`` and leaves the solver set to r.  The
+    mesh's default is a candidate unless ``candidates`` is given."""
     key = _key(solver, shape)
     db = _load() if use_cache else {}
     if key in db:
@@ -85,6 +93,8 @@ def autotune(solver, U, shape, candidates=DEFAULT_CANDIDATES, reps: int = 10,
     dt = solver.cfl_dt(U, 0.3).item() * 0.5
     times = {}
     limit = max(shape[-1], 1)
+    if candidates is DEFAULT_CANDIDATES:
+        candidates = dict.fromkeys((_own_tiling(solver), *candidates))
     for r in candidates:
         if r > limit:
             continue
@@ -99,7 +109,7 @@ def autotune(solver, U, shape, candidates=DEFAULT_CANDIDATES, reps: int = 10,
     return entry
 
 
-BATCH_ROWS = (4, 8, 16, 32)
+BATCH_ROWS = (1, 2, 4, 8, 16, 32)  # and the batch's default
 BATCH_WPB = (1, 2, 4)
 BATCH_GRID = (0, 2048, 4096, 8192, 16384)
 
@@ -129,8 +139,8 @@ def autotune_batch(solver, U, sizes, reps: int = 5, use_cache: bool = True) -> d
             times[k] = time_step(solver, U, V1, Un, dt, reps)
         return times[k]
 
-    best = (16, 4, 0)
-    best = min(((r, best[1], best[2]) for r in BATCH_ROWS), key=lambda c: t(*c))
+    rows = dict.fromkeys((_own_tiling(solver), *BATCH_ROWS))
+    best = min(((r, 4, 0) for r in rows), key=lambda c: t(*c))
     best = min(((best[0], w, best[2]) for w in BATCH_WPB), key=lambda c: t(*c))
     best = min(((best[0], best[1], g) for g in BATCH_GRID), key=lambda c: t(*c))
     solver.tiling = best[0]

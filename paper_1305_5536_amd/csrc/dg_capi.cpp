@@ -126,10 +126,9 @@ static int best_rows(int64_t nrows, int64_t most, double c, Waves waves, Load lo
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Waves of the stage kernels, stage 1 + stage 2 in FP64 (two waves per SIMD and
-// one, by registers), two per SIMD in FP32.
-static double load_stages(int64_t waves, bool f64) {
-  const int64_t n = simds();
+// Waves of the stage kernels over n SIMDs, stage 1 + stage 2 in FP64 (two waves per
+// SIMD and one, by registers), two per SIMD in FP32.
+static double load_stages(int64_t waves, int64_t n, bool f64) {
   return f64 ? (double)(ceil_div(waves, 2 * n) + ceil_div(waves, n))
              : load_shared(ceil_div(waves, n), 0.42);
 }
@@ -149,7 +148,8 @@ static int default_batch_rows(const BatchDesc& d, bool f64) {
       n += ceil_div(d.nx[i], 60) * ceil_div(d.ny[i], std::min<int64_t>(r, d.ny[i]));
     return n;
   };
-  return best_rows(ny, 64, 2.2, waves, [&](int64_t w) { return load_stages(w, f64); });
+  const int64_t n = simds();
+  return best_rows(ny, 64, 2.2, waves, [&](int64_t w) { return load_stages(w, n, f64); });
 }
 
 // Rows per wave of the 2D Euler adjoint kernel over all instances: four rows
@@ -195,9 +195,10 @@ static int default_planes3d(int tiles_x, int ny, int64_t nz, bool f64) {
 // 41 against 49 us; 1000x750 FP32 7 rows, 74 us at 5 against 82 at 4).
 static int default_rows_euler2d(int64_t ntiles_x, int64_t nrows, bool f64) {
   if (env_rows()) return (int)std::min<int64_t>(env_rows(), nrows);
+  const int64_t n = simds();
   return best_rows(
       nrows, f64 ? 128 : 64, 2.0, [&](int64_t r) { return ntiles_x * ceil_div(nrows, r); },
-      [&](int64_t w) { return load_stages(w, f64); });
+      [&](int64_t w) { return load_stages(w, n, f64); });
 }
 
 // Rows per wave of the fused 2D Euler step (DG_STEP_ROWS overrides): four rows

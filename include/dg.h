@@ -358,7 +358,9 @@ dg_status dg_cfl_dt_static(dg_mesh_t mesh, const void* U, double cfl, double* dt
  * one workgroup of four row-waves marches through.  0 restores the library
  * default, which a positive DG_TILE_ROWS (stage kernels, batches) or
  * DG_STEP_ROWS (fused 2D Euler step) environment variable replaces for the
- * whole process.
+ * whole process.  The fused step of a small 2D Euler mesh (four rows or more, and
+ * no more strips of 56 columns by four rows than the GPU has CUs, twice that in
+ * FP32) marches no rows and ignores both.
  * Results do not depend on it (every face and cell is computed with the same
  * arithmetic whatever the tiling); only speed does.  Face-list meshes ignore
  * it.  Returns DG_EINVAL for a negative value. */
@@ -387,7 +389,7 @@ dg_status dg_mesh_geometry(dg_mesh_t mesh, double* generators, double* volume, d
                            int32_t* ring, int32_t* degree);
 
 /* Moving meshes (kind 3): on != 0 makes every following dg_step_mh record HIP
- * events on its stream around its four kernels (limiter; mesh of the half-step
+ * events on its stream around its four phases (limiter; mesh of the half-step
  * generators; fluxes and update; mesh of t^{n+1} with the new state and the dt
  * reduction); 0 stops and drops the record.  dg_moving_timing synchronises the
  * device and writes the average duration of each of the four, in ms, over the

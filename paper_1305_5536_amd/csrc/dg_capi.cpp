@@ -84,9 +84,11 @@ int64_t stage_groups3(int tiles_x, int ny);
 // that share a SIMD hide each other's latency, and the launch costs less than
 // that (the load functions below, fitted to sweeps of R).  So few long waves pay
 // on large meshes, where w is set by the mesh, and one row per wave on small
-// ones, which leave SIMDs idle.  The DG_TILE_ROWS environment variable replaces
-// every default below for the whole process (launch-shape experiments;
-// dg_set_tiling, which the autotuner uses, takes precedence over it).
+// ones, which leave SIMDs idle.  The DG_TILE_ROWS environment variable replaces the
+// defaults of the stage kernels, MUSCL-Hancock steps and batches for the whole process
+// (launch-shape experiments; dg_set_tiling, which the autotuner uses, takes precedence
+// over it), DG_STEP_ROWS those of the marching fused step; nothing replaces the rows of
+// the 2D Euler adjoint and the choice of small_step.
 static int64_t simds() {
   int dev = 0, cus = 256;
   if (hipGetDevice(&dev) != hipSuccess ||
@@ -221,9 +223,11 @@ static int default_step_rows(int64_t ntiles_x, int64_t nrows, bool f64) {
 // is a CU for each (224 x 256, 256 workgroups, 22.8 against 32 us; 280 x 224, 280
 // of them, 34.6 against 33.4), FP32 for two rounds (280 x 256 24.1 against 25.6 us,
 // 392 x 292, 511 workgroups, 25.6 against 26.9; 448^2, 896, 38.0 against 35.2).
-// The choice depends on the mesh alone, not on the tiling.  Meshes of fewer rows
-// than a workgroup takes march, though slower (64 x 2 25 against 17 us): a two-row
-// mesh keeps, bit for bit, the results of the thick mesh that repeats it.
+// The choice depends on the mesh alone: the compiler contracts the energy slopes of
+// the two kernels differently, and a tiling must not change results.  Meshes of fewer
+// rows than a workgroup takes march, though slower (64 x 2 25 against 17 us), as the
+// large meshes do, so that a two-row mesh gives the bits of the large mesh that
+// repeats it (small meshes that repeat it round differently).
 static bool small_step(int64_t ntiles_x, int64_t nrows, bool f64) {
   return nrows >= kSmallRows &&
          ntiles_x * ceil_div(nrows, kSmallRows) <= simds() / (f64 ? 4 : 2);

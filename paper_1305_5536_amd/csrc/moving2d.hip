@@ -3,8 +3,9 @@
 //
 // The mesh is the Voronoi tessellation of generators that move with their
 // cell's fluid velocity (mean momentum over mean density, constant over a
-// step).  Every step rebuilds it on the GPU, one thread per cell, with no
-// atomics and no global triangulation:
+// step).  Every step rebuilds it on the GPU, cell by cell, with no global
+// triangulation; the one atomic counts the cells whose ring is not kept (the order in
+// which they are listed varies from run to run, no result depends on it):
 //   * the cell of generator i is the intersection of the half-planes closer to
 //     i than to each candidate j; the candidates are i's neighbours and their
 //     neighbours in the previous mesh (a cell's new neighbours over one CFL
@@ -17,15 +18,15 @@
 //   * each Voronoi vertex is then recomputed as the circumcentre of its three
 //     generators, in the frame of the smallest of the three indices, so that
 //     every cell that shares a vertex or a face derives it from the same
-//     operands (a face's flux is computed by both of its cells; the canonical
-//     operands make the two results agree);
+//     operands (a face between two workgroups of the update is solved by both; the
+//     canonical operands make the two results agree);
 //   * faces shorter than 1e-10 times their generators' distance (four nearly
 //     cocircular generators) are dropped by both cells;
 //   * areas, centroids and second moments (the mass matrix of Sec. 2.2, which
 //     a moving mesh recomputes every step) are the exact polygon moments.
 // A cell whose candidates do not bound it, a polygon beyond the capacities
 // below, or a neighbour that does not list the cell back, latches status bit 2
-// (reported by dg_check).  Every kernel maps its blocks XCD by XCD
+// (reported by dg_check).  The kernels over all cells map their blocks XCD by XCD
 // (xcd_remap): with cells numbered along a space-filling curve each XCD's L2
 // then holds the positions, rings and states of one compact region, which the
 // neighbour gathers reuse.
@@ -1765,7 +1766,7 @@ void moving_set_timing(dg_mesh* m, int on) {
   m->mvd->timing = on != 0;
 }
 
-// Average durations (ms) of the four kernels of the timed steps since the
+// Average durations (ms) of the four phases of the timed steps since the
 // last call, then a fresh record.
 int moving_timing(dg_mesh* m, double* avg_ms, int* nsteps) {
   MVDev& v = *m->mvd;

@@ -340,7 +340,7 @@ class Solver:
         C.check(C.lib().dg_set_mesh_motion(self._h, int(motion)), "dg_set_mesh_motion")
 
     def set_timing(self, on: bool) -> None:
-        """Moving meshes: record HIP events around the four kernels of each step."""
+        """Moving meshes: record HIP events around the four phases of each step."""
         C.check(C.lib().dg_set_moving_timing(self._h, int(bool(on))), "dg_set_moving_timing")
 
     def kernel_times(self):

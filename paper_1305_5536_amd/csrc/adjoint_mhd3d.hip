@@ -101,9 +101,14 @@ struct PJ3 {
   double c_id, c_L_over_dt, c_extra;
   int nx, ny, nz, nc;
   int plane0, planes, cell0, nr;  // chunk at hand: nr cells (whole rows) from cell0 of these planes
-  int nt, nF;  // cells of a plane in the table: one row more where nr < nx ny; nF = nt (planes + 1)
   T gamma, eps;
   T c4h[3], c15[3], cs[3][3], pt[3][3], half[3], q[3], imu[3], ib[4];
+
+  // cells of a plane in the table (one row more where the chunk has not all rows) and
+  // of the table (computed: the FP64 arguments just fill seven cache lines, and an eighth
+  // cost 0.5 us a launch)
+  __host__ __device__ __forceinline__ int nt() const { return nr < nx * ny ? nr + nx : nr; }
+  __host__ __device__ __forceinline__ int nF() const { return nt() * (planes + 1); }
 };
 
 template <typename T>
@@ -242,11 +247,11 @@ __device__ __forceinline__ void face_adjoint3(const PJ3<T>& p, int eL, int eR, i
 #pragma unroll
     for (int k = 0; k < 8; ++k) Fb[k] = fma(s2, F1[k], F0[k]);
     hlld_vjp<T, D>(uL, uR, p.gamma, p.eps, Fb, bL, bR);
-    T* F = p.F + (size_t)(64 * D + 32 * half1 + 8 * half2) * p.nF + le;
+    T* F = p.F + (size_t)(64 * D + 32 * half1 + 8 * half2) * p.nF() + le;
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      F[(size_t)k * p.nF] = bL[k];
-      F[(size_t)(16 + k) * p.nF] = bR[k];
+      F[(size_t)k * p.nF()] = bL[k];
+      F[(size_t)(16 + k) * p.nF()] = bR[k];
     }
   }
 }
@@ -259,9 +264,9 @@ template <typename T>
 __global__ __launch_bounds__(64) void k_adj3m_face(PJ3<T> p) {
   const int b = blockIdx.x, part = b % 6;
   const int le = (b / 6) * 64 + threadIdx.x;
-  if (le >= p.nF) return;
+  if (le >= p.nF()) return;
   const int nxy = p.nx * p.ny;
-  const int lp = le / p.nt, r = le - lp * p.nt, i = r % p.nx;
+  const int lp = le / p.nt(), r = le - lp * p.nt(), i = r % p.nx;
   int k = p.plane0 + lp, c = p.cell0 + r;  // plane, cell within it
   if (k >= p.nz) k -= p.nz;
   if (c >= nxy) c -= nxy;
@@ -282,12 +287,12 @@ template <typename T, int D, int SIDE>
 __device__ __forceinline__ void add_face3(const PJ3<T>& p, int le, T* g) {
   constexpr int t1 = D == 0 ? 1 : 0, t2 = D == 2 ? 1 : 2;
   const T hn = SIDE == 0 ? p.half[D] : -p.half[D];
-  const T* F = p.F + (size_t)(64 * D + 16 * SIDE) * p.nF + le;
+  const T* F = p.F + (size_t)(64 * D + 16 * SIDE) * p.nF() + le;
   T S[8], A[8], B[8];  // sums over the four points, weighted 1, s1, s2
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const T f00 = F[(size_t)k * p.nF], f01 = F[(size_t)(8 + k) * p.nF];
-    const T f10 = F[(size_t)(32 + k) * p.nF], f11 = F[(size_t)(40 + k) * p.nF];
+    const T f00 = F[(size_t)k * p.nF()], f01 = F[(size_t)(8 + k) * p.nF()];
+    const T f10 = F[(size_t)(32 + k) * p.nF()], f11 = F[(size_t)(40 + k) * p.nF()];
     const T lo = f00 + f01, hi = f10 + f11;
     S[k] = lo + hi;
     A[k] = hi - lo;
@@ -350,7 +355,7 @@ void k_adj3m_cell(PJ3<T> p) {
   T lw[kNC3];
   {
     const int lr = r / p.nx, i = r - lr * p.nx;
-    const int le = lp * p.nt + r;
+    const int le = lp * p.nt() + r;
     T g[kNC3];
 #pragma unroll
     for (int k = 0; k < kNC3; ++k) g[k] = T(0);
@@ -359,7 +364,7 @@ void k_adj3m_cell(PJ3<T> p) {
     add_face3<T, 1, 1>(p, le, g);
     add_face3<T, 1, 0>(p, lr == p.ny - 1 ? le - lr * p.nx : le + p.nx, g);
     add_face3<T, 2, 1>(p, le, g);
-    add_face3<T, 2, 0>(p, le + p.nt, g);
+    add_face3<T, 2, 0>(p, le + p.nt(), g);
     T ce[kNC3], la[kNC3];
     load31(p.W, p.nc, e, ce);
     load31(p.lam, p.nc, e, la);
@@ -572,9 +577,7 @@ hipError_t adjoint3_t(const dg_mesh* m, const void* U, const void* V1, const dou
       const int row0 = (c % nr) * chunk.rows, rows = std::min(chunk.rows, p.ny - row0);
       a.cell0 = p.nx * row0;
       a.nr = p.nx * rows;
-      a.nt = rows < p.ny ? a.nr + p.nx : a.nr;
-      a.nF = a.nt * (a.planes + 1);
-      hipLaunchKernelGGL((k_adj3m_face<T>), dim3(6 * ((a.nF + 63) / 64)), dim3(64), 0, s, a);
+      hipLaunchKernelGGL((k_adj3m_face<T>), dim3(6 * ((a.nF() + 63) / 64)), dim3(64), 0, s, a);
       const dim3 cells((a.nr * a.planes + 255) / 256);
       if (lim)
         hipLaunchKernelGGL((k_adj3m_cell<T, true>), cells, dim3(256), 0, s, a);

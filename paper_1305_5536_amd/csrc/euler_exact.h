@@ -75,7 +75,7 @@ template <typename T, int AX>
 __device__ __forceinline__ void exact_flux(const T* uL, const T* uR, T gamma, T* F, bool& bad) {
   constexpr int TX = 1 - AX;
   const T gm1 = gamma - T(1);
-  const T rtol = sizeof(T) == 8 ? T(1e-8) : T(2.449e-4);
+  const T irtol = sizeof(T) == 8 ? T(1e8) : T(4083.3);  // 1 / relative step
   ESide<T> s[2];
   T ut[2];
 #pragma unroll
@@ -109,7 +109,7 @@ __device__ __forceinline__ void exact_flux(const T* uL, const T* uR, T gamma, T*
     if (!(pn > T(0))) pn = T(0.5) * ps;
     const T step = pn - ps;
     ps = pn;
-    if (fabs(step) <= rtol * pn) {
+    if (irtol * fabs(step) <= pn) {
       fL += dfL * step;
       fR += dfR * step;
       conv = true;

@@ -26,15 +26,15 @@
 //                value and a direction) for the neighbour whose mean set the bound;
 // and at last
 //   k_adj2m_msg  each cell adds the messages of its four neighbours.
-// FP64 instruction issue at one wave per SIMD bounds k_adj2m_face (about 1,050
-// vector instructions a sweep, 47% of the issue slots; waves of their own
-// workgroup, since four to a workgroup wait for the slowest: 0.080 against 0.099
-// ms; a two-wave budget spills 300 B a lane, 0.15 ms); memory traffic bounds
-// k_adj2m_cell (400 MB at 5.7 TB/s).  Measured (512^2, FP64, one adjoint stage):
-// faces 0.089, cells 0.070, messages 0.015 ms; one thread per cell solving each
+// One wave per SIMD bounds k_adj2m_face (about 1,050 vector instructions a sweep in
+// 38% of the issue slots, 17% of a wave's cycles waiting for data and 29% for an
+// instruction to issue; waves of their own workgroup, since four to a workgroup wait
+// for the slowest: 0.080 against 0.099 ms; a two-wave budget spills 300 B a lane, 0.15
+// ms); memory traffic bounds k_adj2m_cell (400 MB at 5.8 TB/s).  Measured (512^2, FP64,
+// one adjoint stage): faces 0.086, cells 0.069, messages 0.014 ms; one thread per cell solving each
 // face from both sides 0.168 + 0.030 + 0.011 ms; with a forward-mode solve per
 // state component and every limiter that reads a cell differentiated, component
-// by component, 0.901 + 0.410 ms.  The adjoint step 2.59 -> 0.37 ms.
+// by component, 0.901 + 0.410 ms.  The adjoint step 2.59 -> 0.38 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

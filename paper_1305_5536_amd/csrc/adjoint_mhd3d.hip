@@ -21,14 +21,14 @@
 //                transpose of its own limiter, with a message per limited variable
 //                for the neighbour whose mean set the bound;
 // and at last k_adj3m_msg, in which each cell adds its neighbours' messages.
-// FP64 instruction issue at one wave per SIMD bounds k_adj3m_face, the traffic of
+// One wave per SIMD bounds k_adj3m_face (39% of the issue slots), the traffic of
 // the face table k_adj3m_cell (two waves per SIMD at 84 B spilled a lane: 0.144
 // against 0.162 ms without).  The chunks' tables take 256 MiB (64^3, one stage:
 // two chunks 0.45 ms; five of 96 MiB 0.49; one of 600 MiB 0.46).  Measured (64^3,
 // FP64, one adjoint stage): faces 0.28, cells 0.14, messages 0.013 ms; one thread
 // per cell solving each face from both sides 0.98 + 0.05 ms; with a forward-mode
 // solve per state component and every limiter that reads a cell differentiated
-// 3.55 + 0.77 ms.  The adjoint step 8.77 -> 0.92 ms.
+// 3.55 + 0.77 ms.  The adjoint step 8.77 -> 0.90 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -576,7 +576,7 @@ __device__ __forceinline__ void nearest_image(const PM_box& b, double& dx, doubl
 // The vertices and neighbours stay in registers; a candidate costs kFast comparisons
 // of its index and kFast products, no list and no dependent scan.  The latency of its
 // three gathers (ring, neighbours' rings, positions) bounds it.  Measured (262144
-// cells, FP64): 0.066 ms, and 0.015 ms for the walk of the listed cells; walking
+// cells, FP64): 0.064 ms, and 0.015 ms for the walk of the listed cells; walking
 // every cell, one thread each over a list of its candidates in LDS, took 0.177
 // ms, its dependent scans (one of all candidates per face) bound by latency.
 template <typename T>
@@ -1193,8 +1193,8 @@ __device__ __forceinline__ void load_pred(const PM<T>& p, int e, Pred<T>& w, T& 
 // one of several between the same pair (small periodic meshes), is solved by the
 // cells that have it.  Two waves per SIMD, which is what the exact solver's 253
 // registers in FP64 allow: with one the gathers are not hidden behind the divergent
-// Newton loops.  Measured (262144 cells, FP64, exact solver): 0.164 ms, 12.2
-// thousand vector instructions a wave (88 us of issue; the rest is the latency of
+// Newton loops.  Measured (262144 cells, FP64, exact solver): 0.149 ms, 11.7
+// thousand vector instructions a wave (80 us of issue; the rest is the latency of
 // each pass's gathers and its slowest Newton solve), against 0.236 ms and 21.7
 // thousand with a thread per cell that walks its ring.
 constexpr int kUpd = 256;

@@ -107,8 +107,11 @@ static int env_rows() {
 }
 
 // Relative cost of w waves on one SIMD: `pair` for two that run together, the
-// pairs one after the other; or each further wave at `more` of the first.
-static double load_pairs(int64_t w, double pair) { return (double)(w / 2) * pair + (double)(w % 2); }
+// pairs one after the other, and `odd` for one beyond them; or each further wave at
+// `more` of the first.
+static double load_pairs(int64_t w, double pair, double odd = 1.0) {
+  return w == 1 ? 1.0 : (double)(w / 2) * pair + (double)(w % 2) * odd;
+}
 static double load_shared(int64_t w, double more) { return 1.0 + more * (double)(w - 1); }
 
 // The R in [1, most] with the least (R + c) load(waves(R)).
@@ -128,11 +131,17 @@ static int best_rows(int64_t nrows, int64_t most, double c, Waves waves, Load lo
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Waves of the stage kernels over n SIMDs, stage 1 + stage 2 in FP64 (two waves per
-// SIMD and one, by registers), two per SIMD in FP32.
-static double load_stages(int64_t waves, int64_t n, bool f64) {
-  return f64 ? (double)(ceil_div(waves, 2 * n) + ceil_div(waves, n))
-             : load_shared(ceil_div(waves, n), 0.42);
+// Waves of the FP64 stage kernels over n SIMDs: stage 1 runs two waves per SIMD, stage 2
+// and MUSCL-Hancock one (by registers), and a pair takes 1.7 times one wave over all of
+// them.  The 1.7 and the three rows beyond a wave's own (kStageRows64) are fitted to 72
+// mesh shapes of 6e3 to 7.5e6 cells and 16 batches, each at all rows: less than 1% above
+// the best row of each on average.  With 1.5 and two rows it was 6%, up to a quarter, on
+// meshes that just fill the chip: 700 x 500 (both stages, MUSCL-Hancock) three rows 59.7
+// and 32.7 us against 54.2 and 27.5 at six, 400 x 900 four rows 67.6 and 37.1 against 58.9
+// and 30.0 at seven.
+constexpr double kStageRows64 = 3.0;
+static double load_stages64(int64_t waves, int64_t n) {
+  return load_pairs(ceil_div(waves, n), 1.7);
 }
 
 // Rows per tile of every instance of a batch (stage kernels).  Measured (RK2
@@ -151,7 +160,9 @@ static int default_batch_rows(const BatchDesc& d, bool f64) {
     return n;
   };
   const int64_t n = simds();
-  return best_rows(ny, 64, 2.2, waves, [&](int64_t w) { return load_stages(w, n, f64); });
+  return best_rows(ny, 64, f64 ? kStageRows64 : 2.2, waves, [&](int64_t w) {
+    return f64 ? load_stages64(w, n) : load_shared(ceil_div(w, n), 0.42);
+  });
 }
 
 // Rows per wave of the 2D Euler adjoint kernel over all instances: four rows
@@ -194,13 +205,21 @@ static int default_planes3d(int tiles_x, int ny, int64_t nz, bool f64) {
 // (2048^2 FP64: 36 rows, 1995 waves, one round of stage 1 and two of stage 2.
 // MUSCL-Hancock with the exact flux and WENO: 64^2 one row, 37 against 90 us at
 // the 4 rows that were the least before, FP32 17 against 34; 512^2 FP32 5 rows
-// 41 against 49 us; 1000x750 FP32 7 rows, 74 us at 5 against 82 at 4).
+// 41 against 49 us; 1000x750 FP32 7 rows, 74 us at 5 against 82 at 4).  In FP32 a pair
+// of waves on a SIMD takes 1.05 of one and a third 0.6 more; where that many rows a wave
+// leave it seven or more, 4096 waves, two full rounds of two per SIMD, are the faster
+// choice (3182 x 750 ten rows 153 against 167 us at eight; 53 shapes, HLL and exact: 0.8%
+// above the best row on average, 3.2% with 0.42 a further wave and two rows).
 static int default_rows_euler2d(int64_t ntiles_x, int64_t nrows, bool f64) {
   if (env_rows()) return (int)std::min<int64_t>(env_rows(), nrows);
-  const int64_t n = simds();
-  return best_rows(
-      nrows, f64 ? 128 : 64, 2.0, [&](int64_t r) { return ntiles_x * ceil_div(nrows, r); },
-      [&](int64_t w) { return load_stages(w, n, f64); });
+  const int64_t n = simds(), full = ceil_div(ntiles_x * nrows, 4 * n);
+  auto waves = [&](int64_t r) { return ntiles_x * ceil_div(nrows, r); };
+  if (f64)
+    return best_rows(nrows, 128, kStageRows64, waves,
+                     [&](int64_t w) { return load_stages64(w, n); });
+  if (full >= 7) return (int)std::min(std::min<int64_t>(full, 64), nrows);
+  return best_rows(nrows, 64, 0.5, waves,
+                   [&](int64_t w) { return load_pairs(ceil_div(w, n), 1.05, 0.6); });
 }
 
 // Rows per wave of the fused 2D Euler step (DG_STEP_ROWS overrides): four rows
@@ -239,14 +258,15 @@ static bool small_step(int64_t ntiles_x, int64_t nrows, bool f64) {
 // 0.148 at 2 rows; 2048^2: 24 rows, 1.39 against 1.43 ms; 128^2: one row, 34
 // against 47 us at 2).  FP32 three waves per SIMD, which hide each other's
 // latency (2048^2: 9 rows, 0.760 ms against 0.773 with 24; 128^2: one row, 27
-// against 37 us at 2).
+// against 37 us at 2; 950 x 281 two rows 75 against 80 us at five; 35 shapes: 1.1% above
+// the best row on average, 4.5% with a further wave at 0.5 of the first).
 static int default_rows_mhd2d(int64_t ntiles_x, int64_t nrows, bool f64) {
   if (env_rows()) return (int)std::min<int64_t>(env_rows(), nrows);
   const int64_t n = simds();
   return best_rows(
       nrows, 32, f64 ? 3.0 : 1.2, [&](int64_t r) { return ntiles_x * ceil_div(nrows, r); },
       [&](int64_t w) {
-        return f64 ? (double)ceil_div(w, n) : load_shared(ceil_div(w, n), 0.5);
+        return f64 ? (double)ceil_div(w, n) : load_shared(ceil_div(w, n), 0.45);
       });
 }
 

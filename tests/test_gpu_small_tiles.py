@@ -112,3 +112,20 @@ def test_fused_step_of_a_small_mesh_matches_the_stage_pair(torch_cuda, shape, li
         assert (a[k] - b[k]).abs().max() <= tol * scale * (1 if k % 3 == 0 else max(shape))
     want = s.cfl_dt(out, 0.2)
     assert abs(float(nxt) - float(want)) <= tol * float(want)
+
+
+@pytest.mark.parametrize("n,physics,precision,rows", [
+    ((700, 500), "euler", "fp64", 6), ((400, 900), "euler", "fp64", 7),
+    ((8, 4096), "euler", "fp64", 4), ((300, 300), "euler", "fp64", 2),
+    ((2048, 2048), "euler", "fp64", 36), ((3182, 750), "euler", "fp32", 10),
+    ((1000, 750), "euler", "fp32", 7), ((950, 281), "mhd", "fp32", 2),
+    ((512, 512), "mhd", "fp64", 5)])
+def test_default_rows(torch_cuda, n, physics, precision, rows):
+    """Default rows on 256 CUs: the fastest of all rows, measured, on meshes that just fill the
+    chip, where a round of waves more or less decides, and on small and large ones."""
+    from paper_1305_5536_amd.solver import Solver, cartesian
+    if torch_cuda.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("rows of another chip")
+    s = Solver(cartesian(n, (0.0, 0.0), (1.0, 1.0)), physics=physics, precision=precision, gamma=G53)
+    assert s.tiling == rows
+    s.close()
